@@ -94,24 +94,18 @@ constexpr int kTunedCells[8][3] = {{
 TILE_TABLE = os.path.join(HERE, "csrc", "tile_table.h")
 # candidate values of each tile constant (see csrc/tile_table.h)
 TILE_SPACE = {
-    "EMT_COUNT_PIECE": (2, 3, 4),
-    "EMT_COUNT_LANE_PIECES": (16, 24, 32),
-    "EMT_COUNT_FETCH": (5, 6, 8),
-    "EMT_COUNT_REFILL": (24, 32, 48),
-    "EMT_FLUSH_UNROLL": (1, 2),
-    "EMT_CHUNK_SEEDS": (64, 128, 256),
-    "EMT_COUNT_BLOCKS": (1024, 2048),
-    "EMT_COUNT_OCCUPANCY": (4, 5),
+    "EMT_COUNT_FETCH": (4, 6, 8),
+    "EMT_CHUNK_SEEDS": (512, 1024, 2048),
+    "EMT_COUNT_THREADS": (256, 512),
+    "EMT_COUNT_BLOCKS": (512, 1024),
+    "EMT_COUNT_OCCUPANCY": (4, 6, 8),
     "EMT_MERGE_WIDE": (12, 16),
     "EMT_CELLS_PER_GRAIN": (4, 8),
 }
 TILE_COMMENTS = {
-    "EMT_COUNT_PIECE": "grains a flush lane tests per queue entry",
-    "EMT_COUNT_LANE_PIECES": "queue entries a lane adds per step",
-    "EMT_COUNT_FETCH": "cell pencils a lane fetches per step",
-    "EMT_COUNT_REFILL": "lanes waiting for a seed before a wave refills",
-    "EMT_FLUSH_UNROLL": "queue words a flush trip loads before testing",
-    "EMT_CHUNK_SEEDS": "seeds a wave takes at a time (single views)",
+    "EMT_COUNT_FETCH": "slabs a lane walks per step",
+    "EMT_CHUNK_SEEDS": "seeds a workgroup takes at a time",
+    "EMT_COUNT_THREADS": "threads of a counting workgroup",
     "EMT_COUNT_BLOCKS": "workgroups of the counting kernel",
     "EMT_COUNT_OCCUPANCY": "waves per SIMD the counting kernel is compiled for",
     "EMT_MERGE_WIDE": "grid-wide merge rounds at most before the per-view tails",
@@ -141,14 +135,6 @@ def write_tiles(path: str, tiles: dict, summary: str) -> None:
 #define EMT_TILE_TABLE_H
 
 {body}
-
-// queue capacities that follow from the above
-#ifndef EMT_COUNT_PIECE_CAP
-#define EMT_COUNT_PIECE_CAP (128 * EMT_COUNT_LANE_PIECES)
-#endif
-#ifndef EMT_COUNT_RUN_CAP
-#define EMT_COUNT_RUN_CAP (64 * EMT_COUNT_FETCH)
-#endif
 
 #endif
 """

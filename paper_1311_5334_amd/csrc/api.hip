@@ -21,6 +21,7 @@
 #include "cell_table.h"
 #include "emt_dev.h"
 #include "emt_host.h"
+#include "line_table.h"
 
 using namespace emt;
 
@@ -59,9 +60,8 @@ struct emt_ctx {
     DevArena stack_buf;  // grain recognition: stack copy, block counts, scan, output
     uint32_t *h_small = nullptr;  // pinned: two words exchanged with the device
     DevPtrs d{};
-    // capacities the buffers currently hold
-    uint32_t cap_n = 0, cap_cells = 0, cap_views = 0, cap_cand = 0, cap_mem = 0;
-    unsigned long long cap_seeds = 0;
+    // capacities the buffers currently hold (nc: line classes)
+    Caps held_caps{};
     // capacities learned from earlier calls
     double seeds_per_grain = 256.0, cand_per_grain = 8.0, mem_per_cand = 24.0;
     // grid-wide merge rounds for the next call: two more than the last call
@@ -243,161 +243,217 @@ int mapped(emt_ctx *ctx, T *&host, T *&dev, size_t &cap, size_t n) {
 
 // Device bytes of each arena for a capacity (ensure carves them in this
 // layout).
-size_t grain_bytes(size_t n) {
-    return bytes_of<int32_t>(3 * n) + 4 * bytes_of<uint32_t>(n) + bytes_of<uint32_t>(n + 1) +
-           2 * bytes_of<int4>(n + kSortedSpare) + bytes_of<unsigned long long>(n);
+size_t grain_bytes(size_t n, int nc) {
+    return bytes_of<int32_t>(3 * n) + 3 * bytes_of<uint32_t>(n) + bytes_of<uint32_t>(nc * n + 1) +
+           bytes_of<int4>(n + kSortedSpare) + bytes_of<unsigned long long>(n);
 }
 size_t seed_bytes(size_t n) {
     return bytes_of<uint2>(n) + bytes_of<uint32_t>(n) + bytes_of<uint32_t>(n / 32 + 1) +
            bytes_of<uint32_t>(n / 32 + 2);
 }
-size_t cand_bytes(size_t n) {
+// The tracks, written by the fit, share their memory with the line classes'
+// orders, and the fit's orders and the result grains share theirs with the
+// records and list words: the seed, counting and listing kernels are done with
+// them by then.
+size_t order_bytes(size_t n_total, size_t n_views, int nc) {
+    return bytes_of<float4>(3 * n_total) + bytes_of<uint32_t>(3 * (n_total + n_views)) +
+           2 * bytes_of<uint32_t>(nc * n_total);
+}
+size_t line_bytes(size_t n_total, int nc) {
+    return bytes_of<uint2>(line_recs(nc) * n_total) +
+           bytes_of<uint2>((size_t)kLineEnt * nc * n_total);
+}
+size_t cand_bytes(size_t n, size_t n_total, size_t n_views, int nc) {
     return bytes_of<Cand>(n) + bytes_of<unsigned long long>(n) + 4 * bytes_of<uint32_t>(n + 1) +
-           7 * bytes_of<uint32_t>(n) + bytes_of<uint8_t>(n) + bytes_of<emt_track>(n);
+           7 * bytes_of<uint32_t>(n) + bytes_of<uint8_t>(n) +
+           std::max(bytes_of<emt_track>(n), order_bytes(n_total, n_views, nc));
 }
-size_t mem_bytes(size_t n) {
-    return 3 * bytes_of<uint32_t>(n) + bytes_of<uint8_t>(n) + bytes_of<long long>(n);
+size_t mem_bytes(size_t n, size_t n_total, int nc) {
+    return bytes_of<uint32_t>(n) + bytes_of<uint8_t>(n) +
+           std::max(2 * bytes_of<uint32_t>(n) + bytes_of<long long>(n), line_bytes(n_total, nc));
 }
-size_t cell_bytes(size_t n) {
-    return 2 * bytes_of<uint32_t>(n) + bytes_of<uint32_t>(scan_scratch_words((uint32_t)n));
-}
-size_t view_bytes(size_t n) {
-    return bytes_of<ViewGrid>(n) + bytes_of<unsigned long long>(n) + 5 * bytes_of<uint32_t>(n + 1) +
-           bytes_of<Counters>(1) + bytes_of<uint32_t>((size_t)max_merge_rounds()) +
-           bytes_of<uint32_t>(kGrabWords) + bytes_of<unsigned long long>(kPartWords) +
-           bytes_of<BatchDesc>(1);
+size_t view_bytes(size_t n, int nc) {
+    return bytes_of<ViewGrid>(n) + bytes_of<LineGrid>(2 * n) + bytes_of<uint32_t>(2 * nc * n) +
+           bytes_of<uint32_t>(n) + bytes_of<unsigned long long>(n) +
+           5 * bytes_of<uint32_t>(n + 1) + bytes_of<Counters>(1) +
+           bytes_of<uint32_t>((size_t)max_merge_rounds()) + bytes_of<uint32_t>(kGrabWords) +
+           bytes_of<unsigned long long>(kPartWords) + bytes_of<BatchDesc>(1);
 }
 // the scan scratch serves every scan: cells, anchors, seeds, candidates
-uint32_t scan_words(const Caps &c) {
+uint32_t scan_words(const Caps &c, int nc) {
     return std::max<uint32_t>(std::max<uint32_t>(c.n_cells, c.cand_cap),
-                              std::max<uint32_t>((uint32_t)(c.seed_cap / 32 + 1), c.n_total)) + 1;
+                              std::max<uint32_t>((uint32_t)(c.seed_cap / 32 + 1),
+                                                 (uint32_t)nc * c.n_total)) + 1;
+}
+size_t scan_bytes(size_t n_cells, size_t n_scan) {
+    return 2 * bytes_of<uint32_t>(n_cells) +
+           bytes_of<uint32_t>(scan_scratch_words((uint32_t)n_scan));
+}
+
+// Sizes the arenas are carved for.
+struct ArenaSizes {
+    size_t grain, seed, cand, mem, cell, view;
+    size_t total() const { return grain + seed + cand + mem + cell + view; }
+};
+ArenaSizes arena_sizes(const Caps &c, int nc) {
+    return {grain_bytes(c.n_total, nc), seed_bytes(c.seed_cap),
+            cand_bytes(c.cand_cap, c.n_total, c.n_views, nc), mem_bytes(c.mem_cap, c.n_total, nc),
+            scan_bytes(c.n_cells, scan_words(c, nc)), view_bytes(c.n_views, nc)};
+}
+
+// Line classes the tables hold: more slope bins make the lines of a class
+// more alike, so fewer grains are tested, and take more memory (118 bytes per
+// grain and class, part of it shared). The most that the budget has room for
+// beside everything else; three classes need no more memory than the buffers
+// they share.
+constexpr int kLineChoices[] = {kLineClasses, 12, 3};
+
+bool same_caps(const Caps &a, const Caps &b) {
+    return a.n_total == b.n_total && a.n_views == b.n_views && a.n_cells == b.n_cells &&
+           a.max_view_n == b.max_view_n && a.seed_cap == b.seed_cap &&
+           a.cand_cap == b.cand_cap && a.mem_cap == b.mem_cap &&
+           a.wide_rounds == b.wide_rounds && a.nc == b.nc;
 }
 
 // Make every buffer hold the capacities in c, carve the pointer table, and
-// raise c to what the buffers hold.
+// raise c to what the buffers hold. The arenas only grow, so c is first raised
+// to the capacities held; they are carved again whenever one changes.
 int ensure(emt_ctx *ctx, Caps &c) {
     int rc;
     DevPtrs &d = ctx->d;
-    if (c.n_total > ctx->cap_n || !ctx->grain_buf.p) {
-        const size_t n = std::max<uint32_t>(c.n_total, 1024);
-        const size_t b = grain_bytes(n);
-        if ((rc = arena(ctx, ctx->grain_buf, b))) return rc;
+    Caps h = ctx->held_caps;
+    h.n_total = std::max({h.n_total, c.n_total, 1024u});
+    h.seed_cap = std::max(h.seed_cap, c.seed_cap);
+    h.cand_cap = std::max(h.cand_cap, c.cand_cap);
+    h.mem_cap = std::max(h.mem_cap, c.mem_cap);
+    h.n_cells = std::max({h.n_cells, c.n_cells, 1u << 16});
+    h.n_views = std::max({h.n_views, c.n_views, 64u});
+    DevArena *const arenas[] = {&ctx->grain_buf, &ctx->seed_buf, &ctx->cand_buf,
+                                &ctx->mem_buf, &ctx->cell_buf, &ctx->view_buf};
+    size_t others = ctx->held;
+    for (const DevArena *a : arenas) others -= a->bytes;
+    ArenaSizes z{};
+    for (int nc : kLineChoices) {
+        h.nc = nc;
+        z = arena_sizes(h, nc);
+        const size_t want[] = {z.grain, z.seed, z.cand, z.mem, z.cell, z.view};
+        size_t sum = others;
+        for (int i = 0; i < 6; ++i) sum += std::max(want[i], arenas[i]->bytes);
+        if (sum <= ctx->budget) break;
+    }
+    if (!same_caps(h, ctx->held_caps)) {
+        const size_t want[] = {z.grain, z.seed, z.cand, z.mem, z.cell, z.view};
+        ctx->held_caps = Caps{};  // nothing is held until all of them are
+        for (int i = 0; i < 6; ++i)
+            if ((rc = arena(ctx, *arenas[i], want[i]))) return rc;
+        if (h.n_views > ctx->h_views_cap) {
+            // matching pinned staging of the view table
+            size_t cap = 0;
+            if (ctx->h_grids) {
+                (void)hipHostFree(ctx->h_grids);
+                ctx->h_grids = nullptr;
+                ctx->h_views_cap = 0;
+            }
+            if ((rc = pinned(ctx, ctx->h_grids, cap, h.n_views))) return rc;
+            ctx->h_views_cap = h.n_views;
+        }
+        ctx->held_caps = h;
+        ctx->gen++;  // pointers move, within the arenas at least
+        const size_t n = h.n_total, nv = h.n_views, nc = (size_t)h.nc;
+        d.nc = h.nc;
         char *p = (char *)ctx->grain_buf.p;
         d.xyz = carve<int32_t>(p, 3 * n);
         d.view_of = carve<uint32_t>(p, n);
         d.cell_of = carve<uint32_t>(p, n);
         d.rank = carve<uint32_t>(p, n);
-        d.seed_cnt = carve<uint32_t>(p, n);
-        d.seed_off = carve<uint32_t>(p, n + 1);
+        d.seed_off = carve<uint32_t>(p, nc * n + 1);
         d.sg = carve<int4>(p, n + kSortedSpare);
-        d.sgf = carve<float4>(p, n + kSortedSpare);
         d.owner = carve<unsigned long long>(p, n);
-        ctx->cap_n = (uint32_t)n;
-    }
-    if (c.seed_cap > ctx->cap_seeds || !ctx->seed_buf.p) {
-        const size_t n = c.seed_cap;
-        const size_t b = seed_bytes(n);
-        if ((rc = arena(ctx, ctx->seed_buf, b))) return rc;
-        char *p = (char *)ctx->seed_buf.p;
-        d.seeds = carve<uint2>(p, n);
-        d.seed_n = carve<uint32_t>(p, n);
-        d.pass = carve<uint32_t>(p, n / 32 + 1);
-        d.pass_pos = carve<uint32_t>(p, n / 32 + 2);
-        ctx->cap_seeds = c.seed_cap;
-    }
-    if (c.cand_cap > ctx->cap_cand || !ctx->cand_buf.p) {
-        const size_t n = c.cand_cap;
-        const size_t b = cand_bytes(n);
-        if ((rc = arena(ctx, ctx->cand_buf, b))) return rc;
-        char *p = (char *)ctx->cand_buf.p;
-        d.cand = carve<Cand>(p, n);
-        d.key = carve<unsigned long long>(p, n);
-        d.cand_n = carve<uint32_t>(p, n + 1);
-        d.cand_thr = carve<uint32_t>(p, n);
-        d.mem_off = carve<uint32_t>(p, n + 1);
-        d.tg_n = carve<uint32_t>(p, n + 1);
-        d.tg_off = carve<uint32_t>(p, n + 1);
-        d.mcount = carve<uint32_t>(p, n);
-        d.act = carve<uint32_t>(p, n);
-        d.act2 = carve<uint32_t>(p, n);
-        d.acc = carve<uint32_t>(p, n);
-        d.grouped = carve<uint32_t>(p, n);
-        d.track_cand = carve<uint32_t>(p, n);
-        d.status = carve<uint8_t>(p, n);
-        d.tracks = carve<emt_track>(p, n);
-        ctx->cap_cand = (uint32_t)n;
-    }
-    if (c.mem_cap > ctx->cap_mem || !ctx->mem_buf.p) {
-        const size_t n = c.mem_cap;
-        const size_t b = mem_bytes(n);
-        if ((rc = arena(ctx, ctx->mem_buf, b))) return rc;
-        char *p = (char *)ctx->mem_buf.p;
-        d.members = carve<uint32_t>(p, n);
-        d.tord = carve<uint32_t>(p, n);
-        d.out_grains = carve<uint32_t>(p, n);
-        d.taken = carve<uint8_t>(p, n);
-        d.tvals = carve<long long>(p, n);
-        ctx->cap_mem = (uint32_t)n;
-    }
-    c.seed_cap = std::max<unsigned long long>(c.seed_cap, ctx->cap_seeds);
-    c.cand_cap = std::max(c.cand_cap, ctx->cap_cand);
-    c.mem_cap = std::max(c.mem_cap, ctx->cap_mem);
-    const uint32_t scan_cap = scan_words(c);
-    if (scan_cap > ctx->cap_cells || !ctx->cell_buf.p) {
-        const size_t n = std::max<uint32_t>(scan_cap, 1u << 16);
-        const size_t b = cell_bytes(n);
-        if ((rc = arena(ctx, ctx->cell_buf, b))) return rc;
-        char *p = (char *)ctx->cell_buf.p;
-        d.cell_count = carve<uint32_t>(p, n);
-        d.cell_start = carve<uint32_t>(p, n);
-        d.scan_part = carve<uint32_t>(p, scan_scratch_words((uint32_t)n));
-        ctx->cap_cells = (uint32_t)n;
-    }
-    if (c.n_views > ctx->cap_views || !ctx->view_buf.p) {
-        const size_t n = std::max<uint32_t>(c.n_views, 64);
-        const size_t b = view_bytes(n);
-        if ((rc = arena(ctx, ctx->view_buf, b))) return rc;
-        char *p = (char *)ctx->view_buf.p;
-        d.grids = carve<ViewGrid>(p, n);
-        d.view_seeds = carve<unsigned long long>(p, n);
-        d.view_cand = carve<uint32_t>(p, n + 1);
-        d.view_ntr = carve<uint32_t>(p, n + 1);
-        d.view_tr_off = carve<uint32_t>(p, n + 1);
-        d.view_cursor = carve<uint32_t>(p, n + 1);
-        d.view_tail = carve<uint32_t>(p, n + 1);
+
+        p = (char *)ctx->seed_buf.p;
+        d.seeds = carve<uint2>(p, h.seed_cap);
+        d.seed_n = carve<uint32_t>(p, h.seed_cap);
+        d.pass = carve<uint32_t>(p, h.seed_cap / 32 + 1);
+        d.pass_pos = carve<uint32_t>(p, h.seed_cap / 32 + 2);
+
+        const size_t k = h.cand_cap;
+        p = (char *)ctx->cand_buf.p;
+        d.cand = carve<Cand>(p, k);
+        d.key = carve<unsigned long long>(p, k);
+        d.cand_n = carve<uint32_t>(p, k + 1);
+        d.cand_thr = carve<uint32_t>(p, k);
+        d.mem_off = carve<uint32_t>(p, k + 1);
+        d.tg_n = carve<uint32_t>(p, k + 1);
+        d.tg_off = carve<uint32_t>(p, k + 1);
+        d.mcount = carve<uint32_t>(p, k);
+        d.act = carve<uint32_t>(p, k);
+        d.act2 = carve<uint32_t>(p, k);
+        d.acc = carve<uint32_t>(p, k);
+        d.grouped = carve<uint32_t>(p, k);
+        d.track_cand = carve<uint32_t>(p, k);
+        d.status = carve<uint8_t>(p, k);
+        char *q = p;
+        d.lsg = carve<float4>(q, 3 * n);
+        d.lkey = carve<uint32_t>(q, 3 * (n + nv));
+        d.seed_cnt = carve<uint32_t>(q, nc * n);
+        d.lrank = carve<uint32_t>(q, nc * n);
+        d.tracks = carve<emt_track>(p, k);
+
+        const size_t m = h.mem_cap;
+        p = (char *)ctx->mem_buf.p;
+        d.members = carve<uint32_t>(p, m);
+        d.taken = carve<uint8_t>(p, m);
+        q = p;
+        d.lrec = carve<uint2>(q, line_recs(h.nc) * n);
+        d.lent = carve<uint2>(q, (size_t)kLineEnt * nc * n);
+        d.tord = carve<uint32_t>(p, m);
+        d.out_grains = carve<uint32_t>(p, m);
+        d.tvals = carve<long long>(p, m);
+
+        p = (char *)ctx->cell_buf.p;
+        d.cell_count = carve<uint32_t>(p, h.n_cells);
+        d.cell_start = carve<uint32_t>(p, h.n_cells);
+        d.scan_part = carve<uint32_t>(p, scan_scratch_words(scan_words(h, h.nc)));
+
+        p = (char *)ctx->view_buf.p;
+        d.grids = carve<ViewGrid>(p, nv);
+        d.lines = carve<LineGrid>(p, 2 * nv);
+        d.lpool = carve<uint32_t>(p, 2 * nc * nv);
+        d.lcoarse = carve<uint32_t>(p, nv);
+        d.view_seeds = carve<unsigned long long>(p, nv);
+        d.view_cand = carve<uint32_t>(p, nv + 1);
+        d.view_ntr = carve<uint32_t>(p, nv + 1);
+        d.view_tr_off = carve<uint32_t>(p, nv + 1);
+        d.view_cursor = carve<uint32_t>(p, nv + 1);
+        d.view_tail = carve<uint32_t>(p, nv + 1);
         d.cnt = carve<Counters>(p, 1);
         d.undecided = carve<uint32_t>(p, (size_t)max_merge_rounds());
         d.grab = carve<uint32_t>(p, kGrabWords);
         d.part64 = carve<unsigned long long>(p, kPartWords);
         d.desc = carve<BatchDesc>(p, 1);
-        ctx->cap_views = (uint32_t)n;
-        // matching pinned staging of the view table
-        size_t cap = 0;
-        if (ctx->h_grids) {
-            (void)hipHostFree(ctx->h_grids);
-            ctx->h_grids = nullptr;
-        }
-        if ((rc = pinned(ctx, ctx->h_grids, cap, n))) return rc;
-        ctx->h_views_cap = (uint32_t)n;
     }
+    c.seed_cap = h.seed_cap;
+    c.cand_cap = h.cand_cap;
+    c.mem_cap = h.mem_cap;
+    c.nc = few_grains(c.n_total, ctx->cfg.cyl_ext) ? 1 : h.nc;
     if (!ctx->h_desc) {
         size_t cap = 0;
         if ((rc = pinned(ctx, ctx->h_desc, cap, 1))) return rc;
     }
     {
-        const size_t nv = ctx->cap_views + 1;
-        HostOut &h = ctx->h;
+        const size_t nv = h.n_views + 1;
+        HostOut &ho = ctx->h;
         HostOut &o = d.out;
-        if ((rc = mapped(ctx, h.cnt, o.cnt, ctx->cap_out_cnt, 1))) return rc;
-        if ((rc = mapped(ctx, h.view_seeds, o.view_seeds, ctx->cap_vs, nv))) return rc;
-        if ((rc = mapped(ctx, h.view_cand, o.view_cand, ctx->cap_vc, nv))) return rc;
-        if ((rc = mapped(ctx, h.view_ntr, o.view_ntr, ctx->cap_vn, nv))) return rc;
-        if ((rc = mapped(ctx, h.view_tr_off, o.view_tr_off, ctx->cap_vo, nv))) return rc;
-        if ((rc = mapped(ctx, h.view_err, o.view_err, ctx->cap_ve, nv))) return rc;
-        if ((rc = mapped(ctx, h.tracks, o.tracks, ctx->cap_out_tracks, c.cand_cap))) return rc;
-        if ((rc = mapped(ctx, h.grains, o.grains, ctx->cap_out_grains, c.mem_cap))) return rc;
+        if ((rc = mapped(ctx, ho.cnt, o.cnt, ctx->cap_out_cnt, 1))) return rc;
+        if ((rc = mapped(ctx, ho.view_seeds, o.view_seeds, ctx->cap_vs, nv))) return rc;
+        if ((rc = mapped(ctx, ho.view_cand, o.view_cand, ctx->cap_vc, nv))) return rc;
+        if ((rc = mapped(ctx, ho.view_ntr, o.view_ntr, ctx->cap_vn, nv))) return rc;
+        if ((rc = mapped(ctx, ho.view_tr_off, o.view_tr_off, ctx->cap_vo, nv))) return rc;
+        if ((rc = mapped(ctx, ho.view_err, o.view_err, ctx->cap_ve, nv))) return rc;
+        if ((rc = mapped(ctx, ho.tracks, o.tracks, ctx->cap_out_tracks, c.cand_cap))) return rc;
+        if ((rc = mapped(ctx, ho.grains, o.grains, ctx->cap_out_grains, c.mem_cap))) return rc;
         if (ctx->cfg.flags & EMT_F_CANDIDATES) {
-            if ((rc = mapped(ctx, h.cands, o.cands, ctx->cap_cands, 3 * (size_t)c.cand_cap)))
+            if ((rc = mapped(ctx, ho.cands, o.cands, ctx->cap_cands, 3 * (size_t)c.cand_cap)))
                 return rc;
         }
     }
@@ -443,18 +499,13 @@ void launch_stage(emt_ctx *ctx, const DevPtrs &run, const Caps &c, hipStream_t s
 }
 
 void launch_stages(emt_ctx *ctx, const Caps &c, hipStream_t s, int stage) {
+    DevPtrs run = ctx->d;
+    run.nc = c.nc;
     if (stage >= 0) {
-        launch_stage(ctx, ctx->d, c, s, stage);
+        launch_stage(ctx, run, c, s, stage);
         return;
     }
-    for (int k = 0; k < kStages; ++k) launch_stage(ctx, ctx->d, c, s, k);
-}
-
-bool same_caps(const Caps &a, const Caps &b) {
-    return a.n_total == b.n_total && a.n_views == b.n_views && a.n_cells == b.n_cells &&
-           a.max_view_n == b.max_view_n && a.seed_cap == b.seed_cap &&
-           a.cand_cap == b.cand_cap && a.mem_cap == b.mem_cap &&
-           a.wide_rounds == b.wide_rounds;
+    for (int k = 0; k < kStages; ++k) launch_stage(ctx, run, c, s, k);
 }
 
 void drop_graphs(emt_ctx *ctx) {
@@ -517,6 +568,7 @@ int launch_sequence(emt_ctx *ctx, const Caps &c) {
 int run_launch(emt_ctx *ctx, const emt_view_in *views, uint32_t nv, const Caps &c) {
     DevPtrs &d = ctx->d;
     hipStream_t s = ctx->stream;
+    ctx->h_desc->n_anchor = (uint32_t)c.nc * ctx->h_desc->n_total;
     record(ctx, 0);
     // stage the grains into the packed buffer
     const bool dev = (ctx->cfg.flags & EMT_F_DEVICE_PTRS) != 0;
@@ -719,6 +771,16 @@ int emt_create(const emt_config *cfg, emt_ctx **out) {
     for (int m = 0; m < 3; ++m) ctx->P.cell_req[m] = cfg->cell[m] ? cfg->cell[m] : kDefaultCell[m];
     for (int b = 0; b < kCellBuckets; ++b)
         for (int m = 0; m < 3; ++m) ctx->P.cell_tab[b][m] = kTunedCells[b][m];
+    for (int b = 0; b < kCellBuckets; ++b)
+        for (int m = 0; m < 3; ++m) ctx->P.line_tab[b][m] = kLineTable[b][m];
+    // Tuning hook: line grids "cell,slab,bins" for every density.
+    if (const char *e = std::getenv("EMT_LINE")) {
+        int v[3];
+        if (std::sscanf(e, "%d,%d,%d", &v[0], &v[1], &v[2]) == 3 && v[0] > 0 && v[1] > 0 &&
+            v[0] <= kSpanMax && v[1] <= kSpanMax && v[2] >= 1 && v[2] <= kSubMax)
+            for (int b = 0; b < kCellBuckets; ++b)
+                for (int m = 0; m < 3; ++m) ctx->P.line_tab[b][m] = v[m];
+    }
     ctx->P.flags = cfg->flags;
     // Tuning hook: fixed cell edges "x,y,z" in units.
     if (const char *e = std::getenv("EMT_CELL")) {
@@ -789,10 +851,11 @@ size_t batch_bytes(const emt_ctx *ctx, unsigned long long n_total, uint32_t n_vi
                    uint32_t max_n) {
     Caps c{};
     if (batch_caps(ctx, n_total, n_views, max_n, &c)) return SIZE_MAX;
-    return grain_bytes(std::max<uint32_t>(c.n_total, 1024)) + seed_bytes(c.seed_cap) +
-           cand_bytes(c.cand_cap) + mem_bytes(c.mem_cap) +
-           cell_bytes(std::max<uint32_t>(scan_words(c), 1u << 16)) +
-           view_bytes(std::max<uint32_t>(c.n_views, 64));
+    c.n_total = std::max(c.n_total, 1024u);
+    c.n_cells = std::max(c.n_cells, 1u << 16);
+    c.n_views = std::max(c.n_views, 64u);
+    // with the fewest line classes: more only use what the budget has left
+    return arena_sizes(c, 3).total();
 }
 
 size_t held_bytes(const emt_ctx *ctx) { return ctx->held; }

@@ -20,8 +20,22 @@ constexpr int kBlock = 256;
 // are doubled until the grid fits.
 constexpr uint32_t kCellsPerGrain = EMT_CELLS_PER_GRAIN;
 constexpr uint32_t kCellsBase = 4096;
-// Entries of the sorted-grain array past the last grain: kernels that load
-// a fixed group of consecutive grains may read (and then ignore) them.
+// Whether a call counts over the binned cells instead of line grids: filling
+// those costs 30 to 60 us, which a small call does not win back (one view of
+// 900 grains: count and members 79 us over the cells, 150 us over line grids;
+// one of 27k: 627 and 416 us), nor does a medium one of short finite cylinders
+// (27k grains, reaching 5 um: equal; 20 um: 600 and 490 us). n_grains: the
+// call's capacity bucket.
+constexpr uint32_t kFewGrains = 8192;
+constexpr uint32_t kFewGrainsShort = 65536;
+constexpr int kShortCylinder = 1000;
+__host__ inline bool few_grains(uint32_t n_grains, int cyl_ext) {
+    return n_grains <= kFewGrains ||
+           (cyl_ext >= 0 && cyl_ext < kShortCylinder && n_grains <= kFewGrainsShort);
+}
+// Entries of the sorted-grain array past the last grain: the counting kernel
+// of those calls loads fixed groups of consecutive grains and may read (and
+// then ignore) them.
 constexpr uint32_t kSortedSpare = 8;
 
 // Per view. Host fills grain_off, n, cell_off, cell_cap and resets lo/hi;
@@ -39,6 +53,30 @@ struct ViewGrid {
     int32_t pad[3];
 };
 
+// Per view: the grids the counting kernel walks, written by k_grid (see
+// there). Face a holds sub * sub classes of ns[a] planes each.
+constexpr int kSubMax = 4;                           // most slope bins an axis
+constexpr int kLineClasses = 3 * kSubMax * kSubMax;  // most line classes a view has
+constexpr int kLineEdge = 2048;                // cells of a plane along u or v
+constexpr int kLineKeys = 4096;                // places a face's grains are sorted into
+constexpr uint32_t kLineBand = 256;            // records a workgroup fills at a time
+constexpr int kPackSpan = 2048;                // units a packed word's u and v reach either way
+// Records a view may use per grain, when tables hold nc classes.
+__host__ __device__ inline uint32_t line_recs(int nc) { return (uint32_t)(nc + nc / 4); }
+constexpr uint32_t kLineEnt = 12;              // list words of a class per grain
+struct LineGrid {
+    int32_t sub;           // slope bins an axis
+    int32_t c, w;          // cell edge and slab thickness (units)
+    int32_t reach;         // cells start this far below the bounding box
+    float ic;              // 1 / c
+    int32_t packed;        // list words hold the grains' coordinates
+    int32_t ns[3];         // slabs along the face's axis
+    int32_t nu[3], nv[3];  // cells of a plane
+    int32_t bu[3];         // records (8 x 4 cells each) in a row of records
+    uint32_t plane[3];     // records from one plane to the next
+    uint32_t face_off[3];  // the face's first record, from the view's first
+};
+
 // Sizes of the batch in flight, in device memory so that one captured launch
 // sequence serves every batch within its capacities.
 struct BatchDesc {
@@ -46,6 +84,7 @@ struct BatchDesc {
     uint32_t n_views;
     uint32_t n_cells;     // cell table entries in use
     uint32_t n_cells_m1;  // n_cells - 1 (scan length of the cell table)
+    uint32_t n_anchor;    // line classes held * n_total (scan length of the seed counts)
 };
 
 // Cell edges by grain density: bucket b holds views with at least
@@ -74,6 +113,7 @@ struct Params {
     uint32_t flags;
     int32_t auto_cells;   // 1: per view from cell_tab by density
     int32_t cell_tab[kCellBuckets][3];
+    int32_t line_tab[kCellBuckets][3];  // line grids: cell edge, slab thickness, slope bins
 };
 
 // Device counters of one call. Totals keep counting past capacities so the
@@ -141,9 +181,8 @@ struct DevPtrs {
     uint32_t *cell_count; // C
     uint32_t *cell_start; // C
     int4 *sg;             // N (+ kSortedSpare) sorted grains: x, y, z relative to lo; w = input index
-    float4 *sgf;          // N (+ kSortedSpare): x, y, z of sg as floats (exact), w = 0
-    uint32_t *seed_cnt;   // N: seeds per anchor
-    uint32_t *seed_off;   // N + 1
+    uint32_t *seed_cnt;   // nc N: seeds by view, line class, anchor in the class's order
+    uint32_t *seed_off;   // nc N + 1
     uint2 *seeds;         // seed_cap
     uint32_t *seed_n;     // seed_cap: count if >= n_min, else 0
     uint32_t *pass;       // seed_cap / 32 + 1 words: bit s % 32 of word s / 32
@@ -180,6 +219,16 @@ struct DevPtrs {
     uint32_t *view_tail;    // V: candidates of each view handed to its merge tail
     unsigned long long *part64;  // kPartWords: spread partial sums of four 64-bit totals
     uint32_t *scan_part;  // scan scratch
+    LineGrid *lines;      // 2 V: the view's line grids, and coarser ones
+    float4 *lsg;          // 3 N: by view and face, the grains sorted (along the face's axis, u,
+                          // v as exact floats; position in the view)
+    uint32_t *lkey;       // 3 (N + V): by view and face, where each key's sorted grains start
+    uint32_t *lrank;      // nc N: by view and class, an anchor's place in its order
+    uint32_t *lpool;      // 2 nc V: list words each class has taken
+    uint32_t *lcoarse;    // V: 1 if the view's lines walk the coarser grids
+    uint2 *lrec;          // line_recs(nc) N: records
+    uint2 *lent;          // kLineEnt nc N: list words
+    int32_t nc;           // line classes the tables hold (3, 12 or 48; 1: lines not classed)
     Counters *cnt;
     const BatchDesc *desc;
     HostOut out;
@@ -196,7 +245,7 @@ struct Caps {
     uint32_t cand_cap;
     uint32_t mem_cap;
     int32_t wide_rounds;      // grid-wide merge rounds before the tail kernel
-    int32_t pad;
+    int32_t nc;               // line classes the tables hold
 };
 
 // Grain recognition: stack geometry and the device buffers of one call.

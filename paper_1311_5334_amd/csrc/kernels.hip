@@ -3,8 +3,10 @@
 // Pipeline (paper Sec. 2, tracking paragraph; hash cells after the Sec. 3
 // footnote), for a batch of views packed one after another:
 //   bin      bounding box per view, counting sort of grains into cells
-//   seeds    all pairs closer than R (one lane per anchor grain)
-//   count    grains within r of each seed's infinite line (one lane per seed)
+//   seeds    all pairs closer than R, ordered by line class (one wave per
+//            anchor grain)
+//   count    grains within r of each seed's infinite line (one lane per seed,
+//            over line grids filled per class; small calls over the cells)
 //   members  grain lists of the seeds that reach n_min
 //   merge    exclusive association, rounds of deterministic reservations
 //   fit      track order, grain order, least-squares direction
@@ -12,6 +14,8 @@
 // chooses which cells to visit and carries a safety margin.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 #include "emt_dev.h"
 
@@ -21,9 +25,6 @@ namespace {
 
 // Tuning constants; -D on the compiler line overrides them (the counting
 // kernel's tiles come from tile_table.h, through emt_dev.h).
-#ifndef EMT_DYN_MIN_SEEDS
-#define EMT_DYN_MIN_SEEDS 8000000
-#endif
 constexpr float kMargin = 4.0f;  // units added to every cell window
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kBlock * kScanItems;
@@ -64,7 +65,7 @@ __device__ __forceinline__ void wave_sync_mem() {
 // workgroup twice).
 __device__ __forceinline__ void add_spread(unsigned long long *part64, int which,
                                            unsigned long long v) {
-    __shared__ unsigned long long s_part[kBlock / 64];
+    __shared__ unsigned long long s_part[16];  // waves of the largest workgroup
     if (lane_id() == 0) s_part[threadIdx.x >> 6] = v;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -252,11 +253,82 @@ __global__ void __launch_bounds__(kBlock) k_bbox(const int32_t *xyz, ViewGrid *g
     }
 }
 
+// ------------------------------------------------------------ line grids
+//
+// The grids the counting kernel walks. A line's class is the axis a of its
+// largest |d| (its face) and which of sub x sub bins its slopes d_u / d_a,
+// d_v / d_a in [-1, 1] fall in (u, v the other two axes). For each class the
+// view is cut along a into slabs of w units, and each slab's middle plane
+// into c x c cells. A line of the class crosses the middle plane of slab k at
+// one point, so it looks at one cell a slab; that cell lists every grain of
+// the slab that any line of the class through the cell can have within r.
+// A grain h units off the middle plane is met by lines that cross the plane
+// within delta |h| + r sqrt(1 + s^2) of (u - s0 h, v - t0 h), (s0, t0) the
+// bin's middle slopes, delta = 1 / sub the bin's half width and s the
+// largest |slope| of the bin: the grain is listed in every cell of that
+// rectangle, widened by kMargin units against the FP32 rounding of the
+// crossing point (below 1 unit for coordinates up to 2^18, and 1.5 units for
+// its fixed-point steps). The exact test decides the grains.
+__device__ __forceinline__ int line_u(int a) { return a == 0 ? 1 : 0; }
+__device__ __forceinline__ int line_v(int a) { return a == 2 ? 1 : 2; }
+
+// Largest distance, in a plane's u or v, between a grain and the cells that
+// list it.
+__device__ __forceinline__ int line_reach(int w, int r) {
+    return w / 2 + 1 + (int)(1.42f * (float)r) + (int)kMargin + 1;
+}
+
+// c and w grow until the view's records fit their share; c is at least
+// `spread` times the half side of a grain's largest rectangle.
+__device__ LineGrid line_grid(const ViewGrid &G, const long long *span, const int *tab, int nc, int r,
+                              double spread) {
+    LineGrid L = {};
+    int sub = tab[2];
+    while (3 * sub * sub > nc) --sub;
+    L.sub = sub;
+    if (G.n == 0) return L;
+    const unsigned long long cap = (unsigned long long)line_recs(nc) * G.n;
+    double c = tab[0], w = tab[1];
+    for (;;) {
+        L.w = (int)w;
+        const double half = 0.5 * w / sub + 1.4143 * r + kMargin;
+        c = fmax(c, half * spread + 2.0);
+        if (c > 0.75 * w) {  // keeps the crossing points' fixed point exact enough
+            w *= 1.19;
+            continue;
+        }
+        L.c = (int)c;
+        L.reach = line_reach(L.w, r);
+        unsigned long long off = 0;
+        bool ok = true;
+        for (int a = 0; a < 3; ++a) {
+            const long long ns = span[a] / L.w + 1;
+            const long long nu = (span[line_u(a)] + 2 * L.reach) / L.c + 1;
+            const long long nv = (span[line_v(a)] + 2 * L.reach) / L.c + 1;
+            ok = ok && ns <= 65535 && nu <= kLineEdge && nv <= kLineEdge;
+            L.ns[a] = (int)ns;
+            L.nu[a] = (int)nu;
+            L.nv[a] = (int)nv;
+            L.bu[a] = (int)((nu + 7) / 8);
+            L.plane[a] = (uint32_t)(L.bu[a] * ((nv + 3) / 4));
+            L.face_off[a] = (uint32_t)off;
+            off += (unsigned long long)L.plane[a] * ns * (sub * sub);
+        }
+        if (ok && off <= cap) break;
+        c *= 1.19;
+        w *= 1.19;
+    }
+    L.ic = 1.0f / (float)L.c;
+    L.packed = 8 * L.c < kPackSpan && 2 * L.reach < kPackSpan ? 1 : 0;
+    return L;
+}
+
 // Cell geometry per view: the requested edges, doubled until the grid has at
 // most cell_cap cells. A view whose span exceeds the limit is marked: its
 // grains still go through the binning (into one cell, so every later view
 // keeps its place in the sorted arrays) but it produces no seeds.
-__global__ void k_grid(ViewGrid *grids, const BatchDesc *desc, Params P) {
+__global__ void k_grid(ViewGrid *grids, LineGrid *lines, uint32_t *pool, uint32_t *coarse,
+                       int nc, const BatchDesc *desc, Params P) {
     const uint32_t v = grid_tid();
     if (v >= desc->n_views) return;
     ViewGrid G = grids[v];
@@ -271,15 +343,13 @@ __global__ void k_grid(ViewGrid *grids, const BatchDesc *desc, Params P) {
     }
     // cell edges: fixed, or by the view's grain density (bounding box)
     int b = 0;
-    if (P.auto_cells) {
-        const double vol_um3 = (double)(span[0] + 1) * (double)(span[1] + 1) *
-                               (double)(span[2] + 1) * 1e-6;
-        const double per_1000 = 1000.0 * (double)G.n / vol_um3;
-        double edge = kCellEdge0;
-        while (b < kCellBuckets - 1 && per_1000 >= edge) {
-            ++b;
-            edge *= 2.0;
-        }
+    const double vol_um3 = (double)(span[0] + 1) * (double)(span[1] + 1) *
+                           (double)(span[2] + 1) * 1e-6;
+    const double per_1000 = 1000.0 * (double)G.n / vol_um3;
+    double edge = kCellEdge0;
+    while (b < kCellBuckets - 1 && per_1000 >= edge) {
+        ++b;
+        edge *= 2.0;
     }
     for (int m = 0; m < 3; ++m) G.cell[m] = P.auto_cells ? P.cell_tab[b][m] : P.cell_req[m];
     if (G.err) {
@@ -300,6 +370,13 @@ __global__ void k_grid(ViewGrid *grids, const BatchDesc *desc, Params P) {
         for (int m = 0; m < 3; ++m) G.cell[m] *= 2;
     }
     grids[v] = G;
+    if (nc == 1) return;  // the lines are not classed
+    // the grid used unless its lists overflow their share, and a coarser one
+    // whose lists cannot: a rectangle covers at most 2 x 2 cells, six words
+    lines[2 * v] = line_grid(G, span, P.line_tab[b], nc, P.r, 2.0 / 3.0);
+    lines[2 * v + 1] = line_grid(G, span, P.line_tab[b], nc, P.r, 2.0);
+    for (int i = 0; i < 2 * nc; ++i) pool[(size_t)v * 2 * nc + i] = 0u;
+    coarse[v] = 0u;
 }
 
 __device__ __forceinline__ int axis_cell(const ViewGrid &G, int m, int x) {
@@ -331,7 +408,7 @@ __global__ void __launch_bounds__(kBlock) k_hist(const int32_t *xyz, const ViewG
 __global__ void __launch_bounds__(kBlock) k_scatter(const int32_t *xyz, const ViewGrid *grids,
                                                     const uint32_t *cell_of, const uint32_t *rank,
                                                     const uint32_t *cell_start, int4 *sg,
-                                                    float4 *sgf, const BatchDesc *desc) {
+                                                    const BatchDesc *desc) {
     const uint32_t v = blockIdx.y;
     if (v >= desc->n_views) return;
     const ViewGrid G = grids[v];
@@ -340,11 +417,10 @@ __global__ void __launch_bounds__(kBlock) k_scatter(const int32_t *xyz, const Vi
         const uint32_t pos = cell_start[cell_of[g]] + rank[g];
         const int x = xyz[3 * g] - G.lo[0], y = xyz[3 * g + 1] - G.lo[1], z = xyz[3 * g + 2] - G.lo[2];
         sg[pos] = make_int4(x, y, z, (int)i);
-        sgf[pos] = make_float4((float)x, (float)y, (float)z, 0.0f);
     }
 }
 
-// ------------------------------------------------------------ line walk
+// ------------------------------------------- line walk over the binned cells
 //
 // Which cells can hold a grain within r of the infinite line p(t) = g + t d?
 // If |k - p(t*)| <= r then |k_m - p_m(t*)| <= r on every axis. Cells along x
@@ -379,14 +455,12 @@ struct Pencil {
     float ta, tb;
     bool live;
 
-    // part/nparts: this lane walks the part-th of nparts equal slices of the
-    // e cells, so that several lanes can share one long line. No divisions:
-    // reciprocals (within 1 ulp) are covered by the kMargin widening.
+    // No divisions: reciprocals (within 1 ulp) are covered by the kMargin
+    // widening.
     // ext >= 0: a finite cylinder, whose grains project at most ext units
     // beyond the seed grains; the walk then covers only that stretch.
     __device__ __forceinline__ void init(const ViewGrid *__restrict__ Gp, int4 g, int idx, int idy,
-                                         int idz, int r, bool valid, int part, int nparts,
-                                         int ext = -1) {
+                                         int idz, int r, int ext) {
         nx = Gp->dims[0];
         const int ny = Gp->dims[1];
         const int nz = Gp->dims[2];
@@ -492,18 +566,12 @@ struct Pencil {
         const float ehi = (de != 0.0f ? fmaxf(ea, eb) : ge) + rr;
         int ie0 = max(0, (int)floorf(fmaxf(elo * ice, -1.0f)));
         ie1 = min(ne - 1, (int)floorf(fminf(ehi * ice, (float)ne)));
-        if (nparts > 1 && ie0 <= ie1) {
-            const int len = ie1 - ie0 + 1, per = (len + nparts - 1) / nparts;
-            const int a0 = ie0 + part * per;
-            ie1 = min(ie1, a0 + per - 1);
-            ie0 = a0;
-        }
         ie = ie0 - 1;
         jf = 1;
         jf1 = 0;
         row_e = 0;
         ta = tb = 0.0f;
-        live = valid && ie0 <= ie1 && tlo <= thi;
+        live = ie0 <= ie1 && tlo <= thi;
     }
 
     // One move of the walk, straight-line: step to the next e cell when the
@@ -591,36 +659,6 @@ __device__ __forceinline__ uint32_t seed_threshold(int dx, int dy, int dz, const
     return t < (long long)cap ? (uint32_t)t : cap;
 }
 
-// Next grab of items for the calling wave: its own
-// XCD's range first, then the others. grab[16 x] is range x's offset
-// counter. Grabs are a quarter of a range's remainder per wave of the XCD,
-// within [gmin, gmax] and a multiple of gmin. Returns false when every
-// range is used up. Wave-uniform.
-__device__ __forceinline__ bool xcd_grab(uint32_t *grab, uint32_t xcd, uint32_t per,
-                                         uint32_t n_items, uint32_t wpx, uint32_t gmin,
-                                         uint32_t gmax, uint32_t &next, uint32_t &end) {
-    uint32_t s = 0xffffffffu, e = 0;
-    if (lane_id() == 0) {
-        for (uint32_t t = 0; t < 8; ++t) {
-            const uint32_t x = (xcd + t) & 7u;
-            const uint32_t lo = min(n_items, x * per), hi = min(n_items, x * per + per);
-            uint32_t *ctr = grab + 16 * x;
-            const uint32_t cur = __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (cur >= hi - lo) continue;
-            uint32_t g = (hi - lo - cur) / (4u * wpx);
-            g = min(gmax, max(gmin, (g + gmin - 1u) / gmin * gmin));
-            const uint32_t at = atomicAdd(ctr, g);
-            if (at >= hi - lo) continue;
-            s = lo + at;
-            e = min(hi, s + g);
-            break;
-        }
-    }
-    next = (uint32_t)__shfl((int)s, 0);
-    end = (uint32_t)__shfl((int)e, 0);
-    return next != 0xffffffffu;
-}
-
 __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -649,13 +687,180 @@ __device__ __forceinline__ uint32_t wave_incl_scan_dpp(uint32_t x) {
 // the seeds of every anchor, a scan turns the counts into offsets, and a
 // second pass writes them: no shared counter, and the seed list comes out in
 // anchor order, so each view's seeds are contiguous.
+// The line class of direction d (up to the rounding at the bins' edges, where
+// both classes list the line's grains): its face, and its slopes' bins.
+__device__ __forceinline__ int line_face(int ax, int ay, int az) {
+    return (ax >= ay && ax >= az) ? 0 : (ay >= az ? 1 : 2);
+}
+
+__device__ __forceinline__ int line_bin(float slope, int sub) {
+    return max(0, min(sub - 1, (int)((slope + 1.0f) * (0.5f * (float)sub))));
+}
+
+__device__ __forceinline__ int line_class(int dx, int dy, int dz, int ns) {
+    const int a = line_face(abs(dx), abs(dy), abs(dz));
+    const float ida = __builtin_amdgcn_rcpf((float)(a == 0 ? dx : a == 1 ? dy : dz));
+    const float su = (float)(a == 0 ? dy : dx) * ida, sv = (float)(a == 2 ? dy : dz) * ida;
+    return ns == 0 ? 0 : (a * ns + line_bin(su, ns)) * ns + line_bin(sv, ns);
+}
+
+// The order of a class's seeds: their anchors by tiles of the plane across
+// the class's middle direction (positions moved along it to the middle of the
+// view), row by row. Lines of one class through one tile stay close together
+// all the way, so the waves that count them read the same records and words.
+// One workgroup per view and class sorts the anchors by counting, in LDS.
+constexpr int kOrderBlock = 1024;
+constexpr int kTiles = 2048;
+
+// The grains of each face in the order k_line_fill and the tests read them:
+// by groups of slabs, and in a group by square tiles of at least 20 um, u
+// fastest. line_tiles: slabs a group, groups, tiles along u and v.
+struct LineTiles {
+    int gs, ng, tu, tv;
+    float it;  // 1 / tile edge
+};
+
+__device__ __forceinline__ int line_key_cap(uint32_t n) { return (int)min((uint32_t)kLineKeys, n); }
+
+__device__ __forceinline__ uint32_t *line_keys(const DevPtrs &d, const ViewGrid &G, uint32_t v,
+                                               int a) {
+    return d.lkey + 3 * ((size_t)G.grain_off + v) + (size_t)a * (line_key_cap(G.n) + 1);
+}
+
+__device__ LineTiles line_tiles(const ViewGrid &G, const LineGrid &L, int a) {
+    LineTiles T;
+    const int cap = line_key_cap(G.n);
+    const int ns = L.ns[a], au = line_u(a), av = line_v(a);
+    T.gs = (ns + cap - 1) / cap;
+    T.ng = (ns + T.gs - 1) / T.gs;
+    const float su = (float)(G.hi[au] - G.lo[au]) + 1.0f, sv = (float)(G.hi[av] - G.lo[av]) + 1.0f;
+    float edge = fmaxf(2000.0f, sqrtf(su * sv * (float)T.ng / (float)cap));
+    for (;;) {
+        T.it = 1.0f / edge;
+        T.tu = (int)(su * T.it) + 1;
+        T.tv = (int)(sv * T.it) + 1;
+        if ((long long)T.ng * T.tu * T.tv <= cap) return T;
+        edge *= 1.25f;
+    }
+}
+
+// One face's grains, sorted by counting in LDS (one workgroup).
+__device__ void line_sort(const DevPtrs &d, const ViewGrid &G, uint32_t v, int a, uint32_t *s_key,
+                          uint32_t *s_wave) {
+    const LineGrid &L = d.lines[2 * v];
+    const LineTiles T = line_tiles(G, L, a);
+    const int gw = T.gs * L.w;  // a group's thickness
+    auto key_of = [&](const int4 &g) {
+        const int ga = a == 0 ? g.x : a == 1 ? g.y : g.z;
+        const float gu = (float)(a == 0 ? g.y : g.x), gv = (float)(a == 2 ? g.y : g.z);
+        const int iu = min(T.tu - 1, (int)(gu * T.it)), iv = min(T.tv - 1, (int)(gv * T.it));
+        return ((ga / gw) * T.tv + iv) * T.tu + iu;
+    };
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const uint32_t n = G.n, goff = G.grain_off;
+    constexpr int kPer = kLineKeys / kOrderBlock;
+    for (int i = threadIdx.x; i < kLineKeys; i += kOrderBlock) s_key[i] = 0u;
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < n; i += kOrderBlock)
+        atomicAdd(&s_key[key_of(d.sg[goff + i])], 1u);
+    __syncthreads();
+    uint32_t c[kPer], sum = 0;
+    for (int i = 0; i < kPer; ++i) sum += c[i] = s_key[kPer * threadIdx.x + i];
+    const uint32_t incl = wave_incl_scan_dpp(sum);
+    if (lane == 63) s_wave[wave] = incl;
+    __syncthreads();
+    uint32_t before = incl - sum;
+    for (int w = 0; w < wave; ++w) before += s_wave[w];
+    uint32_t *start = line_keys(d, G, v, a);
+    for (int i = 0; i < kPer; ++i) {
+        const int key = kPer * threadIdx.x + i;
+        s_key[key] = before;
+        if (key <= line_key_cap(n)) start[key] = before;
+        before += c[i];
+    }
+    if (threadIdx.x == kOrderBlock - 1 && line_key_cap(n) == kLineKeys) start[kLineKeys] = before;
+    __syncthreads();
+    float4 *out = d.lsg + 3 * (size_t)goff + (size_t)a * n;
+    for (uint32_t i = threadIdx.x; i < n; i += kOrderBlock) {
+        const int4 g = d.sg[goff + i];
+        out[atomicAdd(&s_key[key_of(g)], 1u)] =
+            make_float4((float)(a == 0 ? g.x : a == 1 ? g.y : g.z), (float)(a == 0 ? g.y : g.x),
+                        (float)(a == 2 ? g.y : g.z), __uint_as_float(i));
+    }
+}
+
+__global__ void __launch_bounds__(kOrderBlock) k_line_order(DevPtrs d) {
+    __shared__ uint32_t s_tile[kLineKeys > kTiles ? kLineKeys : kTiles];
+    __shared__ uint32_t s_wave[kOrderBlock / 64];
+    const uint32_t v = blockIdx.y;
+    if (v >= d.desc->n_views) return;
+    const ViewGrid *G = &d.grids[v];
+    const uint32_t n = G->n, goff = G->grain_off;
+    if (G->err || n == 0) return;
+    if (blockIdx.x < 3) {
+        line_sort(d, *G, v, (int)blockIdx.x, s_tile, s_wave);
+        return;
+    }
+    const int nsub = d.lines[2 * v].sub, cls = (int)blockIdx.x - 3;
+    if (cls >= 3 * nsub * nsub) return;
+    const int a = cls / (nsub * nsub), sub = cls % (nsub * nsub);
+    const int au = line_u(a), av = line_v(a);
+    const float delta = 1.0f / (float)nsub;
+    const float su0 = (float)(2 * (sub / nsub) + 1) * delta - 1.0f;
+    const float sv0 = (float)(2 * (sub % nsub) + 1) * delta - 1.0f;
+    const float half = 0.5f * (float)(G->hi[a] - G->lo[a]);
+    const float ru = (float)(G->hi[au] - G->lo[au]) + 2.0f * fabsf(su0) * half + 1.0f;
+    const float rv = (float)(G->hi[av] - G->lo[av]) + 2.0f * fabsf(sv0) * half + 1.0f;
+    // about kTiles / 2 square tiles; no more than kTiles whatever the shape
+    const float edge = fmaxf(sqrtf(ru * rv * (2.0f / kTiles)), fmaxf(ru, rv) * (4.0f / kTiles));
+    const float ie = 1.0f / edge;
+    const int tu = min((int)(ru * ie) + 1, kTiles / 2);
+    const int tv = min((int)(rv * ie) + 1, kTiles / tu);
+    auto tile_of = [&](const int4 &g) {
+        const float h = (float)(a == 0 ? g.x : a == 1 ? g.y : g.z) - half;
+        const float u = (float)(a == 0 ? g.y : g.x) - su0 * h + fabsf(su0) * half;
+        const float w = (float)(a == 2 ? g.y : g.z) - sv0 * h + fabsf(sv0) * half;
+        const int iu = max(0, min(tu - 1, (int)(u * ie))), iv = max(0, min(tv - 1, (int)(w * ie)));
+        return iv * tu + iu;
+    };
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    for (int i = threadIdx.x; i < kTiles; i += kOrderBlock) s_tile[i] = 0u;
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < n; i += kOrderBlock) atomicAdd(&s_tile[tile_of(d.sg[goff + i])], 1u);
+    __syncthreads();
+    const uint32_t c0 = s_tile[2 * threadIdx.x], c1 = s_tile[2 * threadIdx.x + 1];
+    const uint32_t incl = wave_incl_scan_dpp(c0 + c1);
+    if (lane == 63) s_wave[wave] = incl;
+    __syncthreads();
+    uint32_t before = incl - c0 - c1;
+    for (int w = 0; w < wave; ++w) before += s_wave[w];
+    s_tile[2 * threadIdx.x] = before;
+    s_tile[2 * threadIdx.x + 1] = before + c0;
+    __syncthreads();
+    uint32_t *rank = d.lrank + (size_t)d.nc * goff + (size_t)cls * n;
+    for (uint32_t i = threadIdx.x; i < n; i += kOrderBlock)
+        rank[i] = atomicAdd(&s_tile[tile_of(d.sg[goff + i])], 1u);
+}
+static_assert(kTiles == 2 * kOrderBlock, "two tiles a thread");
+
+constexpr uint32_t kSeedRun = 64;
+
 template <bool kWrite>
 __global__ void __launch_bounds__(kBlock) k_seeds(DevPtrs d, Caps c, Params P) {
     // per wave: the first flat element of each row, and sorted position
     // minus that (so that grain = dk[r] + element)
     __shared__ uint32_t s_rows[kBlock / 64][2][64];
+    // per wave and class: the anchor's seeds so far, or where the next goes
+    __shared__ uint32_t s_cls[kBlock / 64][kLineClasses];
+    uint32_t *cls_s = s_cls[threadIdx.x >> 6];
     const int lane = lane_id();
-    const uint32_t gw = grid_tid() >> 6, nw = grid_threads() >> 6;
+    // workgroups are dealt to the XCDs in turn: each XCD takes runs of
+    // kSeedRun workgroups' consecutive anchors, whose seeds share lines in
+    // its L2
+    const uint32_t wi = blockIdx.x >> 3;
+    const uint32_t wg = ((wi / kSeedRun) * 8u + (blockIdx.x & 7u)) * kSeedRun + wi % kSeedRun;
+    const uint32_t gw = wg * (kBlock / 64) + (threadIdx.x >> 6);
+    const uint32_t nw = grid_threads() >> 6;
     const int R1 = P.R - 1;
     const int R2 = P.R * P.R;
     const uint32_t n_total = d.desc->n_total;
@@ -671,7 +876,19 @@ __global__ void __launch_bounds__(kBlock) k_seeds(DevPtrs d, Caps c, Params P) {
     for (uint32_t p = gw; p < n_total; p += nw) {
         const uint32_t v = d.view_of[p];
         const ViewGrid *G = &d.grids[v];
-        uint32_t base = kWrite ? d.seed_off[p] : 0u;
+        // the anchor's places in its view's table of classes by ordered anchors
+        const uint32_t tab = (uint32_t)d.nc * G->grain_off, rel = p - G->grain_off;
+        uint32_t at = 0;
+        static_assert(kLineClasses <= 64, "one class a lane");
+        // (one class, anchors in place, where the lines are not classed)
+        const int nsub = d.nc > 1 ? d.lines[2 * v].sub : 0;
+        if (lane < 3 * nsub * nsub && !G->err)
+            at = tab + (uint32_t)lane * G->n + d.lrank[tab + (uint32_t)lane * G->n + rel];
+        else if (lane < d.nc)
+            at = tab + (uint32_t)lane * G->n + rel;
+        wave_lds_sync();  // the previous anchor's are read
+        if (lane < d.nc) cls_s[lane] = kWrite ? d.seed_off[at] : 0u;
+        wave_lds_sync();
         uint32_t mine = 0;
         if (!G->err) {
             const int nx = G->dims[0], ny = G->dims[1], nz = G->dims[2];
@@ -728,17 +945,14 @@ __global__ void __launch_bounds__(kBlock) k_seeds(DevPtrs d, Caps c, Params P) {
                     const int D = ok ? ex * ex + ey * ey + ez * ez : 0;
                     return ok && D > 0 && D < R2;
                 };
-                auto write = [&](bool ok, const int4 &h, uint32_t q) {
-                    const unsigned long long m = __ballot(ok);
-                    if (ok) {
-                        const unsigned long long slot =
-                            (unsigned long long)base + (unsigned long long)__popcll(m & lanes_below());
-                        // stored lower input index first: that grain is the
-                        // seed's i (the fit's origin and key order)
-                        if (slot < c.seed_cap)
-                            d.seeds[slot] = h.w > g.w ? make_uint2(p, q) : make_uint2(q, p);
-                    }
-                    base += (uint32_t)__popcll(m);
+                auto take = [&](bool ok, const int4 &h, uint32_t q) {
+                    if (!ok) return;
+                    const uint32_t slot =
+                        atomicAdd(&cls_s[line_class(h.x - g.x, h.y - g.y, h.z - g.z, nsub)], 1u);
+                    // stored lower input index first: that grain is the
+                    // seed's i (the fit's origin and key order)
+                    if (kWrite && slot < c.seed_cap)
+                        d.seeds[slot] = h.w > g.w ? make_uint2(p, q) : make_uint2(q, p);
                 };
                 // two elements a lane per trip: their row searches and grain
                 // loads are in flight together
@@ -747,19 +961,16 @@ __global__ void __launch_bounds__(kBlock) k_seeds(DevPtrs d, Caps c, Params P) {
                     const uint32_t q0 = grain_of(i0), q1 = grain_of(i1);
                     const int4 h0 = d.sg[q0], h1 = d.sg[q1];
                     const bool ok0 = pairs(h0, i0 < T), ok1 = pairs(h1, i1 < T);
-                    if (kWrite) {
-                        write(ok0, h0, q0);
-                        write(ok1, h1, q1);
-                    } else {
-                        mine += (ok0 ? 1u : 0u) + (ok1 ? 1u : 0u);
-                    }
+                    take(ok0, h0, q0);
+                    take(ok1, h1, q1);
+                    if (!kWrite) mine += (ok0 ? 1u : 0u) + (ok1 ? 1u : 0u);
                 }
             }
         }
         if (!kWrite) {
-            mine = wave_sum(mine);
-            if (lane == 0) d.seed_cnt[p] = mine;
-            wave_total += mine;
+            wave_lds_sync();
+            if (lane < d.nc) d.seed_cnt[at] = cls_s[lane];
+            wave_total += wave_sum(mine);
         }
     }
     if constexpr (!kWrite) add_spread(d.part64, 0, wave_total);
@@ -798,57 +1009,228 @@ __global__ void k_member_total(Counters *cnt, const unsigned long long *part64) 
 
 // ------------------------------------------------------- count / members
 
-constexpr int kWaves = kBlock / 64;
 
-// Counting with lane refill (one kernel counts the seeds and, as a second
-// instance, lists the members of the candidates). A wave owns a chunk of
-// seeds; each lane holds
-// two seed slots in LDS. When a lane's walk ends it closes that slot and at
-// once takes the next seed of the chunk into its other slot, so the wave's
-// time is the sum of its lines' work rather than a multiple of the longest
-// one. Hit counts of a closed slot are final after the next queue flush,
-// which writes them out and frees the slot.
+// Line grids: filling the cells.
 //
-// The queue holds pieces: each run a lane queues is cut into pieces of at
-// most kPiece consecutive grains, and the flush gives every lane one piece.
-// The lane maps its piece to the run by one popcount, reads the seed's line
-// constants once, issues the loads of all kPiece grains together and tests
-// them against the one line, so the mapping and the line constants are paid
-// once per piece and the grain loads of a piece are in flight together.
-constexpr int kCountSlots = 128;
-constexpr int kPiece = EMT_COUNT_PIECE;             // grains per queued piece
-constexpr int kPieceCap = EMT_COUNT_PIECE_CAP;      // queued pieces per wave
-constexpr int kLanePieces = EMT_COUNT_LANE_PIECES;  // pieces a lane queues per step
-constexpr int kCountRunCap = EMT_COUNT_RUN_CAP;     // queued runs per wave
-constexpr int kPieceWords = kPieceCap / 64;
-constexpr int kChunkSeeds = EMT_CHUNK_SEEDS;
-constexpr int kFetch = EMT_COUNT_FETCH;  // pencils a lane fetches per step
-constexpr int kRefillMin = EMT_COUNT_REFILL;  // waiting lanes that start a refill
-constexpr int kFlushUnroll = EMT_FLUSH_UNROLL;  // queue words a flush trip loads together
-static_assert(kFlushUnroll >= 1 && kFlushUnroll <= 4, "flush unroll");
-static_assert(64 * kFetch <= kCountRunCap, "a step's runs must fit the run queue");
-static_assert(kRefillMin >= 1 && kRefillMin <= 64, "refill threshold is a lane count");
-static_assert(64 * kLanePieces <= kPieceCap, "a step's pieces must fit the queue");
-static_assert(kPieceWords <= 64 && kPieceCap % 64 == 0, "one mask word per lane");
-static_assert(kPieceCap <= 4096 && kPiece * kLanePieces < 8192, "run record fields");
-static_assert(kPiece >= 1 && (uint32_t)kPiece - 1u <= kSortedSpare, "piece size");
+// A record covers a block of 8 x 4 cells of a plane: x has a bit for every
+// cell that lists grains, y is the list word of its first such cell, the
+// others following in cell order. A cell's word is its grain, or for several
+// grains x = kLineList and y the first of their words; those are the grains,
+// with kLineList on all but the last. A grain's word holds its coordinates, so
+// that the test needs no other load: 19 bits along the face's axis, 12 bits
+// each, signed, of u and v from the record's multiple of its edge, and its
+// position in the view (20 bits). Cells too large for that (not packed) hold
+// the place among the face's sorted grains in x and the position in y.
+constexpr uint32_t kLineList = 0x80000000u;
 
-template <bool kFinite, bool kEmit = false>
+__device__ __forceinline__ uint2 line_pack(int a, int u, int v, uint32_t rel) {
+    return make_uint2((uint32_t)a | (((uint32_t)u & 0xfffu) << 19),
+                      ((uint32_t)v & 0xfffu) | (rel << 12));
+}
+constexpr int kLineBlock = 256;
+static_assert(kLineBlock == (int)kLineBand, "one record a thread");
+
+// A class's list words: its first, from d.lent.
+__device__ __forceinline__ size_t line_pool(uint32_t nc, uint32_t grain_off, uint32_t n,
+                                            uint32_t cls) {
+    return (size_t)kLineEnt * ((size_t)nc * grain_off + (size_t)cls * n);
+}
+
+// The grid a view's lines walk: the coarser one if a class's list words did
+// not fit.
+__device__ __forceinline__ bool line_coarse(const DevPtrs &d, uint32_t v) {
+    return d.lcoarse[v] != 0u;
+}
+
+__device__ __forceinline__ const LineGrid *line_grid_of(const DevPtrs &d, uint32_t v) {
+    return &d.lines[2 * v + (line_coarse(d, v) ? 1 : 0)];
+}
+
+// One workgroup fills a band of at most kLineBand records of one plane: it
+// counts the grains of every cell in LDS, takes the band's words of the
+// class's pool, and places the grains. The grains that can reach the band are
+// a range of the face's sorted grains. kPass 1 fills the coarser grid of the views that need it.
+template <int kPass>
+__global__ void __launch_bounds__(kLineBlock) k_line_fill(DevPtrs d, Params P) {
+    // 33 words a record keep the threads' counts in different banks
+    __shared__ uint32_t s_cell[kLineBand * 33];
+    __shared__ uint32_t s_wave[kLineBlock / 64], s_base;
+    const uint32_t v = blockIdx.z;
+    if (v >= d.desc->n_views) return;
+    if (kPass == 1 && !line_coarse(d, v)) return;
+    const ViewGrid G = d.grids[v];
+    if (G.err || G.n == 0) return;
+    const LineGrid L = d.lines[2 * v + kPass];
+    const int nsub = L.sub, cls = (int)blockIdx.y;
+    if (cls >= 3 * nsub * nsub) return;
+    const int a = cls / (nsub * nsub), sub = cls % (nsub * nsub);
+    const LineTiles T = line_tiles(G, d.lines[2 * v], a);
+    const int gw = T.gs * d.lines[2 * v].w;
+    const uint32_t *start = line_keys(d, G, v, a);
+    const float4 *sorted = d.lsg + 3 * (size_t)G.grain_off + (size_t)a * G.n;
+    const int span_v = G.hi[line_v(a)] - G.lo[line_v(a)];
+    const float delta = 1.0f / (float)nsub;
+    const float su0 = (float)(2 * (sub / nsub) + 1) * delta - 1.0f;
+    const float sv0 = (float)(2 * (sub % nsub) + 1) * delta - 1.0f;
+    const float su = fabsf(su0) + delta, sv = fabsf(sv0) + delta;
+    const float hu0 = (float)P.r * sqrtf(1.0f + su * su) + kMargin;
+    const float hv0 = (float)P.r * sqrtf(1.0f + sv * sv) + kMargin;
+    const int ns = L.ns[a], nu = L.nu[a], nv = L.nv[a], bu = L.bu[a];
+    const uint32_t plane = L.plane[a];
+    uint2 *recs = d.lrec + (size_t)line_recs(d.nc) * G.grain_off + L.face_off[a] +
+                  (size_t)sub * ns * plane;
+    uint2 *ent = d.lent + line_pool((uint32_t)d.nc, G.grain_off, G.n, (uint32_t)cls);
+    uint32_t *pool = d.lpool + (size_t)(2 * v + kPass) * d.nc + cls;
+    const int nbv = (nv + 3) / 4;
+    const int brows = max(1, min(nbv, (int)kLineBand / bu));  // record rows a band
+    const int nbands = (nbv + brows - 1) / brows;
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    constexpr int kW = kLineBlock / 64;
+    for (uint32_t i = threadIdx.x; i < kLineBand * 33; i += kLineBlock) s_cell[i] = 0u;
+    __syncthreads();
+    for (int item = blockIdx.x; item < ns * nbands; item += gridDim.x) {
+        const int k = item / nbands, r0 = (item % nbands) * brows, r1 = min(nbv, r0 + brows);
+        const int b0 = 4 * r0, b1 = min(nv, 4 * r1);  // cell rows of the band
+        // the sorted grains of the slab that can reach the band
+        const int a0 = k * L.w, a1 = a0 + L.w;
+        const int g0 = a0 / gw, g1 = min((a1 - 1) / gw, T.ng - 1);
+        int t0 = 0, t1 = T.tv - 1;
+        if (g0 == g1) {
+            t0 = max(0, min(t1, (int)((float)max(0, b0 * L.c - 2 * L.reach) * T.it)));
+            t1 = max(0, min(t1, (int)((float)min(span_v, b1 * L.c) * T.it)));
+        }
+        const uint32_t i0 = start[(g0 * T.tv + t0) * T.tu], i1 = start[(g1 * T.tv + t1 + 1) * T.tu];
+        const float fa0 = (float)a0, fa1 = (float)a1, mid = fa0 + 0.5f * (float)L.w;
+        // calls at(cell, record's column and row, grain, its place) for every
+        // cell of the band that lists a grain
+        auto each = [&](auto at) {
+            for (uint32_t i = i0 + threadIdx.x; i < i1; i += kLineBlock) {
+                const float4 g = sorted[i];
+                if (g.x < fa0 || g.x >= fa1) continue;
+                const float h = g.x - mid;
+                const float hu = fmaf(delta, fabsf(h), hu0), hv = fmaf(delta, fabsf(h), hv0);
+                const float cu = g.y + (float)L.reach - su0 * h;
+                const float cv = g.z + (float)L.reach - sv0 * h;
+                const int ju0 = max(0, (int)((cu - hu) * L.ic));
+                const int ju1 = min(nu - 1, (int)((cu + hu) * L.ic));
+                const int jv0 = max(b0, (int)((cv - hv) * L.ic));
+                const int jv1 = min(b1 - 1, (int)((cv + hv) * L.ic));
+                for (int jv = jv0; jv <= jv1; ++jv) {
+                    const int row = ((jv >> 2) - r0) * bu, in = (jv & 3) << 3;
+                    for (int ju = ju0; ju <= ju1; ++ju)
+                        at((uint32_t)((row + (ju >> 3)) * 33 + in + (ju & 7)), ju >> 3, jv >> 2, g, i);
+                }
+            }
+        };
+        each([&](uint32_t cell, int, int, const float4 &, uint32_t) { atomicAdd(&s_cell[cell], 1u); });
+        __syncthreads();
+        // each thread one record: its bits, and how many words its cells need
+        const uint32_t n_rec = (uint32_t)((r1 - r0) * bu);
+        uint32_t *mine = s_cell + threadIdx.x * 33;
+        uint32_t bits = 0, words = 0;
+#pragma unroll 8
+        for (int i = 0; i < 32; ++i) {
+            const uint32_t n = mine[i];
+            bits |= n ? 1u << i : 0u;
+            words += n < 2u ? n : n + 1u;
+        }
+        const uint32_t incl = wave_incl_scan_dpp(words);
+        if (lane == 63) s_wave[wave] = incl;
+        __syncthreads();
+        uint32_t before = incl - words, total = 0;
+        for (int w = 0; w < kW; ++w) {
+            before += w < wave ? s_wave[w] : 0u;
+            total += s_wave[w];
+        }
+        if (threadIdx.x == 0) {
+            s_base = atomicAdd(pool, total);
+            if (s_base + total > kLineEnt * G.n) d.lcoarse[v] = 1u;
+        }
+        __syncthreads();
+        const uint32_t base = s_base + before;
+        const bool room = s_base + total <= kLineEnt * G.n;
+        uint32_t lists = 0;  // the cells of this record that list several grains
+        if (threadIdx.x < n_rec) {
+            recs[(size_t)k * plane + (size_t)r0 * bu + threadIdx.x] =
+                make_uint2(room ? bits : 0u, base);
+            uint32_t word = base, list = base + (uint32_t)__popc(bits);
+            for (uint32_t rest = room ? bits : 0u; rest; rest &= rest - 1u) {
+                const int i = __ffs(rest) - 1;
+                const uint32_t n = mine[i];
+                if (n == 1) {
+                    mine[i] = word;
+                } else {
+                    ent[word] = make_uint2(kLineList, list);
+                    mine[i] = kLineList | list;
+                    lists |= 1u << i;
+                    list += n;
+                }
+                ++word;
+            }
+        }
+        __syncthreads();
+        if (room)
+            each([&](uint32_t cell, int cu8, int rv4, const float4 &g, uint32_t place) {
+                const uint32_t at = atomicAdd(&s_cell[cell], 1u);
+                const uint32_t rel = __float_as_uint(g.w);
+                uint2 w = make_uint2(place, rel);
+                if (L.packed)
+                    w = line_pack((int)g.x, (int)g.y - 8 * L.c * cu8, (int)g.z - 4 * L.c * rv4, rel);
+                w.x |= at & kLineList;
+                ent[at & ~kLineList] = w;
+            });
+        __syncthreads();
+        for (; lists; lists &= lists - 1u) {
+            const uint32_t last = (mine[__ffs(lists) - 1] & ~kLineList) - 1u;
+            ent[last].x &= ~kLineList;
+        }
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < n_rec * 33; i += kLineBlock) s_cell[i] = 0u;
+        __syncthreads();
+    }
+}
+
+// Bound by VALU issue and by the cache lines the record and word loads touch
+// (8 c5 views: VALU 77 % and L1 address unit 90 % busy; L2 hits 95 %). One
+// lookup a slab and 16 tests a seed replace the 20 cell pencils and 84 tests
+// of a walk over the binned cells: 12.3 against 26.0 ms for the 163 M seeds of
+// 8 c5 views, and 230 against 500 us for the 3.3 M of one c2 view.
+//
+// Counting: a wave counts 64 lines at a time, one a lane. The lines of one
+// class (nearly always all 64) step through its slabs together, so that what
+// describes the class stays in scalar registers and the lanes, whose lines
+// run side by side, read neighbouring records. The words of the cells they
+// find go into a queue of the wave in LDS, and whenever it holds 64 of them
+// every lane tests one grain against the line it was found for (in LDS too),
+// so the test runs with all lanes whatever the lines hold.
+constexpr int kFetch = EMT_COUNT_FETCH;            // slabs walked per step
+constexpr int kCountBlock = EMT_COUNT_THREADS;     // threads of a workgroup
+constexpr int kCountWaves = kCountBlock / 64;
+constexpr uint32_t kChunkSeeds = EMT_CHUNK_SEEDS;  // most seeds a workgroup takes at a time
+constexpr uint32_t kApartSeeds = 50000000;         // seeds from which XCDs work apart
+// at most 63 words are left in the queue before a step's are added, and a
+// test adds back at most one for each it takes
+constexpr uint32_t kQueue = 64u * (kFetch + 1);
+// queued: position in the class's pool, lane of the line, and whether the
+// word is one of a cell's list (else a cell's first); the cell, u << 16 | v
+constexpr uint32_t kItemLane = 24, kItemList = 1u << 30;
+// fractional bits of a crossing point: its cell is the upper half word, and a
+// slab's step, rounded to half of the last bit, is off by at most 1.5 units at
+// the far side of the largest view (2^18 / w slabs; line_grid keeps c <= 3/4 w)
+constexpr int kLineBits = 16;
+constexpr float kLineOne = (float)(1 << kLineBits);
+static_assert((unsigned long long)kLineEdge << kLineBits <= 1ull << 31, "crossing points");
+static_assert((unsigned long long)kLineEnt * kNMax <= 1ull << kItemLane, "pool positions");
+
+template <bool kFinite, bool kEmit>
 struct CountLds {
-    // line constants per seed slot (floats): d, -(g_i x d), the band
-    // [tlo, thi] of the FP32 test, and the sorted position of g_i
-    float4 la[kCountSlots];  // dx, dy, dz, tlo
-    float4 lc[kCountSlots];  // -ex, -ey, -ez, thi
-    uint32_t lp[kCountSlots];  // sorted position of g_i (the int64 test)
-    int2 pc[kFinite ? kCountSlots : 1];  // finite cylinder: bounds of g_k.d
-    uint32_t cnt[kCountSlots];
-    // listing the members of candidates: where a slot's grains go, and how
-    // many its list holds (its count)
-    uint32_t out_off[kEmit ? kCountSlots : 1];
-    uint32_t ncap[kEmit ? kCountSlots : 1];
-    unsigned long long mask[kPieceWords];  // bit s: a run starts at piece s
-    uint32_t before[kPieceWords];          // runs starting before word w
-    uint2 run[kCountRunCap];  // first grain; first piece | seed slot << 12 | grains << 19
+    float4 la[64];  // dx, dy, dz, tlo
+    float4 lc[64];  // -ex, -ey, -ez, thi
+    uint32_t lp[64];             // sorted position of g_i (the int64 test)
+    uint32_t cnt[64];
+    int2 pc[kFinite ? 64 : 1];   // finite cylinder: bounds of g_k.d
+    uint2 mo[kEmit ? 64 : 1];    // listing members: where they go, how many
+    uint2 queue[kQueue];
 };
 
 // The counting test in FP32, decided exactly. With coordinates in [0, 2^18]
@@ -862,18 +1244,495 @@ struct CountLds {
 // redone in int64. The widening covers the rounding of the FP32 sum of
 // squares (within 5 * 2^-24 relative) and of the FP32 products forming tlo
 // and thi (|d|^2 < 2^26 rounded, a square, two products: within 4 * 2^-24).
+// The components of g_i x d are differences of two 24-bit products below
+// 2^18 * 4095, so they are exact in int32.
 __device__ __forceinline__ void line_consts(int4 gi, int dx, int dy, int dz, int r, float4 &A,
                                             float4 &C) {
     const float Df = (float)(dx * dx + dy * dy + dz * dz);  // |d| < 2^12: exact in int32
     const float rlo = (float)r - 0.125f, rhi = (float)r + 0.125f;  // exact
     const float tlo = r > 0 ? rlo * rlo * Df * (1.0f - 0x1p-20f) : -1.0f;
     const float thi = rhi * rhi * Df * (1.0f + 0x1p-20f);
-    const long long ex = (long long)gi.y * dz - (long long)gi.z * dy;
-    const long long ey = (long long)gi.z * dx - (long long)gi.x * dz;
-    const long long ez = (long long)gi.x * dy - (long long)gi.y * dx;
+    const int ex = __mul24(gi.y, dz) - __mul24(gi.z, dy);
+    const int ey = __mul24(gi.z, dx) - __mul24(gi.x, dz);
+    const int ez = __mul24(gi.x, dy) - __mul24(gi.y, dx);
     A = make_float4((float)dx, (float)dy, (float)dz, tlo);
     C = make_float4((float)-ex, (float)-ey, (float)-ez, thi);
 }
+
+// Seeds for the waves of a workgroup, a chunk of consecutive ones at a time.
+// Chunks are dealt to the XCDs in turn (as workgroups are), so all XCDs have
+// the same mix of long and short lines; or, from kApartSeeds on, each XCD has
+// an eighth of the list, so that its L2 holds the records and words of views
+// of its own. An XCD whose share is used up takes chunks of the others. The waves
+// of a workgroup take `step` seeds at a time from its chunk: they stay close
+// together in the class's order and so share the CU's cache. range: the
+// chunk's next seed and, in the upper half, its end.
+struct Feed {
+    unsigned long long range;
+    uint32_t lock, done;
+};
+
+// Seeds of a chunk: one a workgroup where its waves take no more than two
+// times each, else about eight, at least a time for every wave and at most
+// kChunkSeeds.
+__device__ __forceinline__ uint32_t chunk_size(uint32_t n_items, uint32_t step) {
+    const uint32_t share = n_items / gridDim.x + 1u, round = step * kCountWaves;
+    if (share <= 2u * round) return (share + step - 1u) / step * step;
+    return min(kChunkSeeds, max(round, share / 8u / step * step));
+}
+
+// Chunks of an XCD's eighth, where the XCDs work apart.
+__device__ __forceinline__ uint32_t chunks_apart(uint32_t n_items, uint32_t size) {
+    return ((n_items + size - 1u) / size + 7u) / 8u;
+}
+
+__device__ __forceinline__ unsigned long long chunk_range(uint32_t chunk, uint32_t size,
+                                                          uint32_t n_items) {
+    const unsigned long long lo = min((unsigned long long)n_items, (unsigned long long)chunk * size);
+    return (min((unsigned long long)n_items, lo + size) << 32) | lo;
+}
+
+// The next chunk, by one lane of the wave that holds the feed's lock. The
+// first chunk of every workgroup is its own without a counter.
+__device__ __forceinline__ unsigned long long next_chunk(uint32_t *grab, uint32_t n_items,
+                                                         uint32_t step) {
+    const uint32_t size = chunk_size(n_items, step), wgs = gridDim.x >> 3;
+    const uint32_t n_chunks = (n_items + size - 1u) / size;
+    const bool apart = n_items >= kApartSeeds;
+    const uint32_t per = chunks_apart(n_items, size);
+    for (uint32_t t = 0; t < 8; ++t) {
+        const uint32_t x = (blockIdx.x + t) & 7u;
+        // chunks x, x + 8, .. or x per .. (x + 1) per - 1
+        const uint32_t mine = apart ? min(n_chunks, (x + 1u) * per) - min(n_chunks, x * per)
+                                    : (n_chunks + 7u - x) / 8u;
+        uint32_t *ctr = grab + 16 * x;
+        const uint32_t cur = __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (wgs + cur >= mine) continue;
+        const uint32_t at = wgs + atomicAdd(ctr, 1u);
+        if (at < mine) return chunk_range(apart ? x * per + at : at * 8u + x, size, n_items);
+    }
+    return 0ull;
+}
+
+// Takes the next seeds [next, next + n) for the calling wave, n <= step.
+// Returns false when every range is used up; n = 0 with true if another wave
+// of the workgroup is fetching a chunk. Wave-uniform.
+__device__ __forceinline__ bool take_seeds(Feed &F, uint32_t *grab, uint32_t n_items,
+                                           uint32_t step, uint32_t &next, uint32_t &n) {
+    uint32_t s = 0, m = 0, ok = 1;
+    if (lane_id() == 0) {
+        volatile Feed *V = &F;
+        unsigned long long r = V->range;
+        if ((uint32_t)r < (uint32_t)(r >> 32)) {
+            r = atomicAdd(&F.range, (unsigned long long)step);
+            s = (uint32_t)r;
+            const uint32_t e = (uint32_t)(r >> 32);
+            m = s < e ? min(step, e - s) : 0u;
+        } else if (V->done) {
+            ok = 0;
+        } else if (atomicCAS(&F.lock, 0u, 1u) == 0u) {
+            // this wave fetches; the others go on with the seeds they have
+            r = V->range;
+            if ((uint32_t)r >= (uint32_t)(r >> 32) && !V->done) {
+                r = next_chunk(grab, n_items, step);
+                if (r == 0ull) {
+                    atomicExch(&F.done, 1u);
+                    ok = 0;
+                } else {
+                    s = (uint32_t)r;
+                    m = min(step, (uint32_t)(r >> 32) - s);
+                    atomicExch(&F.range, r + step);
+                }
+            }
+            __threadfence_block();
+            atomicExch(&F.lock, 0u);
+        }
+    }
+    next = (uint32_t)__builtin_amdgcn_readfirstlane((int)s);
+    n = (uint32_t)__builtin_amdgcn_readfirstlane((int)m);
+    return __builtin_amdgcn_readfirstlane((int)ok) != 0;
+}
+
+// Waves per SIMD the counting kernel is compiled for (the compiler then keeps
+// it within 512 / kCountOccupancy VGPRs).
+constexpr int kCountOccupancy = EMT_COUNT_OCCUPANCY;
+
+// What the lines of one class walk and test, in scalar registers.
+struct LineClass {
+    const uint2 *recs, *ent;
+    const float4 *sorted;
+    uint32_t nu, nv, bu, plane, goff;
+    int face, packed, c8, c4;  // packed words: u = word + c8 column, v = word + c4 row
+};
+
+template <class T>
+__device__ __forceinline__ T *uniform(T *p) {
+    const unsigned long long a = (unsigned long long)p;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
+    return (T *)(((unsigned long long)hi << 32) | lo);
+}
+
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ uint32_t uniform(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+}
+
+__device__ __forceinline__ LineClass line_class_of(const DevPtrs &d, uint32_t v, uint32_t cls) {
+    const LineGrid *L = line_grid_of(d, v);
+    LineClass K;
+    const uint32_t n_sub = (uint32_t)(L->sub * L->sub), a = uniform(cls / n_sub);
+    const uint32_t sub = cls - a * n_sub, n = d.grids[v].n;
+    K.goff = uniform(d.grids[v].grain_off);
+    K.nu = uniform((uint32_t)L->nu[a]);
+    K.nv = uniform((uint32_t)L->nv[a]);
+    K.bu = uniform((uint32_t)L->bu[a]);
+    K.plane = uniform(L->plane[a]);
+    K.recs = uniform(d.lrec + (size_t)line_recs(d.nc) * K.goff + L->face_off[a] +
+                     (size_t)sub * (uint32_t)L->ns[a] * K.plane);
+    K.ent = uniform(d.lent + line_pool((uint32_t)d.nc, K.goff, n, cls));
+    K.sorted = uniform(d.lsg + 3 * (size_t)K.goff + (size_t)a * n);
+    K.face = (int)a;
+    K.packed = uniform(L->packed);
+    K.c8 = uniform(8 * L->c);
+    K.c4 = uniform(4 * L->c);
+    return K;
+}
+
+// A grain's coordinates in the axes of face a: along it, u, v (and its index).
+__device__ __forceinline__ int4 line_axes(int4 g, int a) {
+    return make_int4(a == 0 ? g.x : a == 1 ? g.y : g.z, a == 0 ? g.y : g.x, a == 2 ? g.y : g.z, g.w);
+}
+
+// Takes up to 64 words off the queue's end and tests their grains, one a
+// lane. A cell's first word that points to a list, and a list word with more
+// behind it, put their successor back. Counting adds a hit to its line's
+// count; listing (kEmit) takes that position in the candidate's member list
+// (in any order: the merge treats a list as a set and the fit orders it).
+// Returns how many grains it tested.
+template <bool kFinite, bool kEmit>
+__device__ __forceinline__ uint32_t count_test(CountLds<kFinite, kEmit> &Q, uint32_t &qn,
+                                               const LineClass &K, int tol_r, const DevPtrs &d,
+                                               int lane) {
+    const uint32_t m = min(qn, 64u);
+    qn -= m;
+    const uint2 item = Q.queue[qn + min((uint32_t)lane, m - 1u)];
+    const uint32_t at = item.x & ((1u << kItemLane) - 1u), sl = (item.x >> kItemLane) & 63u;
+    const uint2 w = K.ent[at];
+    const float4 A = Q.la[sl], C = Q.lc[sl];
+    const bool on = (uint32_t)lane < m, list = (item.x & kItemList) != 0;
+    const bool flag = (int)w.x < 0, ptr = !list && flag, more = on && flag;
+    float3 h;
+    uint32_t rel;
+    if (K.packed) {
+        h.x = (float)(w.x & 0x7ffffu);
+        // (bit 31 of w.x is the list flag)
+        h.y = (float)(((int)(w.x << 1) >> 20) + __mul24((int)(item.y >> 19), K.c8));
+        h.z = (float)(((int)(w.y << 20) >> 20) + __mul24((int)((item.y >> 2) & 0x3fffu), K.c4));
+        rel = w.y >> 12;
+    } else {
+        const float4 g = K.sorted[ptr ? 0u : w.x & ~kLineList];
+        h = make_float3(g.x, g.y, g.z);
+        rel = w.y;
+    }
+    const unsigned long long mm = __ballot(more);
+    if (mm) {
+        wave_lds_sync();  // the items have been read
+        if (more)
+            Q.queue[qn + (uint32_t)__popcll(mm & lanes_below())] =
+                make_uint2((ptr ? w.y : at + 1u) | (sl << kItemLane) | kItemList, item.y);
+        qn += (uint32_t)__popcll(mm);
+        wave_lds_sync();
+    }
+    const float c0 = fmaf(h.y, A.z, fmaf(h.z, -A.y, C.x));
+    const float c1 = fmaf(h.z, A.x, fmaf(h.x, -A.z, C.y));
+    const float c2 = fmaf(h.x, A.y, fmaf(h.y, -A.x, C.z));
+    const float fc = fmaf(c0, c0, fmaf(c1, c1, c2 * c2));
+    const bool test = on && !ptr;
+    bool ok = test && fc <= C.w;
+    if (ok && fc > A.w) {
+        // inside the band: decide in int64 from the integer grains (rare)
+        const int dx = (int)A.x, dy = (int)A.y, dz = (int)A.z;
+        const long long D = (long long)dx * dx + (long long)dy * dy + (long long)dz * dz;
+        const int4 gi = line_axes(d.sg[Q.lp[sl]], K.face);
+        const long long wx = (int)h.x - gi.x, wy = (int)h.y - gi.y, wz = (int)h.z - gi.z;
+        const long long e0 = wy * dz - wz * dy, e1 = wz * dx - wx * dz, e2 = wx * dy - wy * dx;
+        ok = e0 * e0 + e1 * e1 + e2 * e2 <= (long long)tol_r * tol_r * D;
+    }
+    if constexpr (kFinite) {
+        const int4 hi = make_int4((int)h.x, (int)h.y, (int)h.z, 0);
+        const int4 Ai = make_int4((int)A.x, (int)A.y, (int)A.z, 0);
+        ok = ok && axial_ok(hi, Ai, Q.pc[sl]);
+    }
+    if (ok) {
+        const uint32_t n = atomicAdd(&Q.cnt[sl], 1u);
+        if constexpr (kEmit) {
+            const uint2 mo = Q.mo[sl];
+            if (n < mo.y) d.members[mo.x + n] = K.goff + rel;
+        }
+    }
+    return (uint32_t)__popcll(__ballot(test));
+}
+
+// kEmit: the members stage. The same walk and test over the candidates
+// instead of the seeds, listing each candidate's grains (its count is known:
+// the list must come out exactly that long).
+template <bool kFinite, bool kEmit>
+__global__ void __launch_bounds__(kCountBlock) __attribute__((amdgpu_waves_per_eu(kCountOccupancy)))
+k_count(DevPtrs d, Caps c, Params P) {
+    __shared__ CountLds<kFinite, kEmit> sQ[kCountWaves];
+    __shared__ Feed s_feed;
+    const int lane = lane_id();
+    CountLds<kFinite, kEmit> &Q = sQ[threadIdx.x >> 6];
+    uint32_t n_items = d.cnt->n_seeds_ok;
+    if constexpr (kEmit) {
+        // nothing to list when the entries overflow their buffer (the call
+        // is re-run)
+        const bool skip = d.cnt->err || d.cnt->n_members > c.mem_cap;
+        n_items = skip ? 0u : min(d.cnt->n_cand, c.cand_cap);
+    }
+    unsigned long long tests = 0, hits = 0;
+    // The listing instance has range counters of its own: the counting one
+    // leaves its counters used up. A wave takes 64 seeds at a time, or fewer
+    // when there are too few for every wave.
+    uint32_t *grab = d.grab + (kEmit ? 8 * 16 : 0);
+    const uint32_t step = min(64u, max(16u, n_items / (grid_threads() >> 6)));
+    if (threadIdx.x == 0) {
+        const uint32_t size = chunk_size(n_items, step), per = chunks_apart(n_items, size);
+        s_feed.range = n_items < kApartSeeds
+                           ? chunk_range(blockIdx.x, size, n_items)
+                           : chunk_range((blockIdx.x & 7u) * per + (blockIdx.x >> 3), size, n_items);
+        s_feed.lock = 0u;
+        s_feed.done = 0u;
+    }
+    __syncthreads();
+    for (;;) {
+        uint32_t s0, n_here;
+        if (!take_seeds(s_feed, grab, n_items, step, s0, n_here)) break;
+        if (n_here == 0) {
+            __builtin_amdgcn_s_sleep(4);  // another wave is fetching a chunk
+            continue;
+        }
+        // one seed a lane: line constants, class and crossing points
+        const uint32_t s = s0 + (uint32_t)lane;
+        const bool have = (uint32_t)lane < n_here;
+        uint32_t key = 0xffffffffu, th = 0, mcap = 0;
+        int iu = -1, idu = 0, iv = -1, idv = 0;
+        float klo = 1.0e9f, khi = -1.0f;
+        if (have) {
+            uint2 pq;
+            uint32_t vw;
+            if constexpr (kEmit) {
+                const Cand cd = d.cand[s];
+                pq = make_uint2(cd.p, cd.q);
+                vw = cd.v;
+                const uint32_t off = d.mem_off[s];
+                mcap = ((unsigned long long)off + cd.n <= c.mem_cap) ? cd.n : 0u;
+                Q.mo[lane] = make_uint2(off, mcap);
+            } else {
+                pq = d.seeds[s];
+                vw = d.view_of[pq.x];
+            }
+            const int4 gi = d.sg[pq.x], gj = d.sg[pq.y];
+            const int dx = gj.x - gi.x, dy = gj.y - gi.y, dz = gj.z - gi.z;
+            th = seed_threshold(dx, dy, dz, P);
+            if constexpr (kEmit) {
+                // the merge's priority key and threshold of the candidate
+                d.key[s] = cand_key(d.cand[s].n, (uint32_t)gi.w, (uint32_t)gj.w);
+                if (P.thr_num) d.cand_thr[s] = th;
+            }
+            if constexpr (kFinite) Q.pc[lane] = axial_bounds(gi, dx, dy, dz, P.cyl_ext);
+            Q.lp[lane] = pq.x;
+            Q.cnt[lane] = 0u;
+            const LineGrid *L = line_grid_of(d, vw);
+            const int a = line_face(abs(dx), abs(dy), abs(dz));
+            // from here in the face's axes: x along it, y = u, z = v
+            const int4 ti = line_axes(gi, a), td = line_axes(make_int4(dx, dy, dz, 0), a);
+            float4 a4, c4;
+            line_consts(ti, td.x, td.y, td.z, P.r, a4, c4);
+            Q.la[lane] = a4;
+            Q.lc[lane] = c4;
+            const float ga = (float)ti.x, da = a4.x;
+            const float ida = __builtin_amdgcn_rcpf(da);
+            const float su = a4.y * ida, sv = a4.z * ida;
+            key = vw * (uint32_t)d.nc +
+                  (uint32_t)((a * L->sub + line_bin(su, L->sub)) * L->sub + line_bin(sv, L->sub));
+            const int nu = a == 0 ? L->nu[0] : a == 1 ? L->nu[1] : L->nu[2];
+            const int nv = a == 0 ? L->nv[0] : a == 1 ? L->nv[1] : L->nv[2];
+            const int ns = a == 0 ? L->ns[0] : a == 1 ? L->ns[1] : L->ns[2];
+            const float w = (float)L->w, ic = L->ic;
+            const float off0 = 0.5f * w - ga;
+            const float u0 = fmaf(su, off0, (float)(ti.y + L->reach)) * ic, du = su * w * ic;
+            const float v0 = fmaf(sv, off0, (float)(ti.z + L->reach)) * ic, dv = sv * w * ic;
+            iu = (int)(u0 * kLineOne);
+            idu = (int)rintf(du * kLineOne);
+            iv = (int)(v0 * kLineOne);
+            idv = (int)rintf(dv * kLineOne);
+            // slabs whose plane the line crosses inside the cells: a bound a
+            // slab too wide costs a look, not a result
+            klo = 0.0f;
+            khi = (float)(ns - 1);
+            if (fabsf(du) > 1e-5f) {
+                const float id = __builtin_amdgcn_rcpf(du);
+                const float t1 = -u0 * id, t2 = ((float)nu - u0) * id;
+                klo = fmaxf(klo, fminf(t1, t2) - 1.0f);
+                khi = fminf(khi, fmaxf(t1, t2) + 1.0f);
+            }
+            if (fabsf(dv) > 1e-5f) {
+                const float id = __builtin_amdgcn_rcpf(dv);
+                const float t1 = -v0 * id, t2 = ((float)nv - v0) * id;
+                klo = fmaxf(klo, fminf(t1, t2) - 1.0f);
+                khi = fminf(khi, fmaxf(t1, t2) + 1.0f);
+            }
+            if constexpr (kFinite) {
+                // grains of the cylinder lie within cyl_ext along the line
+                // and r across it of the seed's stretch of axis a
+                const float reach = (float)P.cyl_ext + (float)P.r + kMargin;
+                const float iw = __builtin_amdgcn_rcpf(w);
+                klo = fmaxf(klo, (fminf(ga, ga + da) - reach) * iw - 1.0f);
+                khi = fminf(khi, (fmaxf(ga, ga + da) + reach) * iw + 1.0f);
+            }
+        }
+        wave_lds_sync();
+        // the classes among the lanes, one after another
+        for (unsigned long long left = __ballot(have); left;) {
+            const uint32_t cls_key =
+                (uint32_t)__builtin_amdgcn_readlane((int)key, __ffsll((long long)left) - 1);
+            const bool mine = key == cls_key;
+            left &= ~__ballot(mine);
+            const uint32_t vw = cls_key / (uint32_t)d.nc;
+            const LineClass K = line_class_of(d, vw, cls_key - vw * (uint32_t)d.nc);
+            const float kmin = wave_min(mine ? klo : 1.0e9f), kmax = wave_max(mine ? khi : -1.0f);
+            if (kmin > kmax) continue;
+            const uint32_t k1 =
+                (uint32_t)__builtin_amdgcn_readfirstlane((int)kmax);
+            // crossing points in cells, kLineBits fractional bits; negative
+            // ones and those past the last cell fail one unsigned compare. (A
+            // line far outside may wrap into the cells: it then tests grains
+            // it need not.) Lanes of other classes stay outside.
+            const uint32_t k0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)kmin);
+            uint32_t u = mine ? (uint32_t)iu + k0 * (uint32_t)idu : 0xffffffffu;
+            uint32_t v = mine ? (uint32_t)iv + k0 * (uint32_t)idv : 0xffffffffu;
+            const uint32_t ddu = mine ? (uint32_t)idu : 0u, ddv = mine ? (uint32_t)idv : 0u;
+            const uint32_t lim_u = K.nu << kLineBits, lim_v = K.nv << kLineBits;
+            // a finite cylinder's own slabs (an empty range has none)
+            const uint32_t first = (uint32_t)klo, slabs = khi >= klo ? (uint32_t)khi - first : 0u;
+            const uint2 *recs = K.recs + (size_t)k0 * K.plane;
+            const uint32_t lane_tag = (uint32_t)lane << kItemLane;
+            uint32_t qn = 0;
+            for (uint32_t k = k0; k <= k1; k += kFetch) {
+                uint2 rec[kFetch];
+                uint32_t cell[kFetch];  // the cell crossed: u << 16 | v
+#pragma unroll
+                for (int f = 0; f < kFetch; ++f) {
+                    const uint32_t lim = k + (uint32_t)f <= k1 ? lim_u : 0u;  // uniform
+                    bool ok = u < lim && v < lim_v;
+                    if constexpr (kFinite) ok = ok && k + (uint32_t)f - first <= slabs;
+                    cell[f] = __builtin_amdgcn_perm(u, v, 0x07060302u);
+                    rec[f].x = 0u;
+                    if (ok) rec[f] = recs[__umul24((cell[f] >> 2) & 0x3fffu, K.bu) + (cell[f] >> 19)];
+                    recs += K.plane;
+                    u += ddu;
+                    v += ddv;
+                }
+#pragma unroll
+                for (int f = 0; f < kFetch; ++f) {
+                    // cell 8 (v & 3) + (u & 7) of the record
+                    const uint32_t bit = ((cell[f] & 3u) << 3) | ((cell[f] >> 16) & 7u);
+                    const uint32_t low = ~(~0u << bit);
+                    const bool in = (rec[f].x >> bit) & 1u;
+                    const unsigned long long m = __ballot(in);
+                    if (in)
+                        Q.queue[__builtin_amdgcn_mbcnt_hi(
+                            (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, qn))] =
+                            make_uint2((rec[f].y + (uint32_t)__popc(rec[f].x & low)) | lane_tag,
+                                       cell[f]);
+                    qn += (uint32_t)__popcll(m);
+                }
+                wave_lds_sync();
+                while (qn >= 64u) tests += count_test(Q, qn, K, P.r, d, lane);
+            }
+            while (qn > 0u) tests += count_test(Q, qn, K, P.r, d, lane);
+        }
+        wave_lds_sync();
+        if (have) {
+            const uint32_t n = Q.cnt[lane];
+            if constexpr (kEmit) {
+                // the same walk and predicate as the count: a list of another
+                // length is never expected; keep every entry a valid grain
+                // index and flag an internal error
+                if (mcap > 0 && n != mcap) {
+                    const uint32_t off = Q.mo[lane].x;
+                    for (uint32_t t = n; t < mcap; ++t) d.members[off + t] = Q.lp[lane];
+                    atomicOr(&d.cnt->err, 2u);
+                }
+            } else {
+                // only counts that reach the threshold are written, with their
+                // bit in the candidate mask (a few percent: scattered 4-byte
+                // stores of every count would each cost a partial line write)
+                hits += n;
+                if (n >= th) {
+                    d.seed_n[s] = n;
+                    atomicOr(&d.pass[s >> 5], 1u << (s & 31u));
+                }
+            }
+        }
+        wave_lds_sync();
+    }
+    if constexpr (!kEmit) {
+        add_spread(d.part64, 2, tests);
+        add_spread(d.part64, 3, wave_sum(hits));
+    }
+}
+
+// ----------------------------------------------- count / members, few grains
+//
+// Counting over the binned cells, for the calls few_grains names. A wave owns a chunk of
+// seeds; each lane holds
+// two seed slots in LDS. When a lane's walk ends it closes that slot and at
+// once takes the next seed of the chunk into its other slot, so the wave's
+// time is the sum of its lines' work rather than a multiple of the longest
+// one. Hit counts of a closed slot are final after the next queue flush,
+// which writes them out and frees the slot.
+//
+// The queue holds pieces: each run a lane queues is cut into pieces of at
+// most kPiece consecutive grains, and the flush gives every lane one piece.
+// The lane maps its piece to the run by one popcount, reads the seed's line
+// constants once, issues the loads of all kPiece grains together and tests
+// them against the one line, so the mapping and the line constants are paid
+// once per piece and the grain loads of a piece are in flight together.
+constexpr int kWaves = kBlock / 64;
+constexpr int kCountSlots = 128;
+constexpr int kPiece = 3;        // grains per queued piece
+constexpr int kLanePieces = 24;  // pieces a lane queues per step
+constexpr int kPencils = 6;      // pencils a lane fetches per step
+constexpr int kRefillMin = 32;   // waiting lanes that start a refill
+constexpr uint32_t kFewChunk = 128;             // seeds a wave takes at a time
+constexpr int kPieceCap = 128 * kLanePieces;    // queued pieces per wave
+constexpr int kRunCap = 64 * kPencils;          // queued runs per wave
+constexpr int kPieceWords = kPieceCap / 64;
+static_assert(64 * kLanePieces <= kPieceCap, "a step's pieces must fit the queue");
+static_assert(kPieceWords <= 64 && kPieceCap % 64 == 0, "one mask word per lane");
+static_assert(kPieceCap <= 4096 && kPiece * kLanePieces < 8192, "run record fields");
+static_assert((uint32_t)kPiece - 1u <= kSortedSpare, "piece size");
+
+template <bool kFinite, bool kEmit>
+struct FewLds {
+    // line constants per seed slot (floats): d, -(g_i x d), the band
+    // [tlo, thi] of the FP32 test, and the sorted position of g_i
+    float4 la[kCountSlots];  // dx, dy, dz, tlo
+    float4 lc[kCountSlots];  // -ex, -ey, -ez, thi
+    uint32_t lp[kCountSlots];  // sorted position of g_i (the int64 test)
+    int2 pc[kFinite ? kCountSlots : 1];  // finite cylinder: bounds of g_k.d
+    uint32_t cnt[kCountSlots];
+    // listing the members of candidates: where a slot's grains go, and how
+    // many its list holds (its count)
+    uint32_t out_off[kEmit ? kCountSlots : 1];
+    uint32_t ncap[kEmit ? kCountSlots : 1];
+    unsigned long long mask[kPieceWords];  // bit s: a run starts at piece s
+    uint32_t before[kPieceWords];          // runs starting before word w
+    uint2 run[kRunCap];  // first grain; first piece | seed slot << 12 | grains << 19
+};
 
 // One queued piece for a flush lane: its run's grains k0 .. k0 + m - 1, the
 // seed slot, the slot's line constants and the piece's grains, all loads
@@ -881,7 +1740,7 @@ __device__ __forceinline__ void line_consts(int4 gi, int dx, int dy, int dz, int
 struct Piece {
     uint32_t k0, m, sl;
     float4 A, C;
-    float4 h[kPiece];
+    int4 h[kPiece];
 };
 
 // Loads piece (w, lane) of a queue holding qn pieces. A lane past the end
@@ -889,9 +1748,9 @@ struct Piece {
 // stays inside the queue and the sorted grains, which carry kPiece - 1 spare
 // entries past the last one.
 template <bool kFinite, bool kEmit>
-__device__ __forceinline__ void piece_load(const CountLds<kFinite, kEmit> &Q, uint32_t w, uint32_t nw,
+__device__ __forceinline__ void piece_load(const FewLds<kFinite, kEmit> &Q, uint32_t w, uint32_t nw,
                                            uint32_t qn, unsigned long long upto, int lane,
-                                           const float4 *__restrict__ sgf, Piece &p) {
+                                           const int4 *__restrict__ sg, Piece &p) {
     const uint32_t wc = min(w, nw - 1u);
     const uint32_t s = (w << 6) + (uint32_t)lane;
     const bool valid = w < nw && s < qn;
@@ -904,7 +1763,7 @@ __device__ __forceinline__ void piece_load(const CountLds<kFinite, kEmit> &Q, ui
     p.m = valid ? min((rec.y >> 19) - (uint32_t)kPiece * q, (uint32_t)kPiece) : 0u;
     p.A = Q.la[p.sl];
     p.C = Q.lc[p.sl];
-    const float4 *pp = sgf + p.k0;
+    const int4 *pp = sg + p.k0;
 #pragma unroll
     for (int t = 0; t < kPiece; ++t) p.h[t] = pp[t];
 }
@@ -912,21 +1771,20 @@ __device__ __forceinline__ void piece_load(const CountLds<kFinite, kEmit> &Q, ui
 // The piece's hits as a bit mask over its grains: the FP32 test, the rare
 // band case in int64.
 template <bool kFinite, bool kEmit>
-__device__ __forceinline__ uint32_t piece_test(const CountLds<kFinite, kEmit> &Q, const Piece &p,
+__device__ __forceinline__ uint32_t piece_test(const FewLds<kFinite, kEmit> &Q, const Piece &p,
                                                int tol_r, const int4 *__restrict__ sg) {
     uint32_t n = 0, amb = 0;
 #pragma unroll
     for (int t = 0; t < kPiece; ++t) {
-        const float4 &h = p.h[t];
+        const float3 h = make_float3((float)p.h[t].x, (float)p.h[t].y, (float)p.h[t].z);
         const float c0 = fmaf(h.y, p.A.z, fmaf(h.z, -p.A.y, p.C.x));
         const float c1 = fmaf(h.z, p.A.x, fmaf(h.x, -p.A.z, p.C.y));
         const float c2 = fmaf(h.x, p.A.y, fmaf(h.y, -p.A.x, p.C.z));
         const float fc = fmaf(c0, c0, fmaf(c1, c1, c2 * c2));
         bool ok = (uint32_t)t < p.m;
         if constexpr (kFinite) {
-            const int4 hi = make_int4((int)h.x, (int)h.y, (int)h.z, 0);
             const int4 Ai = make_int4((int)p.A.x, (int)p.A.y, (int)p.A.z, 0);
-            ok = ok && axial_ok(hi, Ai, Q.pc[p.sl]);
+            ok = ok && axial_ok(p.h[t], Ai, Q.pc[p.sl]);
         }
         const bool in_lo = fc <= p.A.w, in_hi = fc <= p.C.w;
         n |= (ok && in_lo) ? (1u << t) : 0u;
@@ -952,17 +1810,14 @@ __device__ __forceinline__ uint32_t piece_test(const CountLds<kFinite, kEmit> &Q
     return n;
 }
 
-// Tests every queued piece, kFlushUnroll queue words per trip: the loads of
-// all of a trip's pieces are issued before any is tested, so a lane has
-// several chains of LDS and grain loads in flight instead of one.
+// Tests every queued piece.
 // Counting adds a piece's hits to its seed's count with one LDS atomic;
 // listing (kEmit) takes as many positions in the candidate's member list and
 // writes the hit grains' sorted positions there (in any order: the merge
 // treats a list as a set and the fit orders it).
 template <bool kFinite, bool kEmit>
-__device__ __forceinline__ void count_flush(CountLds<kFinite, kEmit> &Q, uint32_t qn, int tol_r,
+__device__ __forceinline__ void count_flush(FewLds<kFinite, kEmit> &Q, uint32_t qn, int tol_r,
                                             const int4 *__restrict__ sg,
-                                            const float4 *__restrict__ sgf,
                                             uint32_t *__restrict__ members, int lane) {
     wave_lds_sync();
     const uint32_t nw = (qn + 63) >> 6;
@@ -973,26 +1828,21 @@ __device__ __forceinline__ void count_flush(CountLds<kFinite, kEmit> &Q, uint32_
     }
     wave_lds_sync();
     const unsigned long long upto = (2ull << lane) - 1ull;
-    for (uint32_t w = 0; w < nw; w += kFlushUnroll) {
-        Piece p[kFlushUnroll];
+    for (uint32_t w = 0; w < nw; ++w) {
+        Piece p;
+        piece_load(Q, w, nw, qn, upto, lane, sg, p);
+        const uint32_t bits = piece_test(Q, p, tol_r, sg);
+        if (bits) {
+            const uint32_t n = (uint32_t)__popc(bits);
+            const uint32_t at = atomicAdd(&Q.cnt[p.sl], n);
+            if constexpr (kEmit) {
+                const uint32_t cap = Q.ncap[p.sl], base = Q.out_off[p.sl];
+                uint32_t pos = at;
 #pragma unroll
-        for (int u = 0; u < kFlushUnroll; ++u)
-            piece_load(Q, w + (uint32_t)u, nw, qn, upto, lane, sgf, p[u]);
-#pragma unroll
-        for (int u = 0; u < kFlushUnroll; ++u) {
-            const uint32_t bits = piece_test(Q, p[u], tol_r, sg);
-            if (bits) {
-                const uint32_t n = (uint32_t)__popc(bits);
-                const uint32_t at = atomicAdd(&Q.cnt[p[u].sl], n);
-                if constexpr (kEmit) {
-                    const uint32_t cap = Q.ncap[p[u].sl], base = Q.out_off[p[u].sl];
-                    uint32_t pos = at;
-#pragma unroll
-                    for (int t = 0; t < kPiece; ++t) {
-                        if (bits & (1u << t)) {
-                            if (pos < cap) members[base + pos] = p[u].k0 + (uint32_t)t;
-                            ++pos;
-                        }
+                for (int t = 0; t < kPiece; ++t) {
+                    if (bits & (1u << t)) {
+                        if (pos < cap) members[base + pos] = p.k0 + (uint32_t)t;
+                        ++pos;
                     }
                 }
             }
@@ -1003,20 +1853,15 @@ __device__ __forceinline__ void count_flush(CountLds<kFinite, kEmit> &Q, uint32_
     wave_lds_sync();
 }
 
-// Waves per SIMD the counting kernel is compiled for: its test phase waits
-// on grain loads, so more resident waves hide more of that latency (the
-// compiler then keeps the kernel within 512 / kCountOccupancy VGPRs).
-constexpr int kCountOccupancy = EMT_COUNT_OCCUPANCY;
-
 // kEmit: the members stage. The same walk and test over the candidates
 // instead of the seeds, listing each candidate's grains (its count is known:
 // the list must come out exactly that long).
 template <bool kFinite, bool kEmit>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kCountOccupancy)))
-k_count(DevPtrs d, Caps c, Params P) {
-    __shared__ CountLds<kFinite, kEmit> sQ[kWaves];
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4)))
+k_count_few(DevPtrs d, Caps c, Params P) {
+    __shared__ FewLds<kFinite, kEmit> sQ[kWaves];
     const int lane = lane_id();
-    CountLds<kFinite, kEmit> &Q = sQ[threadIdx.x >> 6];
+    FewLds<kFinite, kEmit> &Q = sQ[threadIdx.x >> 6];
     uint32_t n_items = d.cnt->n_seeds_ok;
     if constexpr (kEmit) {
         // nothing to list when the entries overflow their buffer (the call
@@ -1027,28 +1872,15 @@ k_count(DevPtrs d, Caps c, Params P) {
     if (lane < kPieceWords) Q.mask[lane] = 0ull;
     wave_lds_sync();
     unsigned long long tests = 0, hits = 0;
-    // Which seeds a wave counts. Few seeds (one view or so, whose grains fit
-    // in L2): wave gw takes chunks gw, gw + nwv, gw + 2 nwv, ... of
-    // kChunkSeeds seeds. Many seeds: they are split into eight ranges, one
-    // per XCD (workgroups are dealt to the XCDs in turn); a wave takes grabs
-    // from its own XCD's range, so that XCD's L2 holds the grains of those
-    // views only, and moves on to the other ranges when its own is used up;
-    // grabs shrink as a range empties, so the waves finish together. (Grabs
-    // cost a device-scope atomic each, too many for a single view.) The
-    // listing instance has range counters of its own: the counting one
-    // leaves its counters used up.
-    const bool dyn = n_items > (uint32_t)EMT_DYN_MIN_SEEDS;
-    const uint32_t gw = grid_tid() >> 6, nwv = grid_threads() >> 6;
-    const uint32_t xcd = blockIdx.x & 7u;
-    const uint32_t per = ((n_items + 7u) / 8u + 63u) & ~63u;
-    const uint32_t wpx = max(1u, (gridDim.x >> 3) * kWaves);
+    // wave gw takes chunks gw, gw + nwv, gw + 2 nwv, ... of kFewChunk seeds;
     // chunks shrink (to a quarter wave at least) when there are too few
     // items to give every wave a full one: a long walk per lane is better
     // than idle waves
-    const uint32_t cs = min((uint32_t)kChunkSeeds, max(16u, (n_items + nwv - 1u) / nwv));
+    const uint32_t gw = grid_tid() >> 6, nwv = grid_threads() >> 6;
+    const uint32_t cs = min(kFewChunk, max(16u, (n_items + nwv - 1u) / nwv));
     uint32_t chunk = gw * cs;
-    uint32_t next = dyn ? 0u : min(chunk, n_items);
-    uint32_t end = dyn ? 0u : min(n_items, chunk + cs);
+    uint32_t next = min(chunk, n_items);
+    uint32_t end = min(n_items, chunk + cs);
     bool more = true;
     bool have = false;
     bool pend0 = false, pend1 = false;  // slot closed, count not yet written
@@ -1057,9 +1889,9 @@ k_count(DevPtrs d, Caps c, Params P) {
     int cur = lane;
     Pencil W;
     W.live = false;
-    Run run[kFetch];
+    Run run[kPencils];
 #pragma unroll
-    for (int f = 0; f < kFetch; ++f) run[f] = Run{0, 0};
+    for (int f = 0; f < kPencils; ++f) run[f] = Run{0, 0};
     uint32_t qn = 0, nr = 0;
     // counts of closed slots are final after a flush: write them, free slots
     auto close = [&](int sl, uint32_t idx, uint32_t th) {
@@ -1098,18 +1930,12 @@ k_count(DevPtrs d, Caps c, Params P) {
     };
     for (;;) {
         {
-            if (dyn) {
-                if (next >= end && more)
-                    more = xcd_grab(d.grab + (kEmit ? 8 * 16 : 0), xcd, per, n_items, wpx, 64u,
-                                    4096u, next, end);
-            } else {
+            more = chunk + nwv * cs < n_items;
+            if (next >= end && more) {
+                chunk += nwv * cs;
+                next = chunk;
+                end = min(n_items, chunk + cs);
                 more = chunk + nwv * cs < n_items;
-                if (next >= end && more) {
-                    chunk += nwv * cs;
-                    next = chunk;
-                    end = min(n_items, chunk + cs);
-                    more = chunk + nwv * cs < n_items;
-                }
             }
             // take the next seeds into free slots. Setting up a seed (its
             // loads, line constants and walk) runs with whatever lanes take
@@ -1160,23 +1986,23 @@ k_count(DevPtrs d, Caps c, Params P) {
                 Q.lc[cur] = C;
                 Q.lp[cur] = pq.x;
                 Q.cnt[cur] = 0;
-                W.init(&d.grids[v], gi, dx, dy, dz, P.r, true, 0, 1, kFinite ? P.cyl_ext : -1);
+                W.init(&d.grids[v], gi, dx, dy, dz, P.r, kFinite ? P.cyl_ext : -1);
                 have = true;
             }
             if (refill) next = min(end, next + n_want);
-            // fetch kFetch runs once the previous ones are queued
+            // fetch kPencils runs once the previous ones are queued
             bool drained = true;
 #pragma unroll
-            for (int f = 0; f < kFetch; ++f) drained = drained && run[f].k >= run[f].e;
+            for (int f = 0; f < kPencils; ++f) drained = drained && run[f].k >= run[f].e;
             if (have && W.live && drained) {
 #pragma unroll
-                for (int f = 0; f < kFetch; ++f) W.fetch(d.cell_start, run[f]);
+                for (int f = 0; f < kPencils; ++f) W.fetch(d.cell_start, run[f]);
             }
             // queue up to kLanePieces pieces of the lane's runs
             uint32_t left = kLanePieces, mine = 0, nrun = 0, mtests = 0;
-            uint32_t len[kFetch], np[kFetch];
+            uint32_t len[kPencils], np[kPencils];
 #pragma unroll
-            for (int f = 0; f < kFetch; ++f) {
+            for (int f = 0; f < kPencils; ++f) {
                 const uint32_t avail = run[f].e > run[f].k ? run[f].e - run[f].k : 0u;
                 len[f] = min(avail, (uint32_t)kPiece * left);
                 np[f] = (len[f] + (uint32_t)kPiece - 1u) / (uint32_t)kPiece;
@@ -1190,8 +2016,8 @@ k_count(DevPtrs d, Caps c, Params P) {
             const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
             // room first: test what is queued if this step's runs do not fit
             if (qn + (tot & 0xffffu) > (uint32_t)kPieceCap ||
-                nr + (tot >> 16) > (uint32_t)kCountRunCap) {
-                count_flush(Q, qn, P.r, d.sg, d.sgf, d.members, lane);
+                nr + (tot >> 16) > (uint32_t)kRunCap) {
+                count_flush(Q, qn, P.r, d.sg, d.members, lane);
                 qn = 0;
                 nr = 0;
                 finalize();
@@ -1202,7 +2028,7 @@ k_count(DevPtrs d, Caps c, Params P) {
                 uint32_t ri = nr + (ex >> 16);
                 const uint32_t tag = (uint32_t)cur << 12;
 #pragma unroll
-                for (int f = 0; f < kFetch; ++f) {
+                for (int f = 0; f < kPencils; ++f) {
                     if (len[f]) {
                         Q.run[ri++] = make_uint2(run[f].k, pos | tag | (len[f] << 19));
                         atomicOr(&Q.mask[pos >> 6], 1ull << (pos & 63));
@@ -1217,7 +2043,7 @@ k_count(DevPtrs d, Caps c, Params P) {
             // a seed whose walk ended and whose runs are all queued is closed
             bool queued = true;
 #pragma unroll
-            for (int f = 0; f < kFetch; ++f) queued = queued && run[f].k >= run[f].e;
+            for (int f = 0; f < kPencils; ++f) queued = queued && run[f].k >= run[f].e;
             if (have && !W.live && queued) {
                 have = false;
                 if (cur == lane) pend0 = true; else pend1 = true;
@@ -1226,7 +2052,7 @@ k_count(DevPtrs d, Caps c, Params P) {
             const uint32_t n_blocked = (uint32_t)__popcll(__ballot(blocked));
             const bool all_done = __ballot(have) == 0 && next >= end && !more;
             if (all_done || n_blocked > 16) {
-                if (qn) count_flush(Q, qn, P.r, d.sg, d.sgf, d.members, lane);
+                if (qn) count_flush(Q, qn, P.r, d.sg, d.members, lane);
                 qn = 0;
                 nr = 0;
                 finalize();
@@ -1256,7 +2082,7 @@ __global__ void __launch_bounds__(kBlock) k_cand_scatter(DevPtrs d, Caps c, Para
     const uint32_t ns = d.cnt->n_seeds_ok;
     for (uint32_t v = grid_tid(); v < d.desc->n_views; v += grid_threads()) {
         const uint32_t g0 = d.grids[v].grain_off, g1 = g0 + d.grids[v].n;
-        const uint32_t s0 = d.seed_off[g0], s1 = d.seed_off[g1];
+        const uint32_t s0 = d.seed_off[d.nc * g0], s1 = d.seed_off[d.nc * g1];
         d.view_seeds[v] = s1 - s0;
         d.view_cand[v] = cand_before(d, min(s1, ns)) - cand_before(d, min(s0, ns));
     }
@@ -1494,7 +2320,7 @@ __global__ void __launch_bounds__(kBlock) k_round(DevPtrs d, Params P, int round
 // First candidate of view v: candidates are listed in seed order, and a
 // view's seeds are contiguous.
 __device__ __forceinline__ uint32_t view_first_cand(const DevPtrs &d, uint32_t v, uint32_t ns) {
-    return cand_before(d, min(d.seed_off[d.grids[v].grain_off], ns));
+    return cand_before(d, min(d.seed_off[d.nc * d.grids[v].grain_off], ns));
 }
 
 // Candidates of different views share no grain, so the rounds the grid-wide
@@ -2387,6 +3213,7 @@ constexpr uint32_t kPersistentBlocks = EMT_PERSISTENT_BLOCKS;  // 8 blocks of 4 
 // bound by its LDS and registers), so no workgroup waits for another's slot
 constexpr uint32_t kCountBlocks = EMT_COUNT_BLOCKS;
 static_assert(kCountBlocks % 8 == 0, "whole workgroups per XCD");
+constexpr uint32_t kFewBlocks = 1024;  // one resident generation of k_count_few
 
 }  // namespace
 
@@ -2402,28 +3229,44 @@ void launch_bin(const DevPtrs &d, const Caps &c, const Params &P, hipStream_t s)
     const uint32_t bx = blocks_for(c.max_view_n, 64);
     dim3 grid(bx, c.n_views);
     k_bbox<<<grid, kBlock, 0, s>>>(d.xyz, d.grids, d.view_of, d.desc);
-    k_grid<<<(c.n_views + 63) / 64, 64, 0, s>>>(d.grids, d.desc, P);
+    k_grid<<<(c.n_views + 63) / 64, 64, 0, s>>>(d.grids, d.lines, d.lpool, d.lcoarse, d.nc,
+                                                   d.desc, P);
     k_hist<<<grid, kBlock, 0, s>>>(d.xyz, d.grids, d.cell_of, d.rank, d.cell_count, d.desc);
     scan_excl(d.cell_count, &d.desc->n_cells_m1, c.n_cells, d.scan_part, d.cell_start, nullptr, s);
-    k_scatter<<<grid, kBlock, 0, s>>>(d.xyz, d.grids, d.cell_of, d.rank, d.cell_start, d.sg, d.sgf,
+    k_scatter<<<grid, kBlock, 0, s>>>(d.xyz, d.grids, d.cell_of, d.rank, d.cell_start, d.sg,
                                       d.desc);
 }
 
 void launch_seeds(const DevPtrs &d, const Caps &c, const Params &P, hipStream_t s) {
-    const uint32_t nb = blocks_for(64ull * c.n_total, 4 * kPersistentBlocks);
+    // whole runs for every XCD
+    const uint32_t nb = (blocks_for(64ull * c.n_total, 4 * kPersistentBlocks) + 8u * kSeedRun - 1u) /
+                        (8u * kSeedRun) * (8u * kSeedRun);
+    if (d.nc > 1) k_line_order<<<dim3(3 + d.nc, c.n_views), kOrderBlock, 0, s>>>(d);
     k_seeds<false><<<nb, kBlock, 0, s>>>(d, c, P);
     // the scan total counts every seed (it wraps only above 2^32 - 1 a call)
     // offsets in uint32: exact whenever the total fits, which k_seed_total checks
-    scan_excl(d.seed_cnt, &d.desc->n_total, c.n_total, d.scan_part, d.seed_off, &d.cnt->n_seeds, s);
+    scan_excl(d.seed_cnt, &d.desc->n_anchor, (uint32_t)d.nc * c.n_total, d.scan_part, d.seed_off, &d.cnt->n_seeds, s);
     k_seed_total<<<1, 64, 0, s>>>(d.cnt, d.part64, c.seed_cap);
     k_seeds<true><<<nb, kBlock, 0, s>>>(d, c, P);
 }
 
 void launch_count(const DevPtrs &d, const Caps &c, const Params &P, hipStream_t s) {
+    if (d.nc == 1) {
+        if (P.cyl_ext >= 0)
+            k_count_few<true, false><<<kFewBlocks, kBlock, 0, s>>>(d, c, P);
+        else
+            k_count_few<false, false><<<kFewBlocks, kBlock, 0, s>>>(d, c, P);
+        return;
+    }
+    // workgroups sharing a class's planes: about 4096 in all, at least four
+    const uint32_t parts = std::max(4u, std::min(128u, 4096u / ((uint32_t)d.nc * c.n_views)));
+    const dim3 grid(parts, d.nc, c.n_views);
+    k_line_fill<0><<<grid, kLineBlock, 0, s>>>(d, P);
+    k_line_fill<1><<<grid, kLineBlock, 0, s>>>(d, P);
     if (P.cyl_ext >= 0)
-        k_count<true, false><<<kCountBlocks, kBlock, 0, s>>>(d, c, P);
+        k_count<true, false><<<kCountBlocks, kCountBlock, 0, s>>>(d, c, P);
     else
-        k_count<false, false><<<kCountBlocks, kBlock, 0, s>>>(d, c, P);
+        k_count<false, false><<<kCountBlocks, kCountBlock, 0, s>>>(d, c, P);
 }
 
 void launch_candidates(const DevPtrs &d, const Caps &c, const Params &P, hipStream_t s) {
@@ -2436,10 +3279,17 @@ void launch_members(const DevPtrs &d, const Caps &c, const Params &P, hipStream_
     scan_excl(d.cand_n, &d.cnt->n_cand, c.cand_cap, d.scan_part, d.mem_off, &d.cnt->n_members, s);
     k_member_total<<<1, 64, 0, s>>>(d.cnt, d.part64);
     // the counting kernel's walk and test, listing the grains of each candidate
+    if (d.nc == 1) {
+        if (P.cyl_ext >= 0)
+            k_count_few<true, true><<<kFewBlocks, kBlock, 0, s>>>(d, c, P);
+        else
+            k_count_few<false, true><<<kFewBlocks, kBlock, 0, s>>>(d, c, P);
+        return;
+    }
     if (P.cyl_ext >= 0)
-        k_count<true, true><<<kCountBlocks, kBlock, 0, s>>>(d, c, P);
+        k_count<true, true><<<kCountBlocks, kCountBlock, 0, s>>>(d, c, P);
     else
-        k_count<false, true><<<kCountBlocks, kBlock, 0, s>>>(d, c, P);
+        k_count<false, true><<<kCountBlocks, kCountBlock, 0, s>>>(d, c, P);
 }
 
 void launch_merge_init(const DevPtrs &d, const Caps &c, const Params &, hipStream_t s) {

@@ -1,0 +1,124 @@
+"""The line grids of the counting kernel against the oracle, at the sizes and
+shapes where their rules change: the number of grains from which they are
+used, cells too large for packed list words, lists that overflow their share
+(a coarser grid then), every face as the long one, a large radius, and the
+budgets that leave room for fewer line classes. Everything is compared
+exactly (candidates element by element; the fit by tests/parity.py)."""
+import numpy as np
+import pytest
+
+from oracle import oracle
+from paper_1311_5334_amd import synth
+from tests.parity import assert_candidates_equal, assert_view_parity
+
+pytestmark = pytest.mark.gpu
+
+FEW = 8192  # grains of a call up to which the binned cells are walked
+
+
+@pytest.fixture(scope="module")
+def emt():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_1311_5334_amd import emt as e
+    e.load()
+    return e
+
+
+def check(emt, views, oracle_cfg=None, **cfg):
+    oracle_cfg = oracle_cfg or {}
+    with emt.Tracker(device=0, flags=emt.EMT_F_CANDIDATES, **cfg) as tr:
+        got = tr(views)
+        cands = [tr.candidates(v) for v in range(len(views))]
+    assert sum(len(c) for c in cands) > 0
+    for xyz, g, c in zip(views, got, cands):
+        ref = oracle.track_view(xyz, **oracle_cfg)
+        assert_candidates_equal(c, ref)
+        assert_view_parity(xyz, g, ref)
+
+
+def moderate(seed, side=205.0, density=4.4):
+    return synth.make_density_view(seed, density, side).xyz
+
+
+def with_lines(seed, n, box, n_lines, per_line):
+    """Uniform grains in a box (units) and straight rows of grains across it."""
+    rng = np.random.default_rng(seed)
+    box = np.asarray(box, np.float64)
+    parts = [rng.uniform(0, 1, (n, 3)) * box]
+    for _ in range(n_lines):
+        p, d = rng.uniform(0.3, 0.7, 3) * box, rng.normal(size=3)
+        d /= np.linalg.norm(d)
+        t = np.arange(per_line) * 700.0
+        row = p + t[:, None] * d
+        parts.append(row[np.all((row >= 0) & (row <= box), axis=1)])
+    return np.rint(np.concatenate(parts)).astype(np.int32)
+
+
+@pytest.mark.parametrize("n", [FEW - 1, FEW, FEW + 1])
+def test_number_of_grains_that_switches(emt, n):
+    xyz = moderate(11)
+    assert len(xyz) > n
+    check(emt, [xyz[:n]])
+
+
+@pytest.mark.parametrize("order", [(0, 1, 2), (2, 0, 1), (1, 2, 0)])
+def test_every_axis_as_the_short_one(emt, order):
+    xyz = np.ascontiguousarray(moderate(12, side=230.0)[:, order])
+    check(emt, [xyz, -xyz])
+
+
+def test_cells_too_large_to_pack(emt):
+    # the largest span (2^18 units) in two axes, few grains per volume
+    side = float(1 << 18)
+    xyz = with_lines(13, 9000, (side, side, 5000.0), 60, 40)
+    xyz[0], xyz[1] = (0, 0, 0), (1 << 18, 1 << 18, 5000)
+    check(emt, [xyz])
+
+
+def test_one_plane(emt):
+    check(emt, [with_lines(14, 9000, (120000.0, 120000.0, 0.0), 40, 30)])
+
+
+def test_lists_that_overflow_their_share(emt):
+    # a plane lattice of pitch 300 = 3 cells, its grains at a slab's edge and
+    # placed so that their rectangles cover 4 x 4 cells of the steepest
+    # classes: 16 words a grain, 12 are a class's share
+    k = np.arange(95) * 300 + 4
+    x, y = np.meshgrid(k, k)
+    xyz = np.stack([x.ravel(), y.ravel(), np.zeros(x.size)], axis=1).astype(np.int32)
+    xyz = np.concatenate([np.zeros((1, 3), np.int32), xyz])
+    check(emt, [xyz], {"R": 700, "n_min": 40}, seed_dist=700, min_grains=40)
+
+
+def test_views_of_all_kinds_in_one_call(emt):
+    check(emt, [moderate(15)[:40], moderate(16), np.zeros((0, 3), np.int32),
+                synth.make_density_view(17, 14.0, 100.0).xyz,
+                with_lines(18, 2000, (150000.0, 90000.0, 4000.0), 20, 20)])
+
+
+def test_large_radius(emt):
+    xyz = synth.make_density_view(19, 1.1, 420.0).xyz
+    assert len(xyz) > FEW
+    check(emt, [xyz], {"r": 300, "n_min": 14}, tol_radius=300, min_grains=14)
+
+
+def test_budgets_with_room_for_fewer_classes(emt):
+    xyz = moderate(20)
+    assert FEW < len(xyz) <= 2 * FEW
+    # from room for every class (about 173 MB) down to the least that is
+    # accepted, where three classes are left
+    mb = 200
+    accepted = []
+    while mb > 100:
+        try:
+            with emt.Tracker(device=0, hbm_budget=mb << 20) as tr:
+                tr([xyz])
+        except emt.EmtError as e:
+            assert e.rc == emt.EMT_ENOMEM
+            break
+        accepted.append(mb)
+        mb -= 1
+    assert len(accepted) > 40
+    for b in (accepted[0], 150, accepted[-1]):
+        check(emt, [xyz], hbm_budget=b << 20)
