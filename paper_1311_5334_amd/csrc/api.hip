@@ -58,7 +58,8 @@ struct emt_ctx {
     // device buffers, grown on demand
     DevArena grain_buf, cell_buf, seed_buf, cand_buf, mem_buf, view_buf, misc_buf;
     DevArena stack_buf;  // grain recognition: stack copy, block counts, scan, output
-    uint32_t *h_small = nullptr;  // pinned: two words exchanged with the device
+    uint32_t *h_small = nullptr;  // mapped pinned word the device writes
+    uint32_t *d_small = nullptr;  // its address on the device
     DevPtrs d{};
     // capacities the buffers currently hold (nc: line classes)
     Caps held_caps{};
@@ -662,12 +663,11 @@ int batch_caps(const emt_ctx *ctx, unsigned long long n_total, uint32_t n_views,
     return EMT_OK;
 }
 
-// Scratch of emt_find_grains_noalloc: the per-tile grain counts, per-group
-// sums, staging slots and the grain total of one recognition call, carved
-// in that order (1 byte a stack pixel plus ~0.1 %). One copy per device,
-// held until the process ends; every call on a device shares it and keeps
-// the last call's contents (the per-group sums, the only words read before
-// they are written, are cleared by a kernel at the start of each call).
+// Scratch of emt_find_grains_noalloc: the per-tile grain counts and staging
+// slots of one recognition call, carved in that order (1 byte a stack pixel
+// plus ~0.05 %). One copy per device, held until the process ends; every call
+// on a device shares it and keeps the last call's contents (no word is read
+// before it is written).
 // Host code never passes the array's name to a kernel: it uses the device
 // address emt_create resolves for each device (scratch_dev).
 constexpr size_t kNoAllocScratchBytes = (size_t)EMT_NOALLOC_SCRATCH_BYTES;
@@ -700,9 +700,9 @@ void *scratch_dev(int device) {
 // Bytes the recognition buffers take when carved from one block.
 size_t grain_scratch_bytes(const StackGeom &G) {
     auto r = [](size_t b) { return ((b + 255) / 256) * 256; };
-    return r(bytes_of<uint32_t>(grain_tile_count(G))) +
+    return r(bytes_of<uint16_t>(grain_tile_count(G))) +
            r(bytes_of<uint32_t>(grain_group_count(G))) +
-           r(bytes_of<uint16_t>(grain_stage_slots(G))) + r(bytes_of<uint32_t>(1));
+           r(bytes_of<uint16_t>(grain_stage_slots(G)));
 }
 
 }  // namespace
@@ -833,7 +833,7 @@ int emt_create(const emt_config *cfg, emt_ctx **out) {
         return rc;
     }
     size_t small_cap = 0;
-    if ((rc = pinned(ctx, ctx->h_small, small_cap, 4)) != EMT_OK) {
+    if ((rc = mapped(ctx, ctx->h_small, ctx->d_small, small_cap, 4)) != EMT_OK) {
         emt_destroy(ctx);
         return rc;
     }
@@ -1088,23 +1088,20 @@ static int find_grains_impl(emt_ctx *ctx, const uint8_t *stack, const emt_stack_
         if (!ctx->h_small) return EMT_EDEVICE;  // made by emt_create
         p = (char *)static_buf;
     } else {
-        const size_t bytes = (dev ? 0 : bytes_of<uint8_t>((size_t)npix)) + bytes_of<uint32_t>(nt) +
+        const size_t bytes = (dev ? 0 : bytes_of<uint8_t>((size_t)npix)) + bytes_of<uint16_t>(nt) +
                              bytes_of<uint32_t>(ng) + bytes_of<uint16_t>(grain_stage_slots(G)) +
-                             bytes_of<uint32_t>(1) +
                              (dev ? 0 : bytes_of<int32_t>(3 * (size_t)max_out));
         int rc;
         if ((rc = arena(ctx, ctx->stack_buf, bytes))) return rc;
-        size_t cap = 0;
-        if (!ctx->h_small && (rc = pinned(ctx, ctx->h_small, cap, 4))) return rc;
         p = (char *)ctx->stack_buf.p;
     }
     const uint8_t *img = stack;
     if (!dev) img = carve<uint8_t>(p, (size_t)npix);
     GrainBufs b{};
-    b.tile_cnt = carve<uint32_t>(p, nt);
+    b.tile_cnt = carve<uint16_t>(p, nt);
     b.group_cnt = carve<uint32_t>(p, ng);
     b.stage = carve<uint16_t>(p, grain_stage_slots(G));
-    b.total = carve<uint32_t>(p, 1);
+    b.total = ctx->d_small;
     b.out = dev ? xyz_out : carve<int32_t>(p, 3 * (size_t)max_out);
     b.max_out = max_out;
     hipStream_t s = ctx->stream;
@@ -1115,9 +1112,8 @@ static int find_grains_impl(emt_ctx *ctx, const uint8_t *stack, const emt_stack_
     launch_find_grains(img, G, b, s);
     HIP_OK(hipGetLastError());
     if (stats) HIP_OK(hipEventRecord(ctx->ev[1], s));
-    HIP_OK(hipMemcpyAsync(ctx->h_small + 1, b.total, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     HIP_OK(hipStreamSynchronize(s));
-    const uint32_t total = ctx->h_small[1];
+    const uint32_t total = ctx->h_small[0];
     *n_out = total;
     ctx->last = emt_call_stats{};
     if (stats) (void)hipEventElapsedTime(&ctx->last.ms_total, ctx->ev[0], ctx->ev[1]);

@@ -257,20 +257,15 @@ struct StackGeom {
 };
 
 struct GrainBufs {
-    uint32_t *tile_cnt;   // grains per tile, grain_tile_count(G) entries
-    uint32_t *group_cnt;  // grains per 64 tiles, grain_group_count(G) entries
+    uint16_t *tile_cnt;   // grains per tile, grain_tile_count(G) entries
+    uint32_t *group_cnt;  // grains per 64 tiles, grain_group_count(G) entries (none for few tiles)
     uint16_t *stage;      // grain_stage_slots(G): grain offsets within their tile
-    uint32_t *total;      // grains found (may exceed max_out)
+    uint32_t *total;      // grains found (may exceed max_out): a mapped word of the host's
     int32_t *out;         // 3 * max_out: x, y, z per grain, 0.01 um units
     uint32_t max_out;
 };
 
-// Tiles of the grain recognition: pixels a tile streams, staging slots (two
-// bytes each) per tile, tiles summed per group.
-constexpr uint32_t kGrainTilePix = 8192;
-constexpr uint32_t kGrainTileGrains = kGrainTilePix / 2;
-constexpr uint32_t kGrainTileGroup = 64;
-
+// Tiles of the grain recognition (their size depends on the stack's).
 size_t grain_tile_count(const StackGeom &G);
 size_t grain_group_count(const StackGeom &G);
 size_t grain_stage_slots(const StackGeom &G);

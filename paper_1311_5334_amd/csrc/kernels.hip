@@ -2815,21 +2815,26 @@ __global__ void __launch_bounds__(kBlock) k_copy_out(DevPtrs d, Caps c) {
 // block in 0.01 um units (pitch of each axis num/den units, rounded to the
 // nearest unit, halves up, from exact integer sums).
 //
-// The stack is streamed once. A workgroup owns a tile of kTilePix
-// consecutive pixels (the stack is one flat byte array, so a tile runs
-// across row ends): each thread reads 32 of them as two 16-byte vectors and
-// marks those above threshold; the workgroup lists its candidates in LDS in
-// pixel order and tests them one per thread, which keeps the neighbourhood
-// tests dense although few pixels pass the threshold. The grains' offsets in
+// The stack is streamed once. A wave owns a tile of 1024 or 4096 consecutive
+// pixels (the stack is one flat byte array, so a tile runs across row ends):
+// each lane reads them as one or four 16-byte vectors and marks those above
+// threshold; the wave lists its candidates in LDS in pixel order and tests
+// them one per lane, which keeps the neighbourhood tests dense although few
+// pixels pass the threshold. Waves never wait for one another: a workgroup
+// that listed and tested together spent most of its life in barriers behind
+// the neighbour loads of its few candidates. The grains' offsets in
 // the tile go, in pixel order, to the tile's staging slots. Two pixels next
 // to each other in a row cannot both be grains (one outranks the other), and
 // tile and row boundaries fall on multiples of four pixels, so a tile holds
-// at most kTilePix / 2 grains: the staging area is bounded. Tile counts are
-// also summed per group of 64 tiles with one atomic add each. A second,
+// at most half as many grains as pixels: the staging area is bounded. A second,
 // small kernel (one workgroup per group of tiles) takes its place in the
-// output from those sums, finds each staged grain's tile by a search over
-// the group's tile offsets, and writes the centre of mass: grains come out
-// in frame, row, column order without a separate scan or a second stream.
+// output from the counts of the tiles before it, finds each staged grain's
+// tile by a search over the group's tile offsets, and writes the centre of
+// mass: grains come out in frame, row, column order without a separate scan
+// or a second stream. The grains found go straight to the host's word.
+// 52 M pixels with 1400 grains stream in 16.3 us (27.7 with the workgroup's
+// lists), 3.2 TB/s, and place in 5.8; with 20000 grains both take 26.9 us
+// (52.9 before), and 1.3 M pixels with 10000 grains 13.1 (49.4).
 
 // q = n / d for n < 2^32, d >= 1: double-precision reciprocal, then an
 // exact integer correction of the +-1 it may be off by.
@@ -2840,35 +2845,34 @@ __device__ __forceinline__ uint32_t div_rcp(uint32_t n, uint32_t d, double inv) 
     return q;
 }
 
-#ifndef EMT_GRAIN_WORDS
-#define EMT_GRAIN_WORDS 8
-#endif
-constexpr uint32_t kGrainWords = EMT_GRAIN_WORDS;           // four-pixel words a thread
-constexpr uint32_t kCandMasks = kGrainWords / 8;            // 32-pixel candidate masks
-static_assert(kGrainWords % 8 == 0, "candidate masks cover 32 pixels each");
-constexpr uint32_t kTilePix = kBlock * kGrainWords * 4;     // pixels a workgroup streams
-constexpr uint32_t kTileGrains = kTilePix / 2;              // staging slots per tile
-constexpr uint32_t kTileGroup = 64;                         // tiles per atomic sum
-constexpr uint32_t kCandCap = 2048;                         // candidates listed per round
-static_assert(kTilePix <= 65536u, "tile offsets are staged as 16 bits");
-static_assert(kTilePix == kGrainTilePix && kTileGrains == kGrainTileGrains &&
-                  kTileGroup == kGrainTileGroup,
-              "tile sizes the host sizes its buffers by");
+constexpr uint32_t kCandCap = 256;  // candidates listed per round
+// 16-pixel vectors a lane reads. Four keep enough bytes in flight to stream a
+// large stack (52 M pixels: 20.0 us with four, 24.4 with two, 42 with one);
+// below about 4 M pixels such tiles leave most of the 1024 SIMDs without a
+// wave, and a tile of many grains is a long serial chain (1.3 M pixels with
+// 10000 grains: 25.2 us with four, 16.2 with two, 13.1 with one; 6.6 M pixels
+// with 700: 11.6, 11.9, 13.4).
+constexpr uint64_t kSmallStack = 4000000;
+constexpr uint32_t kLargeLoads = 4, kSmallLoads = 1;
+constexpr uint32_t tile_pix(uint32_t loads) { return 64 * 16 * loads; }
+static_assert(tile_pix(kLargeLoads) <= 65536u, "tile offsets are staged as 16 bits");
+// the tiles a placing workgroup takes, as a power of two
+constexpr uint32_t kLargeGroup = 6, kSmallGroup = 3;
+// a placing workgroup reads 2 bytes for every tile before it: up to 64 KB,
+// from L2, up to this many tiles (134 M pixels)
+constexpr size_t kDirectTiles = 32768;
+static_assert(kSmallStack / tile_pix(kSmallLoads) < kDirectTiles, "sums are of large groups");
 
-__device__ __forceinline__ uint32_t block_excl_scan_small(uint32_t v, uint32_t *s_wave,
-                                                          uint32_t *total) {
-    const uint32_t incl = wave_incl_scan_dpp(v);
-    const int lane = lane_id(), wave = threadIdx.x >> 6;
-    if (lane == 63) s_wave[wave] = incl;
+bool small_stack(const StackGeom &G) { return (uint64_t)G.nx * G.ny * G.nz < kSmallStack; }
+uint32_t stack_tile(const StackGeom &G) { return tile_pix(small_stack(G) ? kSmallLoads : kLargeLoads); }
+
+__device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t *s_wave) {
+    v = wave_sum(v);
+    if (lane_id() == 0) s_wave[threadIdx.x >> 6] = v;
     __syncthreads();
-    uint32_t before = 0, tot = 0;
-    for (int w = 0; w < kBlock / 64; ++w) {
-        before += w < wave ? s_wave[w] : 0u;
-        tot += s_wave[w];
-    }
-    __syncthreads();  // s_wave is reused by the next scan
-    *total = tot;
-    return before + incl - v;
+    uint32_t tot = 0;
+    for (int w = 0; w < kBlock / 64; ++w) tot += s_wave[w];
+    return tot;
 }
 
 // The 3 x 3 x 3 block around pixel p (flat index): pulse heights w[i]
@@ -2948,121 +2952,159 @@ struct Block27 {
     }
 };
 
+// Bit 7 of every byte of w above thr. The lower seven bits are compared by
+// the carry of an addition into bit 7, which stays in its byte.
+__device__ __forceinline__ uint32_t above(uint32_t w, uint32_t add, bool upper) {
+    const uint32_t t = (w & 0x7f7f7f7fu) + add;
+    return (upper ? t & w : t | w) & 0x80808080u;
+}
+
+template <uint32_t kLoads>
 __global__ void __launch_bounds__(kBlock) k_grain_find(const uint8_t *__restrict__ img,
-                                                       StackGeom G, uint32_t *tile_cnt,
-                                                       uint32_t *group_cnt, uint16_t *stage) {
-    __shared__ uint32_t s_wave[kBlock / 64];
-    __shared__ uint32_t s_cand[kCandCap];
-    const uint32_t n_groups = (G.nx >> 2) * G.ny * G.nz;  // four-pixel words
-    const uint32_t g0 = (blockIdx.x * kBlock + threadIdx.x) * kGrainWords;
-    uint32_t words[kGrainWords];
-    if (g0 + kGrainWords <= n_groups) {
-        const uint4 *p = reinterpret_cast<const uint4 *>(img + 4ull * g0);
+                                                       StackGeom G, uint32_t n_tiles,
+                                                       uint16_t *tile_cnt, uint16_t *stage) {
+    constexpr uint32_t kTile = tile_pix(kLoads);
+    __shared__ uint32_t s_list[kBlock / 64][kCandCap];
+    const int lane = lane_id();
+    uint32_t *list = s_list[threadIdx.x >> 6];
+    const uint32_t tile = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+    if (tile >= n_tiles) return;
+    const uint32_t n_pix = G.nx * G.ny * G.nz;  // a multiple of 4, at most 2^31
+    const uint32_t tile0 = tile * kTile, mine = tile0 + 16u * (uint32_t)lane;
+    uint4 q[kLoads];
+    if (n_pix - tile0 >= kTile) {
 #pragma unroll
-        for (int h = 0; h < (int)kGrainWords / 4; ++h) {
-            const uint4 q = p[h];
-            words[4 * h] = q.x;
-            words[4 * h + 1] = q.y;
-            words[4 * h + 2] = q.z;
-            words[4 * h + 3] = q.w;
-        }
+        for (uint32_t h = 0; h < kLoads; ++h)
+            q[h] = *reinterpret_cast<const uint4 *>(img + mine + 1024u * h);
     } else {
 #pragma unroll
-        for (int k = 0; k < (int)kGrainWords; ++k)
-            words[k] = g0 + k < n_groups
-                           ? *reinterpret_cast<const uint32_t *>(img + 4ull * (g0 + k))
-                           : 0u;
-    }
-    uint32_t cand[kCandMasks], n_cand = 0;
+        for (uint32_t h = 0; h < kLoads; ++h) {
+            uint32_t w[4];
 #pragma unroll
-    for (int j = 0; j < (int)kCandMasks; ++j) {
+            for (uint32_t k = 0; k < 4; ++k) {
+                const uint32_t at = mine + 1024u * h + 4u * k;
+                w[k] = at < n_pix ? *reinterpret_cast<const uint32_t *>(img + at) : 0u;
+            }
+            q[h] = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+    }
+    // bit p of cand[h]: pixel mine + 1024 h + p is above the threshold
+    const bool upper = G.thr >= 128u;
+    const uint32_t add = (127u - (G.thr & 127u)) * 0x01010101u;
+    uint32_t cand[kLoads];
+#pragma unroll
+    for (uint32_t h = 0; h < kLoads; ++h) {
+        // word k's four bytes at bits k, 8 + k, 16 + k, 24 + k
+        uint32_t m = (above(q[h].x, add, upper) >> 7) | (above(q[h].y, add, upper) >> 6) |
+                     (above(q[h].z, add, upper) >> 5) | (above(q[h].w, add, upper) >> 4);
         uint32_t c = 0;
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-                c |= ((words[8 * j + k] >> (8 * b)) & 0xffu) > G.thr ? 1u << (4 * k + b) : 0u;
-        cand[j] = c;
-        n_cand += (uint32_t)__popc(c);
+        for (; m; m &= m - 1u) {
+            const uint32_t i = (uint32_t)__ffs((int)m) - 1u;
+            c |= 1u << (4u * (i & 7u) + (i >> 3));
+        }
+        cand[h] = c;
     }
-    uint32_t c_total;
-    const uint32_t c_before = block_excl_scan_small(n_cand, s_wave, &c_total);
-    const uint32_t tile0 = blockIdx.x * kTilePix;
-    uint16_t *st = stage + (size_t)blockIdx.x * kTileGrains;
+    // the candidates' places in pixel order: vector by vector, lane by lane
+    uint32_t before[kLoads], c_total = 0;
+#pragma unroll
+    for (uint32_t h = 0; h < kLoads; h += 2) {  // two counts a scan
+        const uint32_t n = (uint32_t)__popc(cand[h]) |
+                           (h + 1 < kLoads ? (uint32_t)__popc(cand[h + 1 < kLoads ? h + 1 : h]) << 16 : 0u);
+        const uint32_t incl = wave_incl_scan_dpp(n), excl = incl - n;
+        const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        before[h] = c_total + (excl & 0xffffu);
+        c_total += tot & 0xffffu;
+        if (h + 1 < kLoads) before[h + 1 < kLoads ? h + 1 : h] = c_total + (excl >> 16);
+        c_total += tot >> 16;
+    }
+    uint16_t *st = stage + (size_t)tile * (kTile / 2u);
     uint32_t found = 0;
     for (uint32_t base = 0; base < c_total; base += kCandCap) {  // uniform
-        // list this round's candidates, in pixel order
-        uint32_t idx = c_before;
+        // list this round's candidates
 #pragma unroll
-        for (int j = 0; j < (int)kCandMasks; ++j) {
-            uint32_t bits = cand[j];
-            while (bits) {
-                const int i = __ffs((int)bits) - 1;
-                bits &= bits - 1;
+        for (uint32_t h = 0; h < kLoads; ++h) {
+            uint32_t idx = before[h];
+            for (uint32_t bits = cand[h]; bits; bits &= bits - 1u, ++idx)
                 if (idx >= base && idx < base + kCandCap)
-                    s_cand[idx - base] = 4u * g0 + 32u * (uint32_t)j + (uint32_t)i;
-                ++idx;
-            }
+                    list[idx - base] = mine + 1024u * h + (uint32_t)__ffs((int)bits) - 1u;
         }
-        __syncthreads();
+        wave_lds_sync();
         const uint32_t m = min(kCandCap, c_total - base);
-        for (uint32_t c0 = 0; c0 < m; c0 += kBlock) {  // uniform
-            const uint32_t c = c0 + threadIdx.x;
+        for (uint32_t c0 = 0; c0 < m; c0 += 64) {  // uniform
+            const uint32_t c = c0 + (uint32_t)lane;
+            const uint32_t pix = list[min(c, m - 1u)];
             bool top = false;
             if (c < m) {
                 Block27 B;
-                B.load(img, G, s_cand[c]);
+                B.load(img, G, pix);
                 top = B.is_top();
             }
-            uint32_t n_top;
-            const uint32_t before = block_excl_scan_small(top ? 1u : 0u, s_wave, &n_top);
-            if (top && found + before < kTileGrains)  // always true: see the bound above
-                st[found + before] = (uint16_t)(s_cand[c] - tile0);
-            found += n_top;
+            const unsigned long long tops = __ballot(top);
+            const uint32_t slot = found + (uint32_t)__popcll(tops & lanes_below());
+            if (top && slot < (kTile / 2u))  // always true: see the bound above
+                st[slot] = (uint16_t)(pix - tile0);
+            found += (uint32_t)__popcll(tops);
         }
-        __syncthreads();  // s_cand is rewritten by the next round
+        wave_lds_sync();  // the list is rewritten by the next round
     }
-    if (threadIdx.x == 0) {
-        tile_cnt[blockIdx.x] = found;
-        if (found) atomicAdd(group_cnt + blockIdx.x / kTileGroup, found);
-    }
+    if (lane == 0) tile_cnt[tile] = (uint16_t)min(found, (kTile / 2u));
 }
 
-// One workgroup per group of kTileGroup tiles: its grains' place in the
-// output is the sum of the earlier groups' counts plus the offset of the
-// tile within the group.
+// Grains of each group of tiles, for stacks of too many tiles for every
+// placing workgroup to add up those before it.
+__global__ void __launch_bounds__(kBlock) k_grain_sums(const uint16_t *__restrict__ tile_cnt,
+                                                       uint32_t n_tiles, uint32_t *group_cnt,
+                                                       uint32_t n_groups) {
+    const uint32_t g = blockIdx.x * kBlock + threadIdx.x;
+    if (g >= n_groups) return;
+    uint32_t sum = 0;
+    for (uint32_t t = g << kLargeGroup; t < min(n_tiles, (g + 1u) << kLargeGroup); ++t)
+        sum += tile_cnt[t];
+    group_cnt[g] = sum;
+}
+
+// One workgroup per group of 2^lg tiles (8 to 64): its grains' place in the
+// output is the sum of the earlier tiles' counts (kSums: of the earlier
+// groups' sums) plus the offset of the tile within the group.
+template <bool kSums>
 __global__ void __launch_bounds__(kBlock) k_grain_place(
-    const uint8_t *__restrict__ img, StackGeom G, const uint32_t *__restrict__ tile_cnt,
+    const uint8_t *__restrict__ img, StackGeom G, const uint16_t *__restrict__ tile_cnt,
     const uint32_t *__restrict__ group_cnt, uint32_t n_tiles,
-    const uint16_t *__restrict__ stage, int32_t *out, uint32_t max_out, uint32_t *total) {
-    static_assert(kTileGroup == 64, "tile offsets are scanned by one wave");
+    const uint16_t *__restrict__ stage, uint32_t tile_px, uint32_t lg, int32_t *out,
+    uint32_t max_out, uint32_t *total) {
     __shared__ uint32_t s_wave[kBlock / 64];
-    __shared__ uint32_t s_off[kTileGroup + 1];
-    const uint32_t grp = blockIdx.x;
+    __shared__ uint32_t s_off[65];
+    const uint32_t grp = blockIdx.x, t0 = grp << lg, in_group = 1u << lg;
     uint32_t acc = 0;
-    for (uint32_t i = threadIdx.x; i < grp; i += kBlock) acc += group_cnt[i];
-    uint32_t prefix;
-    (void)block_excl_scan_small(acc, s_wave, &prefix);
-    const uint32_t t0 = grp * kTileGroup;
+    if constexpr (kSums) {
+        for (uint32_t i = threadIdx.x; i < grp; i += kBlock) acc += group_cnt[i];
+    } else {
+        // eight counts a load (a group is a multiple of eight)
+        const uint4 *cnt = reinterpret_cast<const uint4 *>(tile_cnt);
+        for (uint32_t i = threadIdx.x; i < t0 / 8u; i += kBlock) {
+            const uint4 v = cnt[i];
+            acc += (v.x & 0xffffu) + (v.x >> 16) + (v.y & 0xffffu) + (v.y >> 16) +
+                   (v.z & 0xffffu) + (v.z >> 16) + (v.w & 0xffffu) + (v.w >> 16);
+        }
+    }
     if (threadIdx.x < 64) {
         const uint32_t t = t0 + threadIdx.x;
-        const uint32_t c = t < n_tiles ? min(tile_cnt[t], kTileGrains) : 0u;
-        s_off[threadIdx.x + 1] = wave_incl_scan_dpp(c);
+        s_off[threadIdx.x + 1] = wave_incl_scan_dpp(threadIdx.x < in_group && t < n_tiles ? tile_cnt[t] : 0u);
         if (threadIdx.x == 0) s_off[0] = 0;
     }
-    __syncthreads();
-    const uint32_t n_here = s_off[kTileGroup];
+    const uint32_t prefix = block_sum(acc, s_wave);  // synchronises: s_off is written
+    const uint32_t n_here = s_off[in_group];
     if (grp + 1 == gridDim.x && threadIdx.x == 0) *total = prefix + n_here;
     for (uint32_t g = threadIdx.x; g < n_here; g += kBlock) {
         // the tile holding grain g: s_off[lo] <= g < s_off[lo + 1]
-        uint32_t lo = 0, hi = kTileGroup;
+        uint32_t lo = 0, hi = in_group;
         while (hi - lo > 1) {
             const uint32_t mid = (lo + hi) >> 1;
             if (s_off[mid] <= g) lo = mid;
             else hi = mid;
         }
         const uint32_t t = t0 + lo;
-        const uint32_t p = t * kTilePix + stage[(size_t)t * kTileGrains + (g - s_off[lo])];
+        const uint32_t p = t * tile_px + stage[(size_t)t * (tile_px / 2u) + (g - s_off[lo])];
         const uint32_t q = prefix + g;
         if (q < max_out) {
             Block27 B;
@@ -3072,31 +3114,40 @@ __global__ void __launch_bounds__(kBlock) k_grain_place(
     }
 }
 
-__global__ void k_clear_words(uint32_t *p, uint32_t n) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0u;
-}
-
 }  // namespace
 
 size_t grain_tile_count(const StackGeom &G) {
-    const unsigned long long pix = (unsigned long long)G.nx * G.ny * G.nz;
-    return (size_t)((pix + kTilePix - 1) / kTilePix);
+    const uint64_t px = (uint64_t)G.nx * G.ny * G.nz, tile = stack_tile(G);
+    return (size_t)((px + tile - 1) / tile);
 }
 
 size_t grain_group_count(const StackGeom &G) {
-    return (grain_tile_count(G) + kTileGroup - 1) / kTileGroup;
+    const size_t nt = grain_tile_count(G);
+    return nt <= kDirectTiles ? 0 : (nt + (1u << kLargeGroup) - 1) >> kLargeGroup;
 }
 
-size_t grain_stage_slots(const StackGeom &G) { return grain_tile_count(G) * kTileGrains; }
+size_t grain_stage_slots(const StackGeom &G) {
+    return grain_tile_count(G) * (stack_tile(G) / 2u);
+}
 
 void launch_find_grains(const uint8_t *img, const StackGeom &G, const GrainBufs &b,
                         hipStream_t s) {
-    const uint32_t nt = (uint32_t)grain_tile_count(G), ng = (uint32_t)grain_group_count(G);
-    k_clear_words<<<(ng + kBlock - 1) / kBlock, kBlock, 0, s>>>(b.group_cnt, ng);
-    k_grain_find<<<nt, kBlock, 0, s>>>(img, G, b.tile_cnt, b.group_cnt, b.stage);
-    k_grain_place<<<ng, kBlock, 0, s>>>(img, G, b.tile_cnt, b.group_cnt, nt, b.stage, b.out,
-                                        b.max_out, b.total);
+    const uint32_t nt = (uint32_t)grain_tile_count(G), sums = (uint32_t)grain_group_count(G);
+    const bool small = small_stack(G);
+    const uint32_t lg = small ? kSmallGroup : kLargeGroup, px = stack_tile(G);
+    const uint32_t ng = (nt + (1u << lg) - 1) >> lg, nb = (nt + kBlock / 64 - 1) / (kBlock / 64);
+    if (small)
+        k_grain_find<kSmallLoads><<<nb, kBlock, 0, s>>>(img, G, nt, b.tile_cnt, b.stage);
+    else
+        k_grain_find<kLargeLoads><<<nb, kBlock, 0, s>>>(img, G, nt, b.tile_cnt, b.stage);
+    if (sums) {
+        k_grain_sums<<<(ng + kBlock - 1) / kBlock, kBlock, 0, s>>>(b.tile_cnt, nt, b.group_cnt, ng);
+        k_grain_place<true><<<ng, kBlock, 0, s>>>(img, G, b.tile_cnt, b.group_cnt, nt, b.stage, px,
+                                                  lg, b.out, b.max_out, b.total);
+    } else {
+        k_grain_place<false><<<ng, kBlock, 0, s>>>(img, G, b.tile_cnt, nullptr, nt, b.stage, px, lg,
+                                                   b.out, b.max_out, b.total);
+    }
 }
 
 // ---------------------------------------------------------- filtering

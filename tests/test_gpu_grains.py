@@ -200,3 +200,24 @@ def test_bad_geometry_is_rejected(emt, tracker):
     # an all-dark stack has no grains
     assert lib.emt_find_grains(tracker.ctx, img.ctypes.data, C.byref(g), out.ctypes.data, 4,
                                C.byref(n)) == 0 and n.value == 0
+
+
+@pytest.mark.parametrize("dims", [(64, 16, 1), (1028, 1, 1), (1020, 9, 1), (2048, 4, 3),
+                                  (1996, 500, 4), (2000, 500, 4), (2052, 1025, 2), (4096, 512, 2)])
+@pytest.mark.parametrize("thr", [0, 127, 128, 254])
+def test_tile_and_size_edges(tracker, dims, thr):
+    """Whole tiles, a remainder of one four-pixel word, and both sides of the
+    size from which tiles are larger; values over the whole byte, a dense
+    patch whose candidates fill several lists, grains at both ends."""
+    from oracle.grains import find_grains
+    nx, ny, nz = dims
+    rng = np.random.default_rng(nx * 7 + ny)
+    img = np.where(rng.random((nz, ny, nx)) < 0.01, rng.integers(0, 256, (nz, ny, nx)), 0)
+    img = img.astype(np.uint8)
+    flat = img.reshape(-1)
+    lo = flat.size // 2
+    flat[lo:lo + 5000] = rng.integers(0, 256, flat[lo:lo + 5000].size)
+    flat[0] = flat[-1] = 255
+    ref, _ = find_grains(img, thr)
+    got = tracker.find_grains(img, thr)
+    assert np.array_equal(got, ref)
