@@ -280,15 +280,13 @@ size_t view_bytes(size_t n, int nc) {
            bytes_of<uint32_t>((size_t)max_merge_rounds()) + bytes_of<uint32_t>(kGrabWords) +
            bytes_of<unsigned long long>(kPartWords) + bytes_of<BatchDesc>(1);
 }
-// the scan scratch serves every scan: cells, anchors, seeds, candidates
+// the scan scratch serves every scan: cells, anchors, candidates
 uint32_t scan_words(const Caps &c, int nc) {
-    return std::max<uint32_t>(std::max<uint32_t>(c.n_cells, c.cand_cap),
-                              std::max<uint32_t>((uint32_t)(c.seed_cap / 32 + 1),
-                                                 (uint32_t)nc * c.n_total)) + 1;
+    return std::max({c.n_cells, c.cand_cap, (uint32_t)nc * c.n_total}) + 1;
 }
-size_t scan_bytes(size_t n_cells, size_t n_scan) {
-    return 2 * bytes_of<uint32_t>(n_cells) +
-           bytes_of<uint32_t>(scan_scratch_words((uint32_t)n_scan));
+size_t scan_bytes(const Caps &c, int nc) {
+    return 2 * bytes_of<uint32_t>(c.n_cells) +
+           bytes_of<uint32_t>(scan_scratch_words(scan_words(c, nc), c.seed_cap));
 }
 
 // Sizes the arenas are carved for.
@@ -299,7 +297,7 @@ struct ArenaSizes {
 ArenaSizes arena_sizes(const Caps &c, int nc) {
     return {grain_bytes(c.n_total, nc), seed_bytes(c.seed_cap),
             cand_bytes(c.cand_cap, c.n_total, c.n_views, nc), mem_bytes(c.mem_cap, c.n_total, nc),
-            scan_bytes(c.n_cells, scan_words(c, nc)), view_bytes(c.n_views, nc)};
+            scan_bytes(c, nc), view_bytes(c.n_views, nc)};
 }
 
 // Line classes the tables hold: more slope bins make the lines of a class
@@ -414,7 +412,7 @@ int ensure(emt_ctx *ctx, Caps &c) {
         p = (char *)ctx->cell_buf.p;
         d.cell_count = carve<uint32_t>(p, h.n_cells);
         d.cell_start = carve<uint32_t>(p, h.n_cells);
-        d.scan_part = carve<uint32_t>(p, scan_scratch_words(scan_words(h, h.nc)));
+        d.scan_part = carve<uint32_t>(p, scan_scratch_words(scan_words(h, h.nc), h.seed_cap));
 
         p = (char *)ctx->view_buf.p;
         d.grids = carve<ViewGrid>(p, nv);

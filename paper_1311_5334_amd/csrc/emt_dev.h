@@ -290,7 +290,7 @@ void launch_merge(const DevPtrs &d, const Caps &c, const Params &P, hipStream_t 
 void launch_fit(const DevPtrs &d, const Caps &c, const Params &P, hipStream_t s);
 void launch_copy_out(const DevPtrs &d, const Caps &c, const Params &P, hipStream_t s);
 
-size_t scan_scratch_words(uint32_t n_cap);
+size_t scan_scratch_words(uint32_t n_cap, unsigned long long n_seeds);
 int max_merge_rounds();
 int max_wide_rounds();
 

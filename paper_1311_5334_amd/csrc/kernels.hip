@@ -80,28 +80,49 @@ __device__ __forceinline__ void add_spread(unsigned long long *part64, int which
 __device__ __forceinline__ uint32_t grid_tid() { return blockIdx.x * blockDim.x + threadIdx.x; }
 __device__ __forceinline__ uint32_t grid_threads() { return gridDim.x * blockDim.x; }
 
+// Inclusive prefix sum over the 64 lanes with DPP row shifts and row
+// broadcasts (no LDS traffic).
+__device__ __forceinline__ uint32_t wave_incl_scan_dpp(uint32_t x) {
+    uint32_t v = x;
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);  // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);  // row_shr:2
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);  // row_shr:4
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);  // row_shr:8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return v;
+}
+
 // ------------------------------------------------------------------ scan
 
-// Exclusive scan inside one block of kBlock threads.
-__device__ uint32_t block_excl_scan(uint32_t v, uint32_t *total) {
-    __shared__ uint32_t wsum[kBlock / 64];
-    const int lane = lane_id();
+// Exclusive scan inside one block of kThreads threads.
+template <int kThreads = kBlock>
+__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *total) {
+    __shared__ uint32_t wsum[kThreads / 64];
+    const uint32_t incl = wave_incl_scan_dpp(v);
     const int w = threadIdx.x >> 6;
-    uint32_t x = v;
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
-    if (lane == 63) wsum[w] = x;
+    if (lane_id() == 63) wsum[w] = incl;
     __syncthreads();
     uint32_t off = 0, tot = 0;
-    for (int i = 0; i < kBlock / 64; ++i) {
+    for (int i = 0; i < kThreads / 64; ++i) {
         if (i < w) off += wsum[i];
         tot += wsum[i];
     }
     __syncthreads();
     *total = tot;
-    return off + x - v;
+    return off + incl - v;
+}
+
+template <int kThreads = kBlock>
+__device__ __forceinline__ uint32_t block_sum(uint32_t v) {
+    __shared__ uint32_t wsum[kThreads / 64];
+    v = wave_sum(v);
+    if (lane_id() == 0) wsum[threadIdx.x >> 6] = v;
+    __syncthreads();
+    uint32_t tot = 0;
+    for (int i = 0; i < kThreads / 64; ++i) tot += wsum[i];
+    __syncthreads();
+    return tot;
 }
 
 __device__ __forceinline__ uint32_t scan_len(const uint32_t *n_dev, uint32_t n_cap) {
@@ -110,76 +131,210 @@ __device__ __forceinline__ uint32_t scan_len(const uint32_t *n_dev, uint32_t n_c
     return n < n_cap ? n : n_cap;
 }
 
-template <bool kPopc>
-__device__ __forceinline__ uint32_t scan_in(const uint32_t *in, uint32_t i) {
-    const uint32_t v = in[i];
-    return kPopc ? (uint32_t)__popc(v) : v;
+// Items [base, base + kItems) of an array of n, zero past its end; base is a
+// multiple of kItems and the array starts on a 16-byte boundary.
+template <int kItems>
+__device__ __forceinline__ void load_items(const uint32_t *in, uint32_t base, uint32_t n,
+                                           uint32_t (&v)[kItems]) {
+    if (kItems % 4 == 0 && base + kItems <= n) {
+#pragma unroll
+        for (int k = 0; k < kItems; k += 4) {
+            const uint4 q = *reinterpret_cast<const uint4 *>(in + base + k);
+            v[k] = q.x;
+            v[k + 1] = q.y;
+            v[k + 2] = q.z;
+            v[k + 3] = q.w;
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) v[k] = base + k < n ? in[base + k] : 0u;
+    }
 }
 
-template <bool kPopc>
+template <int kItems>
+__device__ __forceinline__ void store_items(uint32_t *out, uint32_t base, uint32_t n,
+                                            const uint32_t (&v)[kItems]) {
+    if (kItems % 4 == 0 && base + kItems <= n) {
+#pragma unroll
+        for (int k = 0; k < kItems; k += 4)
+            *reinterpret_cast<uint4 *>(out + base + k) =
+                make_uint4(v[k], v[k + 1], v[k + 2], v[k + 3]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < kItems; ++k)
+            if (base + k < n) out[base + k] = v[k];
+    }
+}
+
+// What the last workgroup of a scan does with the total.
+enum ScanEnd { kEndTotal, kEndSeeds, kEndMembers };
+struct ScanOut {
+    uint32_t *out, *total;  // total may be null
+    Counters *cnt;
+    const unsigned long long *part64;
+    unsigned long long seed_cap;
+};
+
+// Called by every lane of one wave, once per scan of n items.
+template <ScanEnd kEnd>
+__device__ __forceinline__ void scan_end(const ScanOut &o, uint32_t n, uint32_t total) {
+    if constexpr (kEnd == kEndTotal) {
+        if (lane_id() != 0) return;
+        if (o.total) *o.total = total;
+    } else if constexpr (kEnd == kEndSeeds) {
+        // The seed total of the uint32 scan, replaced by the exact 64-bit
+        // count (saturated to 2^32 - 1), and the number of seeds the later
+        // stages take: none when they do not fit the seed buffer (the host
+        // then re-runs the call with a larger one, or fails if no buffer can
+        // hold them). One of the spread partial sums per lane.
+        const unsigned long long t = wave_sum(o.part64[lane_id() * kPartStride]);
+        if (lane_id() != 0) return;
+        Counters *cnt = o.cnt;
+        cnt->seeds64 = t;
+        const uint32_t ns = t > 0xffffffffull ? 0xffffffffu : (uint32_t)t;
+        cnt->n_seeds = ns;
+        cnt->n_seeds_ok = ns <= o.seed_cap ? ns : 0u;
+        cnt->pass_words = (uint32_t)(((unsigned long long)cnt->n_seeds_ok + 31ull) / 32ull);
+    } else {
+        // Likewise for the member entries (the scan of candidate counts): a
+        // total that wrapped reads as an overflow, so no stage uses the
+        // wrapped offsets. The counting kernel's tests and hits too (it has
+        // finished).
+        const unsigned long long m = wave_sum(o.part64[(kPartSlots + lane_id()) * kPartStride]);
+        const unsigned long long t = wave_sum(o.part64[(2 * kPartSlots + lane_id()) * kPartStride]);
+        const unsigned long long h = wave_sum(o.part64[(3 * kPartSlots + lane_id()) * kPartStride]);
+        if (lane_id() != 0) return;
+        Counters *cnt = o.cnt;
+        cnt->tests = t;
+        cnt->hits = h;
+        cnt->members64 = m;
+        cnt->n_members = m > 0xffffffffull ? 0xffffffffu : (uint32_t)m;
+    }
+    o.out[n] = total;
+}
+
+// The sum of each tile of kBlock * kItems items (their popcounts with kPopc).
+template <bool kPopc, int kItems>
 __global__ void __launch_bounds__(kBlock) k_scan_part(const uint32_t *in, const uint32_t *n_dev,
                                                       uint32_t n_cap, uint32_t *part) {
     const uint32_t n = scan_len(n_dev, n_cap);
-    const uint32_t base = blockIdx.x * kScanTile + threadIdx.x * kScanItems;
-    uint32_t s = 0;
-    for (int i = 0; i < kScanItems; ++i)
-        if (base + i < n) s += scan_in<kPopc>(in, base + i);
-    uint32_t tot;
-    block_excl_scan(s, &tot);
-    if (threadIdx.x == 0) part[blockIdx.x] = tot;
+    if (blockIdx.x * (kBlock * kItems) >= n) return;
+    uint32_t v[kItems], sum = 0;
+    load_items(in, (blockIdx.x * kBlock + threadIdx.x) * kItems, n, v);
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) sum += kPopc ? (uint32_t)__popc(v[k]) : v[k];
+    sum = block_sum(sum);
+    if (threadIdx.x == 0) part[blockIdx.x] = sum;
 }
 
-__global__ void __launch_bounds__(kBlock) k_scan_part_scan(uint32_t *part, uint32_t n_part,
-                                                           const uint32_t *n_dev, uint32_t n_cap,
-                                                           uint32_t *out, uint32_t *total_out) {
+// The tiles' sums to exclusive offsets, where there are too many of them for
+// every later workgroup to add up those before its own.
+constexpr int kScanBlock = 1024;
+__global__ void __launch_bounds__(kScanBlock) k_scan_parts(uint32_t *part, uint32_t tile,
+                                                           const uint32_t *n_dev, uint32_t n_cap) {
     const uint32_t n = scan_len(n_dev, n_cap);
-    const uint32_t nb = (n + kScanTile - 1) / kScanTile;
+    const uint32_t nb = n / tile + (n % tile != 0 ? 1u : 0u);
     uint32_t carry = 0;
-    for (uint32_t base = 0; base < nb; base += kBlock) {
-        const uint32_t i = base + threadIdx.x;
-        const uint32_t v = (i < nb && i < n_part) ? part[i] : 0u;
-        uint32_t tot;
-        const uint32_t ex = block_excl_scan(v, &tot);
-        if (i < nb && i < n_part) part[i] = carry + ex;
+    for (uint32_t base = 0; base < nb; base += kScanBlock * 4) {
+        const uint32_t at = base + threadIdx.x * 4;
+        uint32_t v[4], tot;
+        load_items(part, at, nb, v);
+        uint32_t run = carry + block_excl_scan<kScanBlock>(v[0] + v[1] + v[2] + v[3], &tot);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t x = v[k];
+            v[k] = run;
+            run += x;
+        }
+        store_items(part, at, nb, v);
         carry += tot;
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        out[n] = carry;
-        if (total_out) *total_out = carry;
     }
 }
 
-template <bool kPopc>
+// Offset of this workgroup's tile: the sum of the earlier tiles, or what
+// k_scan_parts left. Called by the whole workgroup.
+template <bool kDirect>
+__device__ __forceinline__ uint32_t tile_offset(const uint32_t *part) {
+    if constexpr (!kDirect) return part[blockIdx.x];
+    uint32_t sum = 0;
+#pragma unroll 4
+    for (uint32_t i = threadIdx.x; i < blockIdx.x; i += kBlock) sum += part[i];
+    return block_sum(sum);
+}
+
+template <bool kDirect, ScanEnd kEnd>
 __global__ void __launch_bounds__(kBlock) k_scan_apply(const uint32_t *in, const uint32_t *n_dev,
                                                        uint32_t n_cap, const uint32_t *part,
-                                                       uint32_t *out) {
+                                                       ScanOut o) {
     const uint32_t n = scan_len(n_dev, n_cap);
-    if (blockIdx.x * kScanTile >= n) return;
+    if (blockIdx.x > 0 && blockIdx.x * kScanTile >= n) return;
     const uint32_t base = blockIdx.x * kScanTile + threadIdx.x * kScanItems;
-    uint32_t v[kScanItems];
-    uint32_t s = 0;
-    for (int i = 0; i < kScanItems; ++i) {
-        v[i] = (base + i < n) ? scan_in<kPopc>(in, base + i) : 0u;
-        s += v[i];
-    }
+    uint32_t v[kScanItems], sum = 0;
+    load_items(in, base, n, v);
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) sum += v[k];
+    const uint32_t off = tile_offset<kDirect>(part);
     uint32_t tot;
-    uint32_t run = block_excl_scan(s, &tot) + part[blockIdx.x];
-    for (int i = 0; i < kScanItems; ++i) {
-        if (base + i < n) out[base + i] = run;
-        run += v[i];
+    uint32_t run = off + block_excl_scan(sum, &tot);
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) {
+        const uint32_t x = v[k];
+        v[k] = run;
+        run += x;
     }
+    store_items(o.out, base, n, v);
+    if (n - blockIdx.x * kScanTile <= (uint32_t)kScanTile && threadIdx.x < 64)
+        scan_end<kEnd>(o, n, off + tot);
 }
 
-// out[i] = sum of in[0..i) for i <= n, n = min(*n_dev, n_cap) (n_cap if no
-// n_dev); *total_out = out[n]. With kPopc the summands are popcount(in[i]).
-template <bool kPopc = false>
+template <ScanEnd kEnd>
+__global__ void __launch_bounds__(kScanBlock) k_scan_one(const uint32_t *in, const uint32_t *n_dev,
+                                                         uint32_t n_cap, ScanOut o) {
+    const uint32_t n = scan_len(n_dev, n_cap);
+    uint32_t carry = 0;
+    for (uint32_t first = 0; first < n; first += kScanBlock * kScanItems) {
+        const uint32_t base = first + threadIdx.x * kScanItems;
+        uint32_t v[kScanItems], sum = 0, tot;
+        load_items(in, base, n, v);
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) sum += v[k];
+        uint32_t run = carry + block_excl_scan<kScanBlock>(sum, &tot);
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) {
+            const uint32_t x = v[k];
+            v[k] = run;
+            run += x;
+        }
+        store_items(o.out, base, n, v);
+        carry += tot;
+    }
+    if (threadIdx.x < 64) scan_end<kEnd>(o, n, carry);
+}
+
+// Tiles whose sums a workgroup adds up itself (see tile_offset).
+constexpr uint32_t kScanDirect = 2048;
+#ifndef EMT_SCAN_ONE
+#define EMT_SCAN_ONE 32768
+#endif
+constexpr uint32_t kScanOne = EMT_SCAN_ONE;
+
+// o.out[i] = sum of in[0..i) for i <= n, n = min(*n_dev, n_cap) (n_cap if no
+// n_dev), then kEnd with the total. In and out start on 16-byte boundaries.
+template <ScanEnd kEnd>
 void scan_excl(const uint32_t *in, const uint32_t *n_dev, uint32_t n_cap, uint32_t *part,
-               uint32_t *out, uint32_t *total_out, hipStream_t s) {
+               const ScanOut &o, hipStream_t s) {
+    if (n_cap <= kScanOne) {
+        k_scan_one<kEnd><<<1, kScanBlock, 0, s>>>(in, n_dev, n_cap, o);
+        return;
+    }
     const uint32_t nb = n_cap / kScanTile + 1;
-    k_scan_part<kPopc><<<nb, kBlock, 0, s>>>(in, n_dev, n_cap, part);
-    k_scan_part_scan<<<1, kBlock, 0, s>>>(part, nb, n_dev, n_cap, out, total_out);
-    k_scan_apply<kPopc><<<nb, kBlock, 0, s>>>(in, n_dev, n_cap, part, out);
+    k_scan_part<false, kScanItems><<<nb, kBlock, 0, s>>>(in, n_dev, n_cap, part);
+    if (nb <= kScanDirect) {
+        k_scan_apply<true, kEnd><<<nb, kBlock, 0, s>>>(in, n_dev, n_cap, part, o);
+    } else {
+        k_scan_parts<<<1, kScanBlock, 0, s>>>(part, kScanTile, n_dev, n_cap);
+        k_scan_apply<false, kEnd><<<nb, kBlock, 0, s>>>(in, n_dev, n_cap, part, o);
+    }
 }
 
 // ------------------------------------------------------------------- bin
@@ -665,19 +820,6 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Inclusive prefix sum over the 64 lanes with DPP row shifts and row
-// broadcasts (no LDS traffic).
-__device__ __forceinline__ uint32_t wave_incl_scan_dpp(uint32_t x) {
-    uint32_t v = x;
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);  // row_shr:1
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);  // row_shr:2
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);  // row_shr:4
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);  // row_shr:8
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31
-    return v;
-}
-
 // ----------------------------------------------------------------- seeds
 //
 // One wave per anchor grain p (a sorted position); lanes take the (y, z)
@@ -975,37 +1117,6 @@ __global__ void __launch_bounds__(kBlock) k_seeds(DevPtrs d, Caps c, Params P) {
     }
     if constexpr (!kWrite) add_spread(d.part64, 0, wave_total);
 }
-
-// The seed total of the uint32 scan, replaced by the exact 64-bit count
-// (saturated to 2^32 - 1), and the number of seeds the later stages take:
-// none when they do not fit the seed buffer (the host then re-runs the call
-// with a larger one, or fails if no buffer can hold them).
-__global__ void k_seed_total(Counters *cnt, const unsigned long long *part64,
-                             unsigned long long seed_cap) {
-    // one wave: the spread partial sums (kPartSlots == 64, one per lane)
-    const unsigned long long s = wave_sum(part64[lane_id() * kPartStride]);
-    if (threadIdx.x != 0) return;
-    cnt->seeds64 = s;
-    const uint32_t n = s > 0xffffffffull ? 0xffffffffu : (uint32_t)s;
-    cnt->n_seeds = n;
-    cnt->n_seeds_ok = n <= seed_cap ? n : 0u;
-    cnt->pass_words = (uint32_t)(((unsigned long long)cnt->n_seeds_ok + 31ull) / 32ull);
-}
-
-// Likewise for the member entries (the scan of candidate counts): a total
-// that wrapped reads as an overflow, so no stage uses the wrapped offsets.
-__global__ void k_member_total(Counters *cnt, const unsigned long long *part64) {
-    const unsigned long long m = wave_sum(part64[(kPartSlots + lane_id()) * kPartStride]);
-    // the counting kernel's tests and hits, summed here (it has finished)
-    const unsigned long long t = wave_sum(part64[(2 * kPartSlots + lane_id()) * kPartStride]);
-    const unsigned long long h = wave_sum(part64[(3 * kPartSlots + lane_id()) * kPartStride]);
-    if (threadIdx.x != 0) return;
-    cnt->tests = t;
-    cnt->hits = h;
-    cnt->members64 = m;
-    cnt->n_members = m > 0xffffffffull ? 0xffffffffu : (uint32_t)m;
-}
-
 
 // ------------------------------------------------------- count / members
 
@@ -2073,25 +2184,52 @@ __device__ __forceinline__ uint32_t cand_before(const DevPtrs &d, uint32_t s) {
     return d.pass_pos[w] + (b ? (uint32_t)__popc(d.pass[w] & ((1u << b) - 1u)) : 0u);
 }
 
-// Candidates in seed order, one mask word per thread: positions from the
-// scan of the words' popcounts; their counts (for the member offsets); and
-// the seeds and candidates of each view (views are contiguous in anchor
-// order, so in seed and in candidate order too). Keys and thresholds are
-// written by the member listing, which loads both seed grains anyway.
-__global__ void __launch_bounds__(kBlock) k_cand_scatter(DevPtrs d, Caps c, Params P) {
-    const uint32_t ns = d.cnt->n_seeds_ok;
-    for (uint32_t v = grid_tid(); v < d.desc->n_views; v += grid_threads()) {
-        const uint32_t g0 = d.grids[v].grain_off, g1 = g0 + d.grids[v].n;
-        const uint32_t s0 = d.seed_off[d.nc * g0], s1 = d.seed_off[d.nc * g1];
-        d.view_seeds[v] = s1 - s0;
-        d.view_cand[v] = cand_before(d, min(s1, ns)) - cand_before(d, min(s0, ns));
+// Candidates in seed order with their counts (for the member offsets). A
+// workgroup takes kBlock * kWords mask words: it scans their popcounts, which
+// places them in the list and in pass_pos, gathers its set bits in LDS and
+// then takes one candidate per thread. Keys and thresholds are written by the
+// member listing, which loads both seed grains anyway.
+constexpr uint32_t kCandList = 2048;  // candidates listed per round
+
+template <int kWords, bool kDirect>
+__global__ void __launch_bounds__(kBlock) k_cand_list(DevPtrs d, Caps c, const uint32_t *part) {
+    static_assert(kBlock * kWords * 32 <= 65536, "bits are listed as 16-bit numbers");
+    __shared__ uint16_t s_list[kCandList];
+    constexpr uint32_t kTile = kBlock * kWords;
+    const uint32_t nwd = d.cnt->pass_words;
+    if (blockIdx.x > 0 && blockIdx.x * kTile >= nwd) return;
+    const uint32_t base = blockIdx.x * kTile + threadIdx.x * kWords;
+    uint32_t w[kWords], pos[kWords], sum = 0;
+    load_items(d.pass, base, nwd, w);
+#pragma unroll
+    for (int k = 0; k < kWords; ++k) sum += (uint32_t)__popc(w[k]);
+    const uint32_t off = tile_offset<kDirect>(part);
+    uint32_t tot;
+    const uint32_t before = block_excl_scan(sum, &tot);
+    uint32_t run = off + before;
+#pragma unroll
+    for (int k = 0; k < kWords; ++k) {
+        pos[k] = run;
+        run += (uint32_t)__popc(w[k]);
+    }
+    store_items(d.pass_pos, base, nwd, pos);
+    if (nwd - blockIdx.x * kTile <= kTile && threadIdx.x == 0) {
+        d.pass_pos[nwd] = off + tot;
+        d.cnt->n_cand = off + tot;
     }
     unsigned long long listed = 0;  // member entries of the listed candidates
-    const uint32_t nwd = d.cnt->pass_words;
-    for (uint32_t w = grid_tid(); w < nwd; w += grid_threads()) {
-        uint32_t bits = d.pass[w];
-        for (uint32_t pos = d.pass_pos[w]; bits && pos < c.cand_cap; ++pos, bits &= bits - 1u) {
-            const uint32_t s = (w << 5) | (uint32_t)(__ffs(bits) - 1);
+    for (uint32_t r0 = 0; r0 < tot; r0 += kCandList) {  // uniform
+        uint32_t at = before - r0;  // wraps for the candidates of earlier rounds
+#pragma unroll
+        for (int k = 0; k < kWords; ++k)
+            for (uint32_t bits = w[k]; bits; bits &= bits - 1u, ++at)
+                if (at < kCandList)
+                    s_list[at] = (uint16_t)(32u * (threadIdx.x * kWords + k) +
+                                            (uint32_t)__ffs((int)bits) - 1u);
+        __syncthreads();
+        const uint32_t m = min(tot - r0, kCandList);
+        for (uint32_t i = threadIdx.x; i < m && off + r0 + i < c.cand_cap; i += kBlock) {
+            const uint32_t s = 32u * kTile * blockIdx.x + s_list[i];
             const uint32_t n = d.seed_n[s];
             listed += n;
             const uint2 pq = d.seeds[s];
@@ -2100,9 +2238,10 @@ __global__ void __launch_bounds__(kBlock) k_cand_scatter(DevPtrs d, Caps c, Para
             cd.q = pq.y;
             cd.n = n;
             cd.v = d.view_of[pq.x];
-            d.cand[pos] = cd;
-            d.cand_n[pos] = n;
+            d.cand[off + r0 + i] = cd;
+            d.cand_n[off + r0 + i] = n;
         }
+        __syncthreads();  // the list is rewritten by the next round
     }
     add_spread(d.part64, 1, wave_sum(listed));
 }
@@ -2150,7 +2289,15 @@ __global__ void __launch_bounds__(kBlock) k_merge_init(DevPtrs d, Caps c) {
         d.status[i] = kUndecided;
         d.mcount[i] = 0;
     }
-    const uint32_t n_total = d.desc->n_total;
+    const uint32_t n_total = d.desc->n_total, ns = cn->n_seeds_ok;
+    // the seeds and candidates of each view (views are contiguous in anchor
+    // order, so in seed and in candidate order too)
+    for (uint32_t v = grid_tid(); v < d.desc->n_views; v += grid_threads()) {
+        const uint32_t g0 = d.grids[v].grain_off, g1 = g0 + d.grids[v].n;
+        const uint32_t s0 = d.seed_off[d.nc * g0], s1 = d.seed_off[d.nc * g1];
+        d.view_seeds[v] = s1 - s0;
+        d.view_cand[v] = cand_before(d, min(s1, ns)) - cand_before(d, min(s0, ns));
+    }
     for (uint32_t g = grid_tid(); g < n_total; g += grid_threads()) {
         d.owner[g] = ~0ull;
     }
@@ -2866,15 +3013,6 @@ static_assert(kSmallStack / tile_pix(kSmallLoads) < kDirectTiles, "sums are of l
 bool small_stack(const StackGeom &G) { return (uint64_t)G.nx * G.ny * G.nz < kSmallStack; }
 uint32_t stack_tile(const StackGeom &G) { return tile_pix(small_stack(G) ? kSmallLoads : kLargeLoads); }
 
-__device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t *s_wave) {
-    v = wave_sum(v);
-    if (lane_id() == 0) s_wave[threadIdx.x >> 6] = v;
-    __syncthreads();
-    uint32_t tot = 0;
-    for (int w = 0; w < kBlock / 64; ++w) tot += s_wave[w];
-    return tot;
-}
-
 // The 3 x 3 x 3 block around pixel p (flat index): pulse heights w[i]
 // (0 outside the stack) with i = 9 (dz+1) + 3 (dy+1) + (dx+1), so
 // neighbours 0..12 come before p in frame, row, column order.
@@ -3072,7 +3210,6 @@ __global__ void __launch_bounds__(kBlock) k_grain_place(
     const uint32_t *__restrict__ group_cnt, uint32_t n_tiles,
     const uint16_t *__restrict__ stage, uint32_t tile_px, uint32_t lg, int32_t *out,
     uint32_t max_out, uint32_t *total) {
-    __shared__ uint32_t s_wave[kBlock / 64];
     __shared__ uint32_t s_off[65];
     const uint32_t grp = blockIdx.x, t0 = grp << lg, in_group = 1u << lg;
     uint32_t acc = 0;
@@ -3092,7 +3229,7 @@ __global__ void __launch_bounds__(kBlock) k_grain_place(
         s_off[threadIdx.x + 1] = wave_incl_scan_dpp(threadIdx.x < in_group && t < n_tiles ? tile_cnt[t] : 0u);
         if (threadIdx.x == 0) s_off[0] = 0;
     }
-    const uint32_t prefix = block_sum(acc, s_wave);  // synchronises: s_off is written
+    const uint32_t prefix = block_sum(acc);  // synchronises: s_off is written
     const uint32_t n_here = s_off[in_group];
     if (grp + 1 == gridDim.x && threadIdx.x == 0) *total = prefix + n_here;
     for (uint32_t g = threadIdx.x; g < n_here; g += kBlock) {
@@ -3268,7 +3405,11 @@ constexpr uint32_t kFewBlocks = 1024;  // one resident generation of k_count_few
 
 }  // namespace
 
-size_t scan_scratch_words(uint32_t n_cap) { return (size_t)n_cap / kScanTile + 2; }
+// tile sums of a scan of n_cap items, or of the mask words of n_seeds seeds
+size_t scan_scratch_words(uint32_t n_cap, unsigned long long n_seeds) {
+    return std::max({(size_t)n_cap / kScanTile, (size_t)(n_seeds / 32 / (4 * kBlock)),
+                     (size_t)kScanDirect}) + 2;
+}
 
 void launch_prepare(const DevPtrs &d, const Caps &c, const Params &, hipStream_t s) {
     k_zero<<<blocks_for(c.n_cells, 1024), kBlock, 0, s>>>(d.cnt, d.view_seeds, d.view_cand,
@@ -3283,7 +3424,8 @@ void launch_bin(const DevPtrs &d, const Caps &c, const Params &P, hipStream_t s)
     k_grid<<<(c.n_views + 63) / 64, 64, 0, s>>>(d.grids, d.lines, d.lpool, d.lcoarse, d.nc,
                                                    d.desc, P);
     k_hist<<<grid, kBlock, 0, s>>>(d.xyz, d.grids, d.cell_of, d.rank, d.cell_count, d.desc);
-    scan_excl(d.cell_count, &d.desc->n_cells_m1, c.n_cells, d.scan_part, d.cell_start, nullptr, s);
+    scan_excl<kEndTotal>(d.cell_count, &d.desc->n_cells_m1, c.n_cells, d.scan_part,
+                         {d.cell_start}, s);
     k_scatter<<<grid, kBlock, 0, s>>>(d.xyz, d.grids, d.cell_of, d.rank, d.cell_start, d.sg,
                                       d.desc);
 }
@@ -3294,10 +3436,9 @@ void launch_seeds(const DevPtrs &d, const Caps &c, const Params &P, hipStream_t 
                         (8u * kSeedRun) * (8u * kSeedRun);
     if (d.nc > 1) k_line_order<<<dim3(3 + d.nc, c.n_views), kOrderBlock, 0, s>>>(d);
     k_seeds<false><<<nb, kBlock, 0, s>>>(d, c, P);
-    // the scan total counts every seed (it wraps only above 2^32 - 1 a call)
-    // offsets in uint32: exact whenever the total fits, which k_seed_total checks
-    scan_excl(d.seed_cnt, &d.desc->n_anchor, (uint32_t)d.nc * c.n_total, d.scan_part, d.seed_off, &d.cnt->n_seeds, s);
-    k_seed_total<<<1, 64, 0, s>>>(d.cnt, d.part64, c.seed_cap);
+    // offsets in uint32: exact whenever the total fits, which the scan's end checks
+    scan_excl<kEndSeeds>(d.seed_cnt, &d.desc->n_anchor, (uint32_t)d.nc * c.n_total, d.scan_part,
+                         {d.seed_off, nullptr, d.cnt, d.part64, c.seed_cap}, s);
     k_seeds<true><<<nb, kBlock, 0, s>>>(d, c, P);
 }
 
@@ -3322,13 +3463,23 @@ void launch_count(const DevPtrs &d, const Caps &c, const Params &P, hipStream_t 
 
 void launch_candidates(const DevPtrs &d, const Caps &c, const Params &P, hipStream_t s) {
     const uint32_t words = (uint32_t)(c.seed_cap / 32 + 1);
-    scan_excl<true>(d.pass, &d.cnt->pass_words, words, d.scan_part, d.pass_pos, &d.cnt->n_cand, s);
-    k_cand_scatter<<<blocks_for(words, kPersistentBlocks), kBlock, 0, s>>>(d, c, P);
+    const uint32_t nb = words / kBlock + 1;
+    if (nb <= kScanDirect) {
+        k_scan_part<true, 1><<<nb, kBlock, 0, s>>>(d.pass, &d.cnt->pass_words, words, d.scan_part);
+        k_cand_list<1, true><<<nb, kBlock, 0, s>>>(d, c, d.scan_part);
+    } else {
+        constexpr int kWords = 4;
+        constexpr uint32_t kTile = kBlock * kWords;
+        const uint32_t nt = words / kTile + 1;
+        k_scan_part<true, kWords><<<nt, kBlock, 0, s>>>(d.pass, &d.cnt->pass_words, words, d.scan_part);
+        k_scan_parts<<<1, kScanBlock, 0, s>>>(d.scan_part, kTile, &d.cnt->pass_words, words);
+        k_cand_list<kWords, false><<<nt, kBlock, 0, s>>>(d, c, d.scan_part);
+    }
 }
 
 void launch_members(const DevPtrs &d, const Caps &c, const Params &P, hipStream_t s) {
-    scan_excl(d.cand_n, &d.cnt->n_cand, c.cand_cap, d.scan_part, d.mem_off, &d.cnt->n_members, s);
-    k_member_total<<<1, 64, 0, s>>>(d.cnt, d.part64);
+    scan_excl<kEndMembers>(d.cand_n, &d.cnt->n_cand, c.cand_cap, d.scan_part,
+                           {d.mem_off, nullptr, d.cnt, d.part64}, s);
     // the counting kernel's walk and test, listing the grains of each candidate
     if (d.nc == 1) {
         if (P.cyl_ext >= 0)
@@ -3382,7 +3533,8 @@ void launch_fit(const DevPtrs &d, const Caps &c, const Params &P, hipStream_t s)
     unsigned long long *gkey = d.owner;
     k_group<<<nb, kBlock, 0, s>>>(d, gkey);
     k_rank<<<nb, kBlock, 0, s>>>(d, gkey);
-    scan_excl(d.tg_n, &d.cnt->n_acc, c.cand_cap, d.scan_part, d.tg_off, &d.cnt->n_track_grains, s);
+    scan_excl<kEndTotal>(d.tg_n, &d.cnt->n_acc, c.cand_cap, d.scan_part,
+                         {d.tg_off, &d.cnt->n_track_grains}, s);
     k_fit<<<nb, kBlock, 0, s>>>(d, P);
 }
 

@@ -122,3 +122,19 @@ def test_budgets_with_room_for_fewer_classes(emt):
     assert len(accepted) > 40
     for b in (accepted[0], 150, accepted[-1]):
         check(emt, [xyz], hbm_budget=b << 20)
+
+
+@pytest.mark.parametrize("copies", [1, 5, 40, 720])
+def test_scans_of_every_size(emt, copies):
+    """From arrays one workgroup scans to ones whose tile sums take a scan of
+    their own (720 views: 2^21 grains in the buffers, 2^23 cells): every copy
+    of a view comes out as the oracle has it."""
+    xyz = moderate(11)[:1500]
+    ref = oracle.track_view(xyz)
+    with emt.Tracker(device=0, flags=emt.EMT_F_CANDIDATES) as tr:
+        got = tr([xyz] * copies)
+        for v in range(copies):
+            assert_candidates_equal(tr.candidates(v), ref)
+    for g in got:
+        assert g["tracks"].tobytes() == got[0]["tracks"].tobytes()
+    assert_view_parity(xyz, got[0], ref)
