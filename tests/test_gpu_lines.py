@@ -138,3 +138,15 @@ def test_scans_of_every_size(emt, copies):
     for g in got:
         assert g["tracks"].tobytes() == got[0]["tracks"].tobytes()
     assert_view_parity(xyz, got[0], ref)
+
+
+def test_dense_call_after_sparse_ones(emt):
+    """The sparse calls leave few grid-wide merge rounds for the next call of
+    their size; the dense one's other rounds are the tail's."""
+    sparse, dense = moderate(11, density=1.0)[:4000], moderate(12, density=20.0)[:4000]
+    with emt.Tracker(device=0, flags=emt.EMT_F_CANDIDATES) as tr:
+        for xyz in (dense, sparse, sparse, dense):
+            got = tr([xyz])[0]
+            ref = oracle.track_view(xyz)
+            assert_candidates_equal(tr.candidates(0), ref)
+            assert_view_parity(xyz, got, ref)
