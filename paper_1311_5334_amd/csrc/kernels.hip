@@ -77,6 +77,9 @@ __device__ __forceinline__ void add_spread(unsigned long long *part64, int which
     __syncthreads();  // s_part is free again for the next call
 }
 
+// (__ballot turns its argument into an integer and compares that)
+__device__ __forceinline__ unsigned long long ballot(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+
 __device__ __forceinline__ uint32_t grid_tid() { return blockIdx.x * blockDim.x + threadIdx.x; }
 __device__ __forceinline__ uint32_t grid_threads() { return gridDim.x * blockDim.x; }
 
@@ -1124,8 +1127,10 @@ __global__ void __launch_bounds__(kBlock) k_seeds(DevPtrs d, Caps c, Params P) {
 // Line grids: filling the cells.
 //
 // A record covers a block of 8 x 4 cells of a plane: x has a bit for every
-// cell that lists grains, y is the list word of its first such cell, the
-// others following in cell order. A cell's word is its grain, or for several
+// cell that lists grains, cell 0's the topmost, y + 1 is the list word of its
+// last such cell, the others following in falling cell order: with the bit of
+// the cell asked for shifted to the top, the sign says whether it lists any and
+// the bits left count the words from y. A cell's word is its grain, or for several
 // grains x = kLineList and y the first of their words; those are the grains,
 // with kLineList on all but the last. A grain's word holds its coordinates, so
 // that the test needs no other load: 19 bits along the face's axis, 12 bits
@@ -1242,7 +1247,7 @@ __global__ void __launch_bounds__(kLineBlock) k_line_fill(DevPtrs d, Params P) {
 #pragma unroll 8
         for (int i = 0; i < 32; ++i) {
             const uint32_t n = mine[i];
-            bits |= n ? 1u << i : 0u;
+            bits |= n ? 0x80000000u >> i : 0u;
             words += n < 2u ? n : n + 1u;
         }
         const uint32_t incl = wave_incl_scan_dpp(words);
@@ -1263,10 +1268,10 @@ __global__ void __launch_bounds__(kLineBlock) k_line_fill(DevPtrs d, Params P) {
         uint32_t lists = 0;  // the cells of this record that list several grains
         if (threadIdx.x < n_rec) {
             recs[(size_t)k * plane + (size_t)r0 * bu + threadIdx.x] =
-                make_uint2(room ? bits : 0u, base);
+                make_uint2(room ? bits : 0u, base - 1u);
             uint32_t word = base, list = base + (uint32_t)__popc(bits);
             for (uint32_t rest = room ? bits : 0u; rest; rest &= rest - 1u) {
-                const int i = __ffs(rest) - 1;
+                const int i = 32 - __ffs(rest);
                 const uint32_t n = mine[i];
                 if (n == 1) {
                     mine[i] = word;
@@ -1302,10 +1307,10 @@ __global__ void __launch_bounds__(kLineBlock) k_line_fill(DevPtrs d, Params P) {
 }
 
 // Bound by VALU issue and by the cache lines the record and word loads touch
-// (8 c5 views: VALU 77 % and L1 address unit 90 % busy; L2 hits 95 %). One
+// (8 c5 views: VALU 76 % busy, 0.84 L1 accesses a cycle; L2 hits 95 %). One
 // lookup a slab and 16 tests a seed replace the 20 cell pencils and 84 tests
-// of a walk over the binned cells: 12.3 against 26.0 ms for the 163 M seeds of
-// 8 c5 views, and 230 against 500 us for the 3.3 M of one c2 view.
+// of a walk over the binned cells: 11.9 against 26.0 ms for the 163 M seeds of
+// 8 c5 views, and 225 against 500 us for the 3.3 M of one c2 view.
 //
 // Counting: a wave counts 64 lines at a time, one a lane. The lines of one
 // class (nearly always all 64) step through its slabs together, so that what
@@ -1324,7 +1329,7 @@ constexpr uint32_t kApartSeeds = 50000000;         // seeds from which XCDs work
 constexpr uint32_t kQueue = 64u * (kFetch + 1);
 // queued: position in the class's pool, lane of the line, and whether the
 // word is one of a cell's list (else a cell's first); the cell, u << 16 | v
-constexpr uint32_t kItemLane = 24, kItemList = 1u << 30;
+constexpr uint32_t kItemLane = 24, kItemList = 1u << 31;
 // fractional bits of a crossing point: its cell is the upper half word, and a
 // slab's step, rounded to half of the last bit, is off by at most 1.5 units at
 // the far side of the largest view (2^18 / w slabs; line_grid keeps c <= 3/4 w)
@@ -1476,19 +1481,18 @@ struct LineClass {
     int face, packed, c8, c4;  // packed words: u = word + c8 column, v = word + c4 row
 };
 
-template <class T>
-__device__ __forceinline__ T *uniform(T *p) {
-    const unsigned long long a = (unsigned long long)p;
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
-    return (T *)(((unsigned long long)hi << 32) | lo);
-}
-
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 __device__ __forceinline__ uint32_t uniform(uint32_t x) {
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
 }
 
+__device__ __forceinline__ size_t uniform(size_t x) {
+    return ((size_t)uniform((uint32_t)(x >> 32)) << 32) | uniform((uint32_t)x);
+}
+
+// Uniform offsets are added to the kernel's own pointers: a pointer put
+// together from two words would be of no known address space, and its loads
+// flat ones, which also wait for and hold up the LDS.
 __device__ __forceinline__ LineClass line_class_of(const DevPtrs &d, uint32_t v, uint32_t cls) {
     const LineGrid *L = line_grid_of(d, v);
     LineClass K;
@@ -1499,15 +1503,21 @@ __device__ __forceinline__ LineClass line_class_of(const DevPtrs &d, uint32_t v,
     K.nv = uniform((uint32_t)L->nv[a]);
     K.bu = uniform((uint32_t)L->bu[a]);
     K.plane = uniform(L->plane[a]);
-    K.recs = uniform(d.lrec + (size_t)line_recs(d.nc) * K.goff + L->face_off[a] +
-                     (size_t)sub * (uint32_t)L->ns[a] * K.plane);
-    K.ent = uniform(d.lent + line_pool((uint32_t)d.nc, K.goff, n, cls));
-    K.sorted = uniform(d.lsg + 3 * (size_t)K.goff + (size_t)a * n);
+    K.recs = d.lrec + uniform((size_t)line_recs(d.nc) * K.goff + L->face_off[a] +
+                              (size_t)sub * (uint32_t)L->ns[a] * K.plane);
+    K.ent = d.lent + uniform((size_t)line_pool((uint32_t)d.nc, K.goff, n, cls));
+    K.sorted = d.lsg + uniform(3 * (size_t)K.goff + (size_t)a * n);
     K.face = (int)a;
     K.packed = uniform(L->packed);
     K.c8 = uniform(8 * L->c);
     K.c4 = uniform(4 * L->c);
     return K;
+}
+
+// A 32-bit byte offset from a uniform pointer: the load adds the two itself.
+template <class T>
+__device__ __forceinline__ const T *at_byte(const T *p, uint32_t offset) {
+    return reinterpret_cast<const T *>(reinterpret_cast<const char *>(p) + offset);
 }
 
 // A grain's coordinates in the axes of face a: along it, u, v (and its index).
@@ -1529,10 +1539,13 @@ __device__ __forceinline__ uint32_t count_test(CountLds<kFinite, kEmit> &Q, uint
     qn -= m;
     const uint2 item = Q.queue[qn + min((uint32_t)lane, m - 1u)];
     const uint32_t at = item.x & ((1u << kItemLane) - 1u), sl = (item.x >> kItemLane) & 63u;
-    const uint2 w = K.ent[at];
+    const uint2 w = *at_byte(K.ent, 8u * at);
     const float4 A = Q.la[sl], C = Q.lc[sl];
-    const bool on = (uint32_t)lane < m, list = (item.x & kItemList) != 0;
-    const bool flag = (int)w.x < 0, ptr = !list && flag, more = on && flag;
+    // lane masks rather than flags: they stay in scalar registers
+    const unsigned long long on = ~0ull >> (64u - m), flag = ballot((int)w.x < 0);
+    const unsigned long long ptrs = flag & ~ballot((int)item.x < 0), more = flag & on;
+    const unsigned long long test = on & ~ptrs;
+    const bool ptr = __builtin_amdgcn_inverse_ballot_w64(ptrs);
     float3 h;
     uint32_t rel;
     if (K.packed) {
@@ -1546,22 +1559,23 @@ __device__ __forceinline__ uint32_t count_test(CountLds<kFinite, kEmit> &Q, uint
         h = make_float3(g.x, g.y, g.z);
         rel = w.y;
     }
-    const unsigned long long mm = __ballot(more);
-    if (mm) {
+    if (more) {
         wave_lds_sync();  // the items have been read
-        if (more)
-            Q.queue[qn + (uint32_t)__popcll(mm & lanes_below())] =
+        if (__builtin_amdgcn_inverse_ballot_w64(more))
+            Q.queue[__builtin_amdgcn_mbcnt_hi((uint32_t)(more >> 32),
+                                              __builtin_amdgcn_mbcnt_lo((uint32_t)more, qn))] =
                 make_uint2((ptr ? w.y : at + 1u) | (sl << kItemLane) | kItemList, item.y);
-        qn += (uint32_t)__popcll(mm);
+        qn += (uint32_t)__popcll(more);
         wave_lds_sync();
     }
     const float c0 = fmaf(h.y, A.z, fmaf(h.z, -A.y, C.x));
     const float c1 = fmaf(h.z, A.x, fmaf(h.x, -A.z, C.y));
     const float c2 = fmaf(h.x, A.y, fmaf(h.y, -A.x, C.z));
     const float fc = fmaf(c0, c0, fmaf(c1, c1, c2 * c2));
-    const bool test = on && !ptr;
-    bool ok = test && fc <= C.w;
-    if (ok && fc > A.w) {
+    const unsigned long long near = test & ballot(fc <= C.w);
+    const unsigned long long band = near & ballot(fc > A.w);
+    bool ok = __builtin_amdgcn_inverse_ballot_w64(near);
+    if (band && __builtin_amdgcn_inverse_ballot_w64(band)) {
         // inside the band: decide in int64 from the integer grains (rare)
         const int dx = (int)A.x, dy = (int)A.y, dz = (int)A.z;
         const long long D = (long long)dx * dx + (long long)dy * dy + (long long)dz * dz;
@@ -1582,7 +1596,7 @@ __device__ __forceinline__ uint32_t count_test(CountLds<kFinite, kEmit> &Q, uint
             if (n < mo.y) d.members[mo.x + n] = K.goff + rel;
         }
     }
-    return (uint32_t)__popcll(__ballot(test));
+    return (uint32_t)__popcll(test);
 }
 
 // kEmit: the members stage. The same walk and test over the candidates
@@ -1706,11 +1720,11 @@ k_count(DevPtrs d, Caps c, Params P) {
         }
         wave_lds_sync();
         // the classes among the lanes, one after another
-        for (unsigned long long left = __ballot(have); left;) {
+        for (unsigned long long left = ballot(have); left;) {
             const uint32_t cls_key =
                 (uint32_t)__builtin_amdgcn_readlane((int)key, __ffsll((long long)left) - 1);
             const bool mine = key == cls_key;
-            left &= ~__ballot(mine);
+            left &= ~ballot(mine);
             const uint32_t vw = cls_key / (uint32_t)d.nc;
             const LineClass K = line_class_of(d, vw, cls_key - vw * (uint32_t)d.nc);
             const float kmin = wave_min(mine ? klo : 1.0e9f), kmax = wave_max(mine ? khi : -1.0f);
@@ -1728,7 +1742,7 @@ k_count(DevPtrs d, Caps c, Params P) {
             const uint32_t lim_u = K.nu << kLineBits, lim_v = K.nv << kLineBits;
             // a finite cylinder's own slabs (an empty range has none)
             const uint32_t first = (uint32_t)klo, slabs = khi >= klo ? (uint32_t)khi - first : 0u;
-            const uint2 *recs = K.recs + (size_t)k0 * K.plane;
+            size_t first_rec = (size_t)k0 * K.plane;  // the slab's, scalar
             const uint32_t lane_tag = (uint32_t)lane << kItemLane;
             uint32_t qn = 0;
             for (uint32_t k = k0; k <= k1; k += kFetch) {
@@ -1741,22 +1755,24 @@ k_count(DevPtrs d, Caps c, Params P) {
                     if constexpr (kFinite) ok = ok && k + (uint32_t)f - first <= slabs;
                     cell[f] = __builtin_amdgcn_perm(u, v, 0x07060302u);
                     rec[f].x = 0u;
-                    if (ok) rec[f] = recs[__umul24((cell[f] >> 2) & 0x3fffu, K.bu) + (cell[f] >> 19)];
-                    recs += K.plane;
+                    if (ok)
+                        rec[f] = *at_byte(K.recs + first_rec, 8u * (__umul24((cell[f] >> 2) & 0x3fffu, K.bu) +
+                                                      (cell[f] >> 19)));
+                    first_rec += K.plane;
                     u += ddu;
                     v += ddv;
                 }
 #pragma unroll
                 for (int f = 0; f < kFetch; ++f) {
-                    // cell 8 (v & 3) + (u & 7) of the record
-                    const uint32_t bit = ((cell[f] & 3u) << 3) | ((cell[f] >> 16) & 7u);
-                    const uint32_t low = ~(~0u << bit);
-                    const bool in = (rec[f].x >> bit) & 1u;
-                    const unsigned long long m = __ballot(in);
+                    // cell 8 (v & 3) + (u & 7) of the record, as the top bit
+                    const uint32_t bits =
+                        rec[f].x << (((cell[f] << 3) | ((cell[f] >> 16) & 7u)) & 31u);
+                    const bool in = (int)bits < 0;
+                    const unsigned long long m = ballot(in);
                     if (in)
                         Q.queue[__builtin_amdgcn_mbcnt_hi(
                             (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, qn))] =
-                            make_uint2((rec[f].y + (uint32_t)__popc(rec[f].x & low)) | lane_tag,
+                            make_uint2((rec[f].y + (uint32_t)__popc(bits)) | lane_tag,
                                        cell[f]);
                     qn += (uint32_t)__popcll(m);
                 }
