@@ -96,6 +96,15 @@ __device__ __forceinline__ uint32_t wave_incl_scan_dpp(uint32_t x) {
     return v;
 }
 
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ uint32_t uniform(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+}
+
+__device__ __forceinline__ unsigned long long uniform(unsigned long long x) {
+    return ((unsigned long long)uniform((uint32_t)(x >> 32)) << 32) | uniform((uint32_t)x);
+}
+
 // ------------------------------------------------------------------ scan
 
 // Exclusive scan inside one block of kThreads threads.
@@ -831,7 +840,11 @@ __device__ __forceinline__ void wave_lds_sync() {
 // makes a seed, stored with the lower input index first. A first pass counts
 // the seeds of every anchor, a scan turns the counts into offsets, and a
 // second pass writes them: no shared counter, and the seed list comes out in
-// anchor order, so each view's seeds are contiguous.
+// anchor order, so each view's seeds are contiguous. Bound by VALU issue (the
+// count pass by itself, the write pass also by its partly written lines, 2.9 GB
+// for 1.3): finding an element's row by counting row ends instead of a search
+// over the row starts, cell bounds by reciprocals and the pair test in FP32
+// took 8 c5 views' passes from 2.9 to 2.45 ms, one c2 view's from 74 to 52 us.
 // The line class of direction d (up to the rounding at the bins' edges, where
 // both classes list the line's grains): its face, and its slopes' bins.
 __device__ __forceinline__ int line_face(int ax, int ay, int az) {
@@ -842,11 +855,12 @@ __device__ __forceinline__ int line_bin(float slope, int sub) {
     return max(0, min(sub - 1, (int)((slope + 1.0f) * (0.5f * (float)sub))));
 }
 
-__device__ __forceinline__ int line_class(int dx, int dy, int dz, int ns) {
-    const int a = line_face(abs(dx), abs(dy), abs(dz));
-    const float ida = __builtin_amdgcn_rcpf((float)(a == 0 ? dx : a == 1 ? dy : dz));
-    const float su = (float)(a == 0 ? dy : dx) * ida, sv = (float)(a == 2 ? dy : dz) * ida;
-    return ns == 0 ? 0 : (a * ns + line_bin(su, ns)) * ns + line_bin(sv, ns);
+__device__ __forceinline__ int line_class(float dx, float dy, float dz, int ns) {
+    const bool x = fabsf(dx) >= fabsf(dy) && fabsf(dx) >= fabsf(dz), z = fabsf(dy) < fabsf(dz);
+    const int a = x ? 0 : (z ? 2 : 1);
+    const float ida = __builtin_amdgcn_rcpf(x ? dx : z ? dz : dy);
+    const float su = (x ? dy : dx) * ida, sv = (x || !z ? dz : dy) * ida;
+    return (a * ns + line_bin(su, ns)) * ns + line_bin(sv, ns);
 }
 
 // The order of a class's seeds: their anchors by tiles of the plane across
@@ -989,12 +1003,15 @@ __global__ void __launch_bounds__(kOrderBlock) k_line_order(DevPtrs d) {
 static_assert(kTiles == 2 * kOrderBlock, "two tiles a thread");
 
 constexpr uint32_t kSeedRun = 64;
+constexpr uint32_t kSeedWords = 64;  // one a lane: 4096 elements
 
 template <bool kWrite>
 __global__ void __launch_bounds__(kBlock) k_seeds(DevPtrs d, Caps c, Params P) {
-    // per wave: the first flat element of each row, and sorted position
-    // minus that (so that grain = dk[r] + element)
-    __shared__ uint32_t s_rows[kBlock / 64][2][64];
+    // per wave: for each row that has grains, the sorted position of its first
+    // minus the row's first flat element (so that grain = dk[r] + element); a
+    // bit for every element that ends a row
+    __shared__ uint32_t s_rows[kBlock / 64][65];
+    __shared__ unsigned long long s_ends[kBlock / 64][kSeedWords];
     // per wave and class: the anchor's seeds so far, or where the next goes
     __shared__ uint32_t s_cls[kBlock / 64][kLineClasses];
     uint32_t *cls_s = s_cls[threadIdx.x >> 6];
@@ -1007,7 +1024,7 @@ __global__ void __launch_bounds__(kBlock) k_seeds(DevPtrs d, Caps c, Params P) {
     const uint32_t gw = wg * (kBlock / 64) + (threadIdx.x >> 6);
     const uint32_t nw = grid_threads() >> 6;
     const int R1 = P.R - 1;
-    const int R2 = P.R * P.R;
+    const float R2 = (float)(P.R * P.R);
     const uint32_t n_total = d.desc->n_total;
     // the write pass has nothing to do when the seeds overflow their buffer
     if (kWrite && d.cnt->n_seeds_ok == 0) return;
@@ -1040,31 +1057,41 @@ __global__ void __launch_bounds__(kBlock) k_seeds(DevPtrs d, Caps c, Params P) {
             const int cx = G->cell[0], cy = G->cell[1], cz = G->cell[2];
             const uint32_t off = G->cell_off;
             const int4 g = d.sg[p];
-            const int x0 = g.x - R1 < 0 ? 0 : (g.x - R1) / cx;
-            const int y0 = g.y - R1 < 0 ? 0 : (g.y - R1) / cy;
-            const int z0 = g.z - R1 < 0 ? 0 : (g.z - R1) / cz;
-            const int x1 = min(nx - 1, (g.x + R1) / cx);
-            const int y1 = min(ny - 1, (g.y + R1) / cy);
-            const int z1 = min(nz - 1, (g.z + R1) / cz);
+            // the box's first and last cells, to the cell or one too wide
+            // (reciprocals; coordinates are below 2^18, and the pair test and
+            // the least position decide what a wider box adds)
+            constexpr float kLess = 1.0f - 0x1p-20f, kMore = 1.0f + 0x1p-20f;
+            const float icx = __builtin_amdgcn_rcpf((float)cx), icy = __builtin_amdgcn_rcpf((float)cy),
+                        icz = __builtin_amdgcn_rcpf((float)cz);
+            const int x0 = (int)((float)max(0, g.x - R1) * (icx * kLess));
+            const int y0 = (int)((float)max(0, g.y - R1) * (icy * kLess));
+            const int z0 = (int)((float)max(0, g.z - R1) * (icz * kLess));
+            const int x1 = min(nx - 1, (int)((float)(g.x + R1) * (icx * kMore)));
+            const int y1 = min(ny - 1, (int)((float)(g.y + R1) * (icy * kMore)));
+            const int z1 = min(nz - 1, (int)((float)(g.z + R1) * (icz * kMore)));
             // each unordered pair once, from the grain with the lower sorted
             // position: rows of the box that sort before the anchor's own row
             // hold only lower positions, and in its row the scan starts past it
-            const int yp = min(ny - 1, g.y / cy), zp = min(nz - 1, g.z / cz);
+            const int yp = min(ny - 1, (int)((float)g.y * (icy * kLess)));
+            const int zp = min(nz - 1, (int)((float)g.z * (icz * kLess)));
             const int nyr = y1 - y0 + 1;
+            const float inyr = __builtin_amdgcn_rcpf((float)nyr) * kMore;
             const int nrows = nyr * (z1 - z0 + 1);
             const int row_p = (zp - z0) * nyr + (yp - y0);
             // the rows' grains are taken as one flat range: lane L tests
-            // elements b + L and b + 64 + L of each trip, each found in row
-            // r, the last row whose first element is at or below it (a
-            // binary search over the rows' starts in LDS), so every lane has
-            // grains whatever the row lengths
-            uint32_t *ex_s = s_rows[threadIdx.x >> 6][0];
-            uint32_t *dk_s = s_rows[threadIdx.x >> 6][1];
+            // elements b + L and b + 64 + L of each trip, so every lane has
+            // grains whatever the row lengths. An element is of the row
+            // numbered by the row ends before it: those of earlier words are
+            // counted as the trips go on, those of its own by two instructions
+            // on the word, which is the same for all lanes.
+            uint32_t *dk_s = s_rows[threadIdx.x >> 6];
+            unsigned long long *ends_s = s_ends[threadIdx.x >> 6];
             for (int rb = row_p; rb < nrows; rb += 64) {
                 const int rr = rb + lane;
                 uint32_t k0 = 0, k1 = 0;
                 if (rr < nrows) {
-                    const int y = y0 + rr % nyr, z = z0 + rr / nyr;
+                    const int rz = (int)((float)rr * inyr);  // exact: rr < 2^18
+                    const int y = y0 + rr - rz * nyr, z = z0 + rz;
                     const uint32_t row = off + (uint32_t)((z * ny + y) * nx);
                     k0 = max(d.cell_start[row + x0], p + 1);
                     k1 = d.cell_start[row + x1 + 1];
@@ -1072,43 +1099,58 @@ __global__ void __launch_bounds__(kBlock) k_seeds(DevPtrs d, Caps c, Params P) {
                 const uint32_t len = k1 > k0 ? k1 - k0 : 0u;
                 const uint32_t incl = wave_incl_scan_dpp(len);
                 const uint32_t T = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+                const unsigned long long some = ballot(len > 0);
+                const uint32_t slot = __builtin_amdgcn_mbcnt_hi(
+                    (uint32_t)(some >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)some, 0u));
                 wave_lds_sync();  // the previous block's readers are done
-                ex_s[lane] = incl - len;
-                dk_s[lane] = k0 - (incl - len);
-                wave_lds_sync();
-                // the grain of flat element i (the anchor itself past the end)
-                auto grain_of = [&](uint32_t i) -> uint32_t {
-                    uint32_t r = 0;
-#pragma unroll
-                    for (uint32_t step = 32; step > 0; step >>= 1)
-                        r = ex_s[r + step] <= i ? r + step : r;
-                    return i < T ? dk_s[r] + i : p;
-                };
-                auto pairs = [&](const int4 &h, bool ok) {
-                    const int ex = h.x - g.x, ey = h.y - g.y, ez = h.z - g.z;
-                    ok = ok && abs(ex) <= R1 && abs(ey) <= R1 && abs(ez) <= R1;
-                    const int D = ok ? ex * ex + ey * ey + ez * ez : 0;
-                    return ok && D > 0 && D < R2;
-                };
-                auto take = [&](bool ok, const int4 &h, uint32_t q) {
-                    if (!ok) return;
-                    const uint32_t slot =
-                        atomicAdd(&cls_s[line_class(h.x - g.x, h.y - g.y, h.z - g.z, nsub)], 1u);
-                    // stored lower input index first: that grain is the
-                    // seed's i (the fit's origin and key order)
-                    if (kWrite && slot < c.seed_cap)
-                        d.seeds[slot] = h.w > g.w ? make_uint2(p, q) : make_uint2(q, p);
-                };
-                // two elements a lane per trip: their row searches and grain
-                // loads are in flight together
-                for (uint32_t b = 0; b < T; b += 128) {
-                    const uint32_t i0 = b + (uint32_t)lane, i1 = i0 + 64;
-                    const uint32_t q0 = grain_of(i0), q1 = grain_of(i1);
-                    const int4 h0 = d.sg[q0], h1 = d.sg[q1];
-                    const bool ok0 = pairs(h0, i0 < T), ok1 = pairs(h1, i1 < T);
-                    take(ok0, h0, q0);
-                    take(ok1, h1, q1);
-                    if (!kWrite) mine += (ok0 ? 1u : 0u) + (ok1 ? 1u : 0u);
+                if (len) dk_s[slot] = k0 - (incl - len);
+                uint32_t rows = 0;  // rows that end before word e0
+                for (uint32_t e0 = 0; e0 < T; e0 += 64 * kSeedWords) {
+                    ends_s[lane] = 0ull;
+                    wave_lds_sync();
+                    const uint32_t end = incl - 1u - e0;
+                    if (len && end < 64 * kSeedWords) atomicOr(&ends_s[end >> 6], 1ull << (end & 63u));
+                    wave_lds_sync();
+                    // the grain of flat element i, of word m (past the end the
+                    // anchor itself, which makes no pair)
+                    auto grain_of = [&](uint32_t i, unsigned long long m) -> uint32_t {
+                        const uint32_t r = __builtin_amdgcn_mbcnt_hi(
+                            (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, rows));
+                        rows += (uint32_t)__popcll(m);
+                        return i < T ? dk_s[r] + i : p;
+                    };
+                    // |g_h - g|^2 in (0, R^2): R^2 is below 2^24, so a sum below
+                    // it is exact in FP32 and one above it stays above
+                    auto pairs = [&](const int4 &h, float3 &e) {
+                        e = make_float3((float)(h.x - g.x), (float)(h.y - g.y), (float)(h.z - g.z));
+                        const float D = fmaf(e.x, e.x, fmaf(e.y, e.y, e.z * e.z));
+                        return D > 0.0f && D < R2;
+                    };
+                    auto take = [&](bool ok, const int4 &h, const float3 &e, uint32_t q) {
+                        if (!ok) return;
+                        const uint32_t slot =
+                            atomicAdd(&cls_s[nsub ? line_class(e.x, e.y, e.z, nsub) : 0], 1u);
+                        // stored lower input index first: that grain is the
+                        // seed's i (the fit's origin and key order)
+                        if (kWrite && slot < c.seed_cap)
+                            d.seeds[slot] = h.w > g.w ? make_uint2(p, q) : make_uint2(q, p);
+                    };
+                    // two elements a lane per trip: their row searches and grain
+                    // loads are in flight together
+                    const uint32_t e1 = min(T, e0 + 64 * kSeedWords);
+                    for (uint32_t b = e0; b < e1; b += 128) {
+                        const uint32_t i0 = b + (uint32_t)lane, i1 = i0 + 64;
+                        const unsigned long long *word = ends_s + ((b - e0) >> 6);
+                        const uint32_t q0 = grain_of(i0, uniform(word[0]));
+                        const uint32_t q1 = grain_of(i1, uniform(word[1]));
+                        const int4 h0 = d.sg[q0], h1 = d.sg[q1];
+                        float3 d0, d1;
+                        const bool ok0 = pairs(h0, d0), ok1 = pairs(h1, d1);
+                        take(ok0, h0, d0, q0);
+                        take(ok1, h1, d1, q1);
+                        if (!kWrite) mine += (ok0 ? 1u : 0u) + (ok1 ? 1u : 0u);
+                    }
+                    wave_lds_sync();  // the words have been read
                 }
             }
         }
@@ -1481,15 +1523,6 @@ struct LineClass {
     int face, packed, c8, c4;  // packed words: u = word + c8 column, v = word + c4 row
 };
 
-__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ __forceinline__ uint32_t uniform(uint32_t x) {
-    return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
-}
-
-__device__ __forceinline__ size_t uniform(size_t x) {
-    return ((size_t)uniform((uint32_t)(x >> 32)) << 32) | uniform((uint32_t)x);
-}
-
 // Uniform offsets are added to the kernel's own pointers: a pointer put
 // together from two words would be of no known address space, and its loads
 // flat ones, which also wait for and hold up the LDS.
@@ -1503,10 +1536,10 @@ __device__ __forceinline__ LineClass line_class_of(const DevPtrs &d, uint32_t v,
     K.nv = uniform((uint32_t)L->nv[a]);
     K.bu = uniform((uint32_t)L->bu[a]);
     K.plane = uniform(L->plane[a]);
-    K.recs = d.lrec + uniform((size_t)line_recs(d.nc) * K.goff + L->face_off[a] +
+    K.recs = d.lrec + uniform(line_recs(d.nc) * (unsigned long long)K.goff + L->face_off[a] +
                               (size_t)sub * (uint32_t)L->ns[a] * K.plane);
-    K.ent = d.lent + uniform((size_t)line_pool((uint32_t)d.nc, K.goff, n, cls));
-    K.sorted = d.lsg + uniform(3 * (size_t)K.goff + (size_t)a * n);
+    K.ent = d.lent + uniform((unsigned long long)line_pool((uint32_t)d.nc, K.goff, n, cls));
+    K.sorted = d.lsg + uniform(3ull * K.goff + (unsigned long long)a * n);
     K.face = (int)a;
     K.packed = uniform(L->packed);
     K.c8 = uniform(8 * L->c);
