@@ -68,6 +68,8 @@ struct emt_ctx {
     // grid-wide merge rounds for the next call of each size class (the
     // capacity bucket of n_total, by its power of two; 0: not known yet)
     int8_t next_wide[32] = {};
+    // seeds per grain of the last call of each size class (0: none)
+    float last_seeds[32] = {};
 
     // pinned host buffers
     int32_t *h_xyz = nullptr;
@@ -434,7 +436,7 @@ int ensure(emt_ctx *ctx, Caps &c) {
     c.seed_cap = h.seed_cap;
     c.cand_cap = h.cand_cap;
     c.mem_cap = h.mem_cap;
-    c.nc = few_grains(c.n_total, ctx->cfg.cyl_ext) ? 1 : h.nc;
+    c.nc = c.few ? 1 : h.nc;
     if (!ctx->h_desc) {
         size_t cap = 0;
         if ((rc = pinned(ctx, ctx->h_desc, cap, 1))) return rc;
@@ -659,6 +661,7 @@ int batch_caps(const emt_ctx *ctx, unsigned long long n_total, uint32_t n_views,
                          4096, (unsigned long long)(ctx->seeds_per_grain * (double)c.n_total)));
     c.cand_cap = clamp_cap(ctx->cand_per_grain * (double)c.n_total);
     c.mem_cap = clamp_cap(ctx->mem_per_cand * (double)c.cand_cap);
+    c.few = few_grains(n_total, max_n, ctx->cfg.cyl_ext, ctx->last_seeds[size_class(c.n_total)]);
     const int wide = ctx->next_wide[size_class(c.n_total)];
     c.wide_rounds = wide > 0 ? wide : max_wide_rounds();
     *out = c;
@@ -1006,6 +1009,8 @@ int finish_views(emt_ctx *ctx, emt_view_out *out) {
     const int spare = c.n_total <= kTailGrains ? 1 : 2, least = c.n_total <= kTailGrains ? 2 : 6;
     ctx->next_wide[size_class(c.n_total)] = (int8_t)std::min(
         max_wide_rounds(), std::max(least, (int)std::min(h.rounds, 255u) + spare));
+    if (ctx->h_desc->n_total)
+        ctx->last_seeds[size_class(c.n_total)] = (float)h.seeds64 / (float)ctx->h_desc->n_total;
     emt_call_stats &st = ctx->last;
     st = emt_call_stats{};
     st.n_seeds = h.seeds64;

@@ -20,18 +20,28 @@ constexpr int kBlock = 256;
 // are doubled until the grid fits.
 constexpr uint32_t kCellsPerGrain = EMT_CELLS_PER_GRAIN;
 constexpr uint32_t kCellsBase = 4096;
-// Whether a call counts over the binned cells instead of line grids: filling
-// those costs 30 to 60 us, which a small call does not win back (one view of
-// 900 grains: count and members 79 us over the cells, 150 us over line grids;
-// one of 27k: 627 and 416 us), nor does a medium one of short finite cylinders
-// (27k grains, reaching 5 um: equal; 20 um: 600 and 490 us). n_grains: the
-// call's capacity bucket.
-constexpr uint32_t kFewGrains = 8192;
-constexpr uint32_t kFewGrainsShort = 65536;
+// Whether a call counts over the binned cells instead of line grids: those
+// cost 60 us and more for every view, which its seeds have to win back.
+// seeds_per_grain: of the last call of its size, 0 if there was none.
+// Measured (call times in us, cells / line grids): 32 views of 1800 grains at
+// 1.5, 4.4, 10 and 30 per 1000 um^3 (123, 198, 441, 1314 thousand seeds a
+// view) 477 / 607, 828 / 856, 1475 / 1357, 3245 / 2181; 4 views of 7000 at 1.5,
+// 4.4 and 10 (1.1, 3.1, 6.9 million seeds in all) 290 / 318, 557 / 557, 1043 /
+// 726. Without a call before it, by grains: 48 views of 900 1201 / 1351, 3 of
+// 27 thousand at 11 2690 / 3911. Short finite cylinders find few grains: 27
+// thousand reaching 3 um 508 / 586, 20 um 640 / 630.
+constexpr unsigned long long kFewGrains = 8192;
+constexpr uint32_t kFewViewGrains = 1024;
+constexpr unsigned long long kFewGrainsShort = 65536;
 constexpr int kShortCylinder = 1000;
-__host__ inline bool few_grains(uint32_t n_grains, int cyl_ext) {
-    return n_grains <= kFewGrains ||
-           (cyl_ext >= 0 && cyl_ext < kShortCylinder && n_grains <= kFewGrainsShort);
+constexpr double kFewSeeds = 2.5e6, kFewViewSeeds = 280e3;
+__host__ inline bool few_grains(unsigned long long n_grains, uint32_t largest_view, int cyl_ext,
+                                double seeds_per_grain) {
+    if (cyl_ext >= 0 && cyl_ext < kShortCylinder && n_grains <= kFewGrainsShort) return true;
+    if (seeds_per_grain > 0.0)
+        return seeds_per_grain * (double)n_grains <= kFewSeeds ||
+               seeds_per_grain * (double)largest_view <= kFewViewSeeds;
+    return n_grains <= kFewGrains || largest_view <= kFewViewGrains;
 }
 // Entries of the sorted-grain array past the last grain: the counting kernel
 // of those calls loads fixed groups of consecutive grains and may read (and
@@ -244,6 +254,7 @@ struct Caps {
     unsigned long long seed_cap;
     uint32_t cand_cap;
     uint32_t mem_cap;
+    bool few;                 // counts over the binned cells (see few_grains)
     int32_t wide_rounds;      // grid-wide merge rounds before the tail kernel
     int32_t nc;               // line classes the tables hold
 };

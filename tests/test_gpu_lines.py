@@ -150,3 +150,19 @@ def test_dense_call_after_sparse_ones(emt):
             ref = oracle.track_view(xyz)
             assert_candidates_equal(tr.candidates(0), ref)
             assert_view_parity(xyz, got, ref)
+
+
+@pytest.mark.parametrize("n,views", [(700, 14), (1500, 8), (9000, 1)])
+def test_path_learned_from_the_call_before(emt, n, views):
+    """Small views in a large call, and calls that are over line grids the
+    first time and over the binned cells once their seeds are known (and the
+    other way round, after a dense call of the same size)."""
+    sparse = [moderate(20 + k, side=420.0, density=1.2)[:n] for k in range(views)]
+    dense = [moderate(40 + k, side=150.0, density=9.0)[:n] for k in range(views)]
+    with emt.Tracker(device=0, flags=emt.EMT_F_CANDIDATES) as tr:
+        for batch in (sparse, sparse, dense, dense, sparse):
+            got = tr(batch)
+            for v in (0, views - 1):
+                ref = oracle.track_view(batch[v])
+                assert_candidates_equal(tr.candidates(v), ref)
+                assert_view_parity(batch[v], got[v], ref)
