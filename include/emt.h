@@ -49,8 +49,8 @@ extern "C" {
                                       emt_view_candidates                     */
 
 /* Stage indices of emt_call_stats.ms. */
-#define EMT_STAGE_STAGE 0   /* copy grains in                                */
-#define EMT_STAGE_BIN 1     /* bounding box, cell histogram, scan, scatter   */
+#define EMT_STAGE_STAGE 0   /* copies of grains BIN cannot read in place     */
+#define EMT_STAGE_BIN 1     /* grains in, bounding box, cells, scatter       */
 #define EMT_STAGE_SEED 2    /* seed pairs closer than R                      */
 #define EMT_STAGE_COUNT 3   /* grains within r of every seed line           */
 #define EMT_STAGE_MEMBERS 4 /* candidate member lists                       */

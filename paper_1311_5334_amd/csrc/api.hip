@@ -74,8 +74,10 @@ struct emt_ctx {
     // pinned host buffers
     int32_t *h_xyz = nullptr;
     size_t h_xyz_cap = 0;
+    // tables of the views, in mapped memory the device reads
     ViewGrid *h_grids = nullptr;
-    uint32_t h_views_cap = 0;
+    const int32_t **h_src = nullptr;  // each view's grains, where the device reads them
+    size_t h_grids_cap = 0, h_src_cap = 0, h_desc_cap = 0;
     // results, in mapped pinned memory written by the device
     HostOut h{};                  // host addresses
     size_t cap_out_views = 0, cap_out_cnt = 0, cap_out_tracks = 0, cap_out_grains = 0;
@@ -347,17 +349,6 @@ int ensure(emt_ctx *ctx, Caps &c) {
         ctx->held_caps = Caps{};  // nothing is held until all of them are
         for (int i = 0; i < 6; ++i)
             if ((rc = arena(ctx, *arenas[i], want[i]))) return rc;
-        if (h.n_views > ctx->h_views_cap) {
-            // matching pinned staging of the view table
-            size_t cap = 0;
-            if (ctx->h_grids) {
-                (void)hipHostFree(ctx->h_grids);
-                ctx->h_grids = nullptr;
-                ctx->h_views_cap = 0;
-            }
-            if ((rc = pinned(ctx, ctx->h_grids, cap, h.n_views))) return rc;
-            ctx->h_views_cap = h.n_views;
-        }
         ctx->held_caps = h;
         ctx->gen++;  // pointers move, within the arenas at least
         const size_t n = h.n_total, nv = h.n_views, nc = (size_t)h.nc;
@@ -437,9 +428,18 @@ int ensure(emt_ctx *ctx, Caps &c) {
     c.cand_cap = h.cand_cap;
     c.mem_cap = h.mem_cap;
     c.nc = c.few ? 1 : h.nc;
-    if (!ctx->h_desc) {
-        size_t cap = 0;
-        if ((rc = pinned(ctx, ctx->h_desc, cap, 1))) return rc;
+    {
+        // (a table that moves bumps the generation, so no captured sequence
+        // keeps its address)
+        BatchDesc *dd = const_cast<BatchDesc *>(d.in_desc);
+        ViewGrid *dg = const_cast<ViewGrid *>(d.in_grids);
+        const int32_t **ds = const_cast<const int32_t **>(d.in_src);
+        if ((rc = mapped(ctx, ctx->h_desc, dd, ctx->h_desc_cap, 1))) return rc;
+        d.in_desc = dd;
+        if ((rc = mapped(ctx, ctx->h_grids, dg, ctx->h_grids_cap, h.n_views))) return rc;
+        d.in_grids = dg;
+        if ((rc = mapped(ctx, ctx->h_src, ds, ctx->h_src_cap, h.n_views))) return rc;
+        d.in_src = ds;
     }
     {
         const size_t nv = h.n_views + 1;
@@ -564,28 +564,37 @@ int launch_sequence(emt_ctx *ctx, const Caps &c) {
     return EMT_OK;
 }
 
-// Enqueue one attempt at the whole batch on the context's stream: staging
-// copies, then the kernel sequence. Nothing waits.
+// Enqueue one attempt at the whole batch on the context's stream: the
+// views' addresses, then the kernel sequence. Nothing waits.
 int run_launch(emt_ctx *ctx, const emt_view_in *views, uint32_t nv, const Caps &c) {
     DevPtrs &d = ctx->d;
     hipStream_t s = ctx->stream;
     ctx->h_desc->n_anchor = (uint32_t)c.nc * ctx->h_desc->n_total;
     record(ctx, 0);
-    // stage the grains into the packed buffer
-    const bool dev = (ctx->cfg.flags & EMT_F_DEVICE_PTRS) != 0;
-    if (dev) {
+    // Where the first kernels read the grains: the staging buffer, or the
+    // caller's device buffers. Addresses a kernel of this device could not
+    // read (a peer's memory, the host's) or not as words are copied.
+    if (ctx->cfg.flags & EMT_F_DEVICE_PTRS) {
         for (uint32_t v = 0; v < nv; ++v) {
+            int32_t *packed = d.xyz + 3 * (size_t)ctx->h_grids[v].grain_off;
+            ctx->h_src[v] = packed;
             if (!views[v].n_grains) continue;
-            HIP_OK(hipMemcpyAsync((void *)(d.xyz + 3 * (size_t)ctx->h_grids[v].grain_off),
-                                  views[v].xyz, 12 * (size_t)views[v].n_grains,
-                                  hipMemcpyDeviceToDevice, s));
+            hipPointerAttribute_t at{};
+            const bool known = hipPointerGetAttributes(&at, views[v].xyz) == hipSuccess;
+            if (!known) (void)hipGetLastError();
+            if (known && at.type == hipMemoryTypeDevice && at.device == ctx->cfg.device &&
+                ((uintptr_t)views[v].xyz & 3u) == 0)
+                ctx->h_src[v] = views[v].xyz;
+            else
+                HIP_OK(hipMemcpyAsync(packed, views[v].xyz, 12 * (size_t)views[v].n_grains,
+                                      hipMemcpyDeviceToDevice, s));
         }
-    } else if (ctx->h_desc->n_total) {
-        HIP_OK(hipMemcpyAsync((void *)d.xyz, ctx->h_xyz, 12 * (size_t)ctx->h_desc->n_total,
-                              hipMemcpyHostToDevice, s));
+    } else {
+        void *staged = nullptr;
+        if (ctx->h_desc->n_total) HIP_OK(hipHostGetDevicePointer(&staged, ctx->h_xyz, 0));
+        for (uint32_t v = 0; v < nv; ++v)
+            ctx->h_src[v] = (const int32_t *)staged + 3 * (size_t)ctx->h_grids[v].grain_off;
     }
-    HIP_OK(hipMemcpyAsync(d.grids, ctx->h_grids, sizeof(ViewGrid) * nv, hipMemcpyHostToDevice, s));
-    HIP_OK(hipMemcpyAsync((void *)d.desc, ctx->h_desc, sizeof(BatchDesc), hipMemcpyHostToDevice, s));
     record(ctx, 1);
     int rc = launch_sequence(ctx, c);
     if (rc) {
@@ -1247,7 +1256,7 @@ void emt_destroy(emt_ctx *ctx) {
                           &ctx->mem_buf, &ctx->view_buf, &ctx->misc_buf, &ctx->stack_buf};
     for (DevArena *a : arenas)
         if (a->p) (void)hipFree(a->p);
-    void *hosts[] = {ctx->h_small, ctx->h_xyz, ctx->h_grids, ctx->h_desc, ctx->h.cnt, ctx->h.view_seeds,
+    void *hosts[] = {ctx->h_small, ctx->h_xyz, ctx->h_grids, (void *)ctx->h_src, ctx->h_desc, ctx->h.cnt, ctx->h.view_seeds,
                      ctx->h.view_cand, ctx->h.view_ntr, ctx->h.view_tr_off, ctx->h.view_err,
                      ctx->h.tracks, ctx->h.grains, ctx->h.cands};
     for (void *p : hosts)

@@ -183,7 +183,11 @@ struct HostOut {
 
 // All device buffers of one call, as raw pointers.
 struct DevPtrs {
-    const int32_t *xyz;   // packed input, N x 3
+    // the host's mapped memory: sizes, view records and where each view's grains are
+    const BatchDesc *in_desc;
+    const ViewGrid *in_grids;
+    const int32_t *const *in_src;
+    int32_t *xyz;         // packed input, N x 3
     ViewGrid *grids;
     uint32_t *view_of;    // N
     uint32_t *cell_of;    // N
@@ -240,7 +244,7 @@ struct DevPtrs {
     uint2 *lent;          // kLineEnt nc N: list words
     int32_t nc;           // line classes the tables hold (3, 12 or 48; 1: lines not classed)
     Counters *cnt;
-    const BatchDesc *desc;
+    BatchDesc *desc;
     HostOut out;
 };
 

@@ -351,46 +351,78 @@ void scan_excl(const uint32_t *in, const uint32_t *n_dev, uint32_t n_cap, uint32
 
 // ------------------------------------------------------------------- bin
 
-__global__ void __launch_bounds__(kBlock) k_zero(Counters *cnt, unsigned long long *view_seeds,
-                                                 uint32_t *view_cand, uint32_t *view_ntr,
-                                                 uint32_t *view_cursor, uint32_t *view_tail,
-                                                 uint32_t *cell_count, uint32_t *grab,
-                                                 unsigned long long *part64,
-                                                 const BatchDesc *desc) {
+// The call's sizes and view records, from the host's mapped memory, and
+// everything that starts at zero. (A copy command a table cost 3 us each.)
+__global__ void __launch_bounds__(kBlock) k_zero(DevPtrs d) {
+    __shared__ BatchDesc s_desc;  // the host's words, read once a workgroup
+    constexpr uint32_t kDescWords = sizeof(BatchDesc) / 4, kGridWords = sizeof(ViewGrid) / 4;
     const uint32_t tid = grid_tid();
-    const uint32_t n_views = desc->n_views, n_cells = desc->n_cells;
+    if (threadIdx.x < kDescWords) {
+        const uint32_t w = reinterpret_cast<const uint32_t *>(d.in_desc)[threadIdx.x];
+        reinterpret_cast<uint32_t *>(&s_desc)[threadIdx.x] = w;
+        if (blockIdx.x == 0) reinterpret_cast<uint32_t *>(d.desc)[threadIdx.x] = w;
+    }
+    __syncthreads();
+    const uint32_t n_views = s_desc.n_views, n_cells = s_desc.n_cells;
     if (tid == 0) {
         Counters z = {};
-        *cnt = z;
+        *d.cnt = z;
     }
-    for (uint32_t i = tid; i < (uint32_t)kGrabWords; i += grid_threads()) grab[i] = 0;
-    for (uint32_t i = tid; i < (uint32_t)kPartWords; i += grid_threads()) part64[i] = 0;
+    const uint32_t *in = reinterpret_cast<const uint32_t *>(d.in_grids);
+    uint32_t *grids = reinterpret_cast<uint32_t *>(d.grids);
+    for (uint32_t i = tid; i < n_views * kGridWords; i += grid_threads()) grids[i] = in[i];
+    for (uint32_t i = tid; i < (uint32_t)kGrabWords; i += grid_threads()) d.grab[i] = 0;
+    for (uint32_t i = tid; i < (uint32_t)kPartWords; i += grid_threads()) d.part64[i] = 0;
     for (uint32_t v = tid; v < n_views; v += grid_threads()) {
-        view_seeds[v] = 0;
-        view_cand[v] = 0;
-        view_ntr[v] = 0;
-        view_cursor[v] = 0;
-        view_tail[v] = 0;
+        d.view_seeds[v] = 0;
+        d.view_cand[v] = 0;
+        d.view_ntr[v] = 0;
+        d.view_cursor[v] = 0;
+        d.view_tail[v] = 0;
     }
-    for (uint32_t i = tid; i < n_cells; i += grid_threads()) cell_count[i] = 0;
+    for (uint32_t i = tid; i < n_cells; i += grid_threads()) d.cell_count[i] = 0;
 }
 
-// Bounding box of every view (grid origin) and the view index of each grain.
-__global__ void __launch_bounds__(kBlock) k_bbox(const int32_t *xyz, ViewGrid *grids,
-                                                 uint32_t *view_of, const BatchDesc *desc) {
+// The views' grains into one packed array, the bounding box of every view
+// (grid origin) and the view index of each grain. A view is read from where
+// it is, in device memory or the host's mapped memory, as consecutive words:
+// of a tile of kBlock grains a thread reads words t, kBlock + t and
+// 2 kBlock + t, which are one x, one y and one z as kBlock = 1 (mod 3). (A
+// copy command a view cost 2.3 us: 150 us for 64 views.)
+__global__ void __launch_bounds__(kBlock) k_bbox(int32_t *xyz, const int32_t *const *src,
+                                                 ViewGrid *grids, uint32_t *view_of,
+                                                 const BatchDesc *desc) {
+    static_assert(kBlock % 3 == 1, "a thread's words are of three axes");
     const uint32_t v = blockIdx.y;
     if (v >= desc->n_views) return;
     const uint32_t off = grids[v].grain_off, n = grids[v].n;
-    int lo[3] = {INT32_MAX, INT32_MAX, INT32_MAX};
-    int hi[3] = {INT32_MIN, INT32_MIN, INT32_MIN};
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        const size_t g = (size_t)off + i;
-        view_of[g] = v;
-        for (int m = 0; m < 3; ++m) {
-            const int x = xyz[3 * g + m];
-            lo[m] = min(lo[m], x);
-            hi[m] = max(hi[m], x);
+    const uint32_t first = threadIdx.x % 3u;  // axis of the thread's first word
+    int l[3] = {INT32_MAX, INT32_MAX, INT32_MAX};
+    int h[3] = {INT32_MIN, INT32_MIN, INT32_MIN};
+    if (blockIdx.x * kBlock < n) {
+        const int32_t *in = src[v];
+        int32_t *out = xyz + 3 * (size_t)off;
+        for (uint32_t t = blockIdx.x * kBlock; t < n; t += gridDim.x * kBlock) {
+            if (t + threadIdx.x < n) view_of[(size_t)off + t + threadIdx.x] = v;
+            const uint32_t end = 3u * min(n - t, (uint32_t)kBlock);
+#pragma unroll
+            for (uint32_t m = 0; m < 3; ++m) {
+                const uint32_t w = m * kBlock + threadIdx.x;
+                if (w >= end) continue;
+                const int x = in[3 * (size_t)t + w];
+                out[3 * (size_t)t + w] = x;
+                l[m] = min(l[m], x);
+                h[m] = max(h[m], x);
+            }
         }
+    }
+    // word m of a thread is of axis (first + m) mod 3
+    int lo[3], hi[3];
+#pragma unroll
+    for (uint32_t m = 0; m < 3; ++m) {
+        const uint32_t k = m + 3u - first;
+        lo[m] = k % 3u == 0 ? l[0] : k % 3u == 1 ? l[1] : l[2];
+        hi[m] = k % 3u == 0 ? h[0] : k % 3u == 1 ? h[1] : h[2];
     }
     for (int m = 0; m < 3; ++m) {
         for (int o = 32; o > 0; o >>= 1) {
@@ -1119,8 +1151,8 @@ __global__ void __launch_bounds__(kBlock) k_seeds(DevPtrs d, Caps c, Params P) {
                         rows += (uint32_t)__popcll(m);
                         return i < T ? dk_s[r] + i : p;
                     };
-                    // |g_h - g|^2 in (0, R^2): R^2 is below 2^24, so a sum below
-                    // it is exact in FP32 and one above it stays above
+                    // |g_h - g|^2 in (0, R^2): R^2 is at most 2^24, so a sum below
+                    // it is exact in FP32 and any other stays at or above it
                     auto pairs = [&](const int4 &h, float3 &e) {
                         e = make_float3((float)(h.x - g.x), (float)(h.y - g.y), (float)(h.z - g.z));
                         const float D = fmaf(e.x, e.x, fmaf(e.y, e.y, e.z * e.z));
@@ -3461,15 +3493,13 @@ size_t scan_scratch_words(uint32_t n_cap, unsigned long long n_seeds) {
 }
 
 void launch_prepare(const DevPtrs &d, const Caps &c, const Params &, hipStream_t s) {
-    k_zero<<<blocks_for(c.n_cells, 1024), kBlock, 0, s>>>(d.cnt, d.view_seeds, d.view_cand,
-                                                          d.view_ntr, d.view_cursor, d.view_tail,
-                                                          d.cell_count, d.grab, d.part64, d.desc);
+    k_zero<<<blocks_for(c.n_cells, 256), kBlock, 0, s>>>(d);
 }
 
 void launch_bin(const DevPtrs &d, const Caps &c, const Params &P, hipStream_t s) {
     const uint32_t bx = blocks_for(c.max_view_n, 64);
     dim3 grid(bx, c.n_views);
-    k_bbox<<<grid, kBlock, 0, s>>>(d.xyz, d.grids, d.view_of, d.desc);
+    k_bbox<<<grid, kBlock, 0, s>>>(d.xyz, d.in_src, d.grids, d.view_of, d.desc);
     k_grid<<<(c.n_views + 63) / 64, 64, 0, s>>>(d.grids, d.lines, d.lpool, d.lcoarse, d.nc,
                                                    d.desc, P);
     k_hist<<<grid, kBlock, 0, s>>>(d.xyz, d.grids, d.cell_of, d.rank, d.cell_count, d.desc);

@@ -489,3 +489,24 @@ def test_candidate_lists_in_a_batch(emt, oracle_mod):
         t(views[:1])
         with pytest.raises(emt.EmtError):
             t.candidates(0)
+
+
+@pytest.mark.parametrize("sizes", [(1, 0, 2), (255, 256, 257), (3, 511, 0, 4000), (70000,)])
+def test_views_read_where_they_are(sizes):
+    """Device views are read in place, at any offset of whole words and any
+    number of grains about a workgroup's 256: the same as from the host."""
+    import torch
+    from paper_1311_5334_amd import emt, synth
+    side = 300.0 if max(sizes) > 5000 else 120.0
+    xyz = synth.make_density_view(3, 16.0 if max(sizes) > 5000 else 6.0, side).xyz
+    flat = torch.from_numpy(np.concatenate([xyz, xyz])).cuda()
+    host, dev, at = [], [], 1
+    for n in sizes:
+        host.append(np.ascontiguousarray(flat[at:at + n].cpu().numpy()))
+        dev.append(flat[at:at + n])
+        assert len(host[-1]) == n
+        at += n + 1
+    with emt.Tracker(device=0) as h, emt.Tracker(device=0, flags=emt.EMT_F_DEVICE_PTRS) as t:
+        for a, b in zip(h(host), t(dev)):
+            assert a["tracks"].tobytes() == b["tracks"].tobytes()
+            assert a["grains"].tobytes() == b["grains"].tobytes()
