@@ -1453,7 +1453,8 @@ __device__ __forceinline__ void line_consts(int4 gi, int dx, int dy, int dz, int
 // Chunks are dealt to the XCDs in turn (as workgroups are), so all XCDs have
 // the same mix of long and short lines; or, from kApartSeeds on, each XCD has
 // an eighth of the list, so that its L2 holds the records and words of views
-// of its own. An XCD whose share is used up takes chunks of the others. The waves
+// of its own; candidates always (a third of their loads hit L2 when dealt in
+// turn; the members stage of 8 c5 views 2.24 -> 1.70 ms). An XCD whose share is used up takes chunks of the others. The waves
 // of a workgroup take `step` seeds at a time from its chunk: they stay close
 // together in the class's order and so share the CU's cache. range: the
 // chunk's next seed and, in the upper half, its end.
@@ -1485,10 +1486,9 @@ __device__ __forceinline__ unsigned long long chunk_range(uint32_t chunk, uint32
 // The next chunk, by one lane of the wave that holds the feed's lock. The
 // first chunk of every workgroup is its own without a counter.
 __device__ __forceinline__ unsigned long long next_chunk(uint32_t *grab, uint32_t n_items,
-                                                         uint32_t step) {
+                                                         uint32_t step, bool apart) {
     const uint32_t size = chunk_size(n_items, step), wgs = gridDim.x >> 3;
     const uint32_t n_chunks = (n_items + size - 1u) / size;
-    const bool apart = n_items >= kApartSeeds;
     const uint32_t per = chunks_apart(n_items, size);
     for (uint32_t t = 0; t < 8; ++t) {
         const uint32_t x = (blockIdx.x + t) & 7u;
@@ -1508,7 +1508,8 @@ __device__ __forceinline__ unsigned long long next_chunk(uint32_t *grab, uint32_
 // Returns false when every range is used up; n = 0 with true if another wave
 // of the workgroup is fetching a chunk. Wave-uniform.
 __device__ __forceinline__ bool take_seeds(Feed &F, uint32_t *grab, uint32_t n_items,
-                                           uint32_t step, uint32_t &next, uint32_t &n) {
+                                           uint32_t step, bool apart, uint32_t &next,
+                                           uint32_t &n) {
     uint32_t s = 0, m = 0, ok = 1;
     if (lane_id() == 0) {
         volatile Feed *V = &F;
@@ -1524,7 +1525,7 @@ __device__ __forceinline__ bool take_seeds(Feed &F, uint32_t *grab, uint32_t n_i
             // this wave fetches; the others go on with the seeds they have
             r = V->range;
             if ((uint32_t)r >= (uint32_t)(r >> 32) && !V->done) {
-                r = next_chunk(grab, n_items, step);
+                r = next_chunk(grab, n_items, step, apart);
                 if (r == 0ull) {
                     atomicExch(&F.done, 1u);
                     ok = 0;
@@ -1684,21 +1685,23 @@ k_count(DevPtrs d, Caps c, Params P) {
     unsigned long long tests = 0, hits = 0;
     // The listing instance has range counters of its own: the counting one
     // leaves its counters used up. A wave takes 64 seeds at a time, or fewer
-    // when there are too few for every wave.
+    // when there are too few for every wave (candidates: for eight times each,
+    // as they are far apart and take unlike times: 16 c3 views' members stage
+    // 247 -> 215 us).
     uint32_t *grab = d.grab + (kEmit ? 8 * 16 : 0);
-    const uint32_t step = min(64u, max(16u, n_items / (grid_threads() >> 6)));
+    const uint32_t step = min(64u, max(16u, n_items / ((grid_threads() >> 6) * (kEmit ? 8u : 1u))));
+    const bool apart = kEmit || n_items >= kApartSeeds;
     if (threadIdx.x == 0) {
         const uint32_t size = chunk_size(n_items, step), per = chunks_apart(n_items, size);
-        s_feed.range = n_items < kApartSeeds
-                           ? chunk_range(blockIdx.x, size, n_items)
-                           : chunk_range((blockIdx.x & 7u) * per + (blockIdx.x >> 3), size, n_items);
+        s_feed.range = apart ? chunk_range((blockIdx.x & 7u) * per + (blockIdx.x >> 3), size, n_items)
+                             : chunk_range(blockIdx.x, size, n_items);
         s_feed.lock = 0u;
         s_feed.done = 0u;
     }
     __syncthreads();
     for (;;) {
         uint32_t s0, n_here;
-        if (!take_seeds(s_feed, grab, n_items, step, s0, n_here)) break;
+        if (!take_seeds(s_feed, grab, n_items, step, apart, s0, n_here)) break;
         if (n_here == 0) {
             __builtin_amdgcn_s_sleep(4);  // another wave is fetching a chunk
             continue;
