@@ -3381,24 +3381,36 @@ void launch_find_grains(const uint8_t *img, const StackGeom &G, const GrainBufs 
 // thresholds in registers and walks kFilterFrames frames, loading all of
 // them before it computes, so the maps are read once per frame group and
 // raw and filtered pixels stream through once.
+//
+// With x = (raw * gain + 128) / 256 < 2^16 all that is max(0, (255 - thr) - x):
+// from x = 255 on both are 0. So a pixel is one 24-bit multiply-add, and two
+// pixels share a saturating 16-bit subtraction and a byte permutation to pack
+// them: 14 instructions for four pixels. The output goes past the caches, which
+// the next frames' pixels can use. Calls on 52 M pixels 35.8 -> 32.8 us (kernel
+// 20.1 -> 16.9; a copy of as many bytes 13.2), on 210 M pixels 95.5 -> 86.5.
 
 namespace {
 
 constexpr uint32_t kFilterFrames = 8;
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+
+// Pixels 2 h and 2 h + 1 of word r in the halves; g: their gains, room: their
+// 255 - thr.
+__device__ __forceinline__ uint32_t filter_pair(uint32_t r, int h, uint32_t g, uint32_t room) {
+    const uint32_t a = __umul24((r >> (16 * h)) & 0xffu, g & 0xffffu) + 128u;
+    const uint32_t b = __umul24((r >> (16 * h + 8)) & 0xffu, g >> 16) + 128u;
+    const uint32_t x = __builtin_amdgcn_perm(b, a, 0x06050201u);  // a >> 8 | b >> 8 << 16
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(us2, room),
+                                                                      __builtin_bit_cast(us2, x)));
+}
+
 __device__ __forceinline__ uint32_t filter_word(uint32_t r, uint32_t g01, uint32_t g23,
-                                                uint32_t t) {
-    uint32_t o = 0;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-        const uint32_t rb = (r >> (8 * b)) & 0xffu;
-        const uint32_t gb = ((b < 2 ? g01 : g23) >> (16 * (b & 1))) & 0xffffu;
-        const uint32_t tb = (t >> (8 * b)) & 0xffu;
-        const uint32_t tuned = min(255u, (__umul24(rb, gb) + 128u) >> 8);
-        const uint32_t inv = 255u - tuned;
-        o |= (inv > tb ? inv - tb : 0u) << (8 * b);
-    }
-    return o;
+                                                uint32_t room01, uint32_t room23) {
+    return __builtin_amdgcn_perm(filter_pair(r, 1, g23, room23), filter_pair(r, 0, g01, room01),
+                                 0x06040200u);
 }
 
 template <int kPix>  // pixels a thread owns in each frame: 4 or 16
@@ -3427,6 +3439,13 @@ __global__ void __launch_bounds__(kBlock) k_filter(const uint8_t *__restrict__ r
         g[1] = ga.y;
         t[0] = reinterpret_cast<const uint32_t *>(thr)[c];
     }
+    // 255 - thr in the same halves as the gains
+    uint32_t room[2 * kW];
+#pragma unroll
+    for (int k = 0; k < kW; ++k) {
+        room[2 * k] = 0x00ff00ffu - __builtin_amdgcn_perm(0u, t[k], 0x0c010c00u);
+        room[2 * k + 1] = 0x00ff00ffu - __builtin_amdgcn_perm(0u, t[k], 0x0c030c02u);
+    }
     uint32_t r[kFilterFrames][kW];
 #pragma unroll
     for (int f = 0; f < (int)kFilterFrames; ++f) {
@@ -3444,10 +3463,12 @@ __global__ void __launch_bounds__(kBlock) k_filter(const uint8_t *__restrict__ r
         if ((uint32_t)f >= nf) break;
         uint32_t o[kW];
 #pragma unroll
-        for (int k = 0; k < kW; ++k) o[k] = filter_word(r[f][k], g[2 * k], g[2 * k + 1], t[k]);
+        for (int k = 0; k < kW; ++k) 
+            o[k] = filter_word(r[f][k], g[2 * k], g[2 * k + 1], room[2 * k], room[2 * k + 1]);
         const size_t off = (size_t)(z0 + f) * plane + (size_t)c * kPix;
         if constexpr (kPix == 16)
-            *reinterpret_cast<uint4 *>(out + off) = make_uint4(o[0], o[1], o[2], o[3]);
+            __builtin_nontemporal_store(u32x4{o[0], o[1], o[2], o[3]},
+                                        reinterpret_cast<u32x4 *>(out + off));
         else
             *reinterpret_cast<uint32_t *>(out + off) = o[0];
     }

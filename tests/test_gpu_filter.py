@@ -132,3 +132,20 @@ def test_largest_stack_in_place(emt):
     tm = thr.view(-1).cpu().numpy()[plane]
     expect = filter_stack(before.reshape(1, 1, -1), gm.reshape(1, -1), tm.reshape(1, -1))
     assert np.array_equal(after, expect.reshape(-1))
+
+
+@pytest.mark.parametrize("width", [512, 516])
+def test_every_pulse_height_and_threshold(tracker, width):
+    """Every pulse height (a frame each) with every threshold (a row each) and
+    gains over the whole range, the largest and those about 1 among them, at
+    frame sizes of both vector widths."""
+    from oracle.filtering import filter_stack
+    rng = np.random.default_rng(width)
+    gains = np.concatenate([np.arange(0, 6), np.arange(250, 262), [32767, 32768, 65534, 65535]])
+    gain = rng.integers(0, 65536, (256, width)).astype(np.uint16)
+    gain[:, :len(gains)] = gains
+    thr = np.repeat(np.arange(256, dtype=np.uint8)[:, None], width, axis=1)
+    raw = np.broadcast_to(np.arange(256, dtype=np.uint8)[:, None, None], (256, 256, width))
+    raw = np.ascontiguousarray(raw)
+    raw[:, 100:, 300:] = rng.integers(0, 256, raw[:, 100:, 300:].shape)
+    assert np.array_equal(tracker.filter_stack(raw, gain, thr), filter_stack(raw, gain, thr))
