@@ -323,12 +323,14 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_one(const uint32_t *in, con
     if (threadIdx.x < 64) scan_end<kEnd>(o, n, carry);
 }
 
-// Tiles whose sums a workgroup adds up itself (see tile_offset).
-constexpr uint32_t kScanDirect = 2048;
-#ifndef EMT_SCAN_ONE
-#define EMT_SCAN_ONE 32768
-#endif
-constexpr uint32_t kScanOne = EMT_SCAN_ONE;
+// Bound by launches: a scan is one to three kernels of 3 to 5 us. Up to
+// kScanDirect tiles a workgroup adds up the sums before its own (32 KB from L2
+// at most; with 256 tiles one c2 view 735 us, with 2048 713, one c5 view 3541,
+// with more 3509; calls of eight c5 views do not care). Up to kScanOne items
+// one workgroup scans alone, 8192 at a time: one view of 900 grains 177 us, 182
+// without, and no difference between 16 and 128 thousand.
+constexpr uint32_t kScanDirect = 8192;
+constexpr uint32_t kScanOne = 32768;
 
 // o.out[i] = sum of in[0..i) for i <= n, n = min(*n_dev, n_cap) (n_cap if no
 // n_dev), then kEnd with the total. In and out start on 16-byte boundaries.
@@ -3502,8 +3504,8 @@ uint32_t blocks_for(unsigned long long n, uint32_t max_blocks) {
 #define EMT_PERSISTENT_BLOCKS 2048
 #endif
 constexpr uint32_t kPersistentBlocks = EMT_PERSISTENT_BLOCKS;  // 8 blocks of 4 waves per CU
-// the counting kernel's grid: one resident generation (4 workgroups per CU,
-// bound by its LDS and registers), so no workgroup waits for another's slot
+// the counting kernel's grid: one resident generation (two workgroups of
+// twelve waves per CU, bound by registers and LDS), so none waits for a slot
 constexpr uint32_t kCountBlocks = EMT_COUNT_BLOCKS;
 static_assert(kCountBlocks % 8 == 0, "whole workgroups per XCD");
 constexpr uint32_t kFewBlocks = 1024;  // one resident generation of k_count_few
