@@ -879,6 +879,7 @@ __device__ __forceinline__ void wave_lds_sync() {
 // for 1.3): finding an element's row by counting row ends instead of a search
 // over the row starts, cell bounds by reciprocals and the pair test in FP32
 // took 8 c5 views' passes from 2.9 to 2.45 ms, one c2 view's from 74 to 52 us.
+// The write pass puts an anchor's seeds in order in LDS first (kSeedStage).
 // The line class of direction d (up to the rounding at the bins' edges, where
 // both classes list the line's grains): its face, and its slopes' bins.
 __device__ __forceinline__ int line_face(int ax, int ay, int az) {
@@ -1038,6 +1039,11 @@ static_assert(kTiles == 2 * kOrderBlock, "two tiles a thread");
 
 constexpr uint32_t kSeedRun = 64;
 constexpr uint32_t kSeedWords = 64;  // one a lane: 4096 elements
+// Seeds of an anchor put in order in LDS before they are written: its classes'
+// seeds lie 48 bytes here and there, and written as they were found the open
+// lines of all waves outgrew the L2 (write pass of 32 c5 views 8.8 -> 6.4 ms, of
+// 8 1.75 -> 1.45; 384: 7.1, 768: 6.3 but one c2 view 105 -> 113 us in all).
+constexpr uint32_t kSeedStage = 512;
 
 template <bool kWrite>
 __global__ void __launch_bounds__(kBlock) k_seeds(DevPtrs d, Caps c, Params P) {
@@ -1048,6 +1054,10 @@ __global__ void __launch_bounds__(kBlock) k_seeds(DevPtrs d, Caps c, Params P) {
     __shared__ unsigned long long s_ends[kBlock / 64][kSeedWords];
     // per wave and class: the anchor's seeds so far, or where the next goes
     __shared__ uint32_t s_cls[kBlock / 64][kLineClasses];
+    // write pass: the anchor's seeds by class, each its partner (top bit: the
+    // anchor comes first) and where it goes
+    __shared__ uint2 s_out[kWrite ? kBlock / 64 : 1][kWrite ? kSeedStage : 1];
+    __shared__ uint32_t s_dst[kWrite ? kBlock / 64 : 1][kLineClasses];
     uint32_t *cls_s = s_cls[threadIdx.x >> 6];
     const int lane = lane_id();
     // workgroups are dealt to the XCDs in turn: each XCD takes runs of
@@ -1083,9 +1093,24 @@ __global__ void __launch_bounds__(kBlock) k_seeds(DevPtrs d, Caps c, Params P) {
         else if (lane < d.nc)
             at = tab + (uint32_t)lane * G->n + rel;
         wave_lds_sync();  // the previous anchor's are read
-        if (lane < d.nc) cls_s[lane] = kWrite ? d.seed_off[at] : 0u;
+        uint32_t n_seeds = 0;
+        if constexpr (kWrite) {
+            const uint32_t o0 = lane < d.nc ? d.seed_off[at] : 0u;
+            const uint32_t len = lane < d.nc ? d.seed_off[at + 1u] - o0 : 0u;
+            const uint32_t incl = wave_incl_scan_dpp(len);
+            n_seeds = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            if (lane < d.nc) {
+                cls_s[lane] = incl - len;
+                s_dst[threadIdx.x >> 6][lane] = o0 - (incl - len);
+            }
+        } else if (lane < d.nc) {
+            cls_s[lane] = 0u;
+        }
         wave_lds_sync();
         uint32_t mine = 0;
+        auto put = [&](bool first, uint32_t q, uint32_t dst) {
+            if (dst < c.seed_cap) d.seeds[dst] = first ? make_uint2(p, q) : make_uint2(q, p);
+        };
         if (!G->err) {
             const int nx = G->dims[0], ny = G->dims[1], nz = G->dims[2];
             const int cx = G->cell[0], cy = G->cell[1], cz = G->cell[2];
@@ -1160,14 +1185,20 @@ __global__ void __launch_bounds__(kBlock) k_seeds(DevPtrs d, Caps c, Params P) {
                         const float D = fmaf(e.x, e.x, fmaf(e.y, e.y, e.z * e.z));
                         return D > 0.0f && D < R2;
                     };
+                    // stored lower input index first: that grain is the
+                    // seed's i (the fit's origin and key order)
                     auto take = [&](bool ok, const int4 &h, const float3 &e, uint32_t q) {
                         if (!ok) return;
-                        const uint32_t slot =
-                            atomicAdd(&cls_s[nsub ? line_class(e.x, e.y, e.z, nsub) : 0], 1u);
-                        // stored lower input index first: that grain is the
-                        // seed's i (the fit's origin and key order)
-                        if (kWrite && slot < c.seed_cap)
-                            d.seeds[slot] = h.w > g.w ? make_uint2(p, q) : make_uint2(q, p);
+                        const int cls = nsub ? line_class(e.x, e.y, e.z, nsub) : 0;
+                        const uint32_t slot = atomicAdd(&cls_s[cls], 1u);
+                        if constexpr (kWrite) {
+                            const uint32_t dst = s_dst[threadIdx.x >> 6][cls] + slot;
+                            const uint32_t first = h.w > g.w ? 0x80000000u : 0u;
+                            if (slot < kSeedStage)
+                                s_out[threadIdx.x >> 6][slot] = make_uint2(q | first, dst);
+                            else
+                                put(first != 0u, q, dst);
+                        }
                     };
                     // two elements a lane per trip: their row searches and grain
                     // loads are in flight together
@@ -1188,8 +1219,14 @@ __global__ void __launch_bounds__(kBlock) k_seeds(DevPtrs d, Caps c, Params P) {
                 }
             }
         }
-        if (!kWrite) {
-            wave_lds_sync();
+        wave_lds_sync();
+        if constexpr (kWrite) {
+            const uint32_t m = min(n_seeds, kSeedStage);
+            for (uint32_t i = (uint32_t)lane; i < m; i += 64) {
+                const uint2 o = s_out[threadIdx.x >> 6][i];
+                put((int)o.x < 0, o.x & 0x7fffffffu, o.y);
+            }
+        } else {
             if (lane < d.nc) d.seed_cnt[at] = cls_s[lane];
             wave_total += wave_sum(mine);
         }

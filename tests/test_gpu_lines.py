@@ -166,3 +166,10 @@ def test_path_learned_from_the_call_before(emt, n, views):
                 ref = oracle.track_view(batch[v])
                 assert_candidates_equal(tr.candidates(v), ref)
                 assert_view_parity(batch[v], got[v], ref)
+
+
+@pytest.mark.parametrize("n,side", [(3000, 45.0), (9000, 70.0)])
+def test_more_seeds_than_an_anchor_stages(emt, n, side):
+    """Anchors with more seeds than are put in order before they are written."""
+    xyz = synth.make_box_view(5, n, (side, side, side)).xyz
+    check(emt, [xyz], dict(n_min=5), min_grains=5)
