@@ -369,7 +369,7 @@ def measure_grains(emt, torch, stacks, calls: int = 20) -> dict:
                          "traffic": grain_traffic_for_current_kernel(),
                          "note": "stack bytes read once and 12 bytes written per grain "
                                  "(algorithmic), over the device time of the whole "
-                                 "recognition: clear, find and place kernels"}}
+                                 "recognition: find and place kernels"}}
 
 
 def measure_filter(emt, torch, raws, calls: int = 20) -> dict:
