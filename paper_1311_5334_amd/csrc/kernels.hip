@@ -369,6 +369,7 @@ __global__ void __launch_bounds__(kBlock) k_zero(DevPtrs d) {
     if (tid == 0) {
         Counters z = {};
         *d.cnt = z;
+        d.view_tr_off[0] = 0;
     }
     const uint32_t *in = reinterpret_cast<const uint32_t *>(d.in_grids);
     uint32_t *grids = reinterpret_cast<uint32_t *>(d.grids);
@@ -2627,12 +2628,14 @@ __global__ void __launch_bounds__(kTailBlock) k_merge_tail(DevPtrs d, Params P, 
     const uint32_t group = threadIdx.x / kMergeGroup;
     constexpr uint32_t kTailGroups = kTailBlock / kMergeGroup;
     const uint32_t c0 = view_first_cand(d, view, d.cnt->n_seeds_ok);
+    // (the only view of a call has the undecided list as it is)
+    const int at = gridDim.x > 1 ? last_round + 2 : last_round + 1;
     if (threadIdx.x == 0) {
-        s_n[0] = d.view_tail[view];
+        s_n[0] = gridDim.x > 1 ? d.view_tail[view] : d.undecided[last_round];
         s_n[1] = 0;
     }
     __syncthreads();
-    uint32_t *list[2] = {merge_list(d, last_round + 2) + c0, merge_list(d, last_round + 3) + c0};
+    uint32_t *list[2] = {merge_list(d, at) + c0, merge_list(d, at + 1) + c0};
     int cur = 0;
     uint32_t rounds = 0;
     const uint32_t limit = s_n[0] + 2;
@@ -2806,18 +2809,42 @@ __global__ void __launch_bounds__(kBlock) k_group(DevPtrs d, unsigned long long 
 
 // Track order within a view = key order (the order of acceptance in the
 // one-by-one reading); rank by counting smaller keys of the same view.
+// A workgroup's tracks are of one view as a rule: it takes the view's keys to
+// LDS, 256 at a time, which all its lanes then read together. (Bound by the
+// chain of key loads before: with two launches less for a single view, one c2
+// view 732 -> 721 us, one c5 view 3494 -> 3429.)
 __global__ void __launch_bounds__(kBlock) k_rank(DevPtrs d, const unsigned long long *gkey) {
+    __shared__ unsigned long long s_key[kBlock];
+    constexpr uint32_t kStep = 16;
     const uint32_t na = d.cnt->n_acc;
-    for (uint32_t s = grid_tid(); s < na; s += grid_threads()) {
-        const uint32_t ci = d.grouped[s];
+    for (uint32_t base = blockIdx.x * kBlock; base < na; base += grid_threads()) {  // uniform
+        const uint32_t s = base + threadIdx.x;
+        const bool ok = s < na;
+        const uint32_t ci = d.grouped[ok ? s : base];
         const uint32_t v = d.cand[ci].v;
         const uint32_t b = d.view_tr_off[v], e = b + d.view_ntr[v];
-        const unsigned long long key = gkey[s];
+        const unsigned long long key = gkey[ok ? s : base];
         uint32_t rank = 0;
+        const uint32_t v0 = d.cand[d.grouped[base]].v;
+        if (v0 == d.cand[d.grouped[min(base + kBlock, na) - 1u]].v) {
+            const uint32_t b0 = d.view_tr_off[v0], e0 = b0 + d.view_ntr[v0];
+            for (uint32_t t = b0; t < e0; t += kBlock) {
+                __syncthreads();  // the keys before have been read
+                s_key[threadIdx.x] = t + threadIdx.x < e0 ? gkey[t + threadIdx.x] : ~0ull;
+                __syncthreads();
+                const uint32_t m = min((uint32_t)kBlock, e0 - t);
+                for (uint32_t i = 0; i < m; i += kStep)
+#pragma unroll
+                    for (uint32_t k = 0; k < kStep; ++k) rank += s_key[i + k] < key ? 1u : 0u;
+            }
+        } else {
 #pragma unroll 8
-        for (uint32_t t = b; t < e; ++t) rank += gkey[t] < key ? 1u : 0u;
-        d.track_cand[b + rank] = ci;
-        d.tg_n[b + rank] = d.mcount[ci];
+            for (uint32_t t = b; t < e; ++t) rank += gkey[t] < key ? 1u : 0u;
+        }
+        if (ok) {
+            d.track_cand[b + rank] = ci;
+            d.tg_n[b + rank] = d.mcount[ci];
+        }
     }
 }
 
@@ -3656,7 +3683,7 @@ void launch_merge(const DevPtrs &d, const Caps &c, const Params &P, hipStream_t 
         k_round<1><<<nb, kBlock, 0, s>>>(d, P, round);
         if (round >= 1 && nb > 1024) nb = nb / 2 > 1024 ? nb / 2 : 1024;
     }
-    k_tail_split<<<64, kBlock, 0, s>>>(d, wide - 1);
+    if (c.n_views > 1) k_tail_split<<<64, kBlock, 0, s>>>(d, wide - 1);
     k_merge_tail<<<c.n_views, kTailBlock, 0, s>>>(d, P, wide - 1);
 }
 
@@ -3670,7 +3697,7 @@ void launch_copy_out(const DevPtrs &d, const Caps &c, const Params &, hipStream_
 void launch_fit(const DevPtrs &d, const Caps &c, const Params &P, hipStream_t s) {
     const uint32_t nb = blocks_for(c.cand_cap, kPersistentBlocks);
     k_collect<<<nb, kBlock, 0, s>>>(d, c);
-    k_view_offsets<<<1, kBlock, 0, s>>>(d);
+    if (c.n_views > 1) k_view_offsets<<<1, kBlock, 0, s>>>(d);  // one view's is 0
     // keys of the grouped tracks reuse the owner array (merge is over)
     unsigned long long *gkey = d.owner;
     k_group<<<nb, kBlock, 0, s>>>(d, gkey);
