@@ -210,7 +210,7 @@ int pinned(emt_ctx *ctx, T *&p, size_t &cap, size_t n) {
     }
     size_t want = std::max<size_t>(n, 1024);
     want += want / 4;
-    if (hipHostMalloc((void **)&p, want * sizeof(T), hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc((void **)&p, want * sizeof(T), hipHostMallocCoherent) != hipSuccess) {
         (void)hipGetLastError();
         return EMT_ENOMEM;
     }
@@ -218,9 +218,11 @@ int pinned(emt_ctx *ctx, T *&p, size_t &cap, size_t n) {
     return EMT_OK;
 }
 
-// Mapped pinned host memory the device writes results into.
+// Mapped pinned host memory the device writes results into, or (coherent, so
+// that no cache keeps the last call's words) reads the call's tables from.
 template <class T>
-int mapped(emt_ctx *ctx, T *&host, T *&dev, size_t &cap, size_t n) {
+int mapped(emt_ctx *ctx, T *&host, T *&dev, size_t &cap, size_t n,
+           unsigned flags = hipHostMallocMapped) {
     if (cap >= n && host) return EMT_OK;
     if (host) {
         if (hipHostFree(host) != hipSuccess) {
@@ -233,7 +235,7 @@ int mapped(emt_ctx *ctx, T *&host, T *&dev, size_t &cap, size_t n) {
     }
     ctx->gen++;
     size_t want = std::max<size_t>(n, 64);
-    if (hipHostMalloc((void **)&host, want * sizeof(T), hipHostMallocMapped) != hipSuccess) {
+    if (hipHostMalloc((void **)&host, want * sizeof(T), flags) != hipSuccess) {
         (void)hipGetLastError();
         host = nullptr;
         return EMT_ENOMEM;
@@ -434,11 +436,12 @@ int ensure(emt_ctx *ctx, Caps &c) {
         BatchDesc *dd = const_cast<BatchDesc *>(d.in_desc);
         ViewGrid *dg = const_cast<ViewGrid *>(d.in_grids);
         const int32_t **ds = const_cast<const int32_t **>(d.in_src);
-        if ((rc = mapped(ctx, ctx->h_desc, dd, ctx->h_desc_cap, 1))) return rc;
+        constexpr unsigned kRead = hipHostMallocMapped | hipHostMallocCoherent;
+        if ((rc = mapped(ctx, ctx->h_desc, dd, ctx->h_desc_cap, 1, kRead))) return rc;
         d.in_desc = dd;
-        if ((rc = mapped(ctx, ctx->h_grids, dg, ctx->h_grids_cap, h.n_views))) return rc;
+        if ((rc = mapped(ctx, ctx->h_grids, dg, ctx->h_grids_cap, h.n_views, kRead))) return rc;
         d.in_grids = dg;
-        if ((rc = mapped(ctx, ctx->h_src, ds, ctx->h_src_cap, h.n_views))) return rc;
+        if ((rc = mapped(ctx, ctx->h_src, ds, ctx->h_src_cap, h.n_views, kRead))) return rc;
         d.in_src = ds;
     }
     {

@@ -510,3 +510,19 @@ def test_views_read_where_they_are(sizes):
         for a, b in zip(h(host), t(dev)):
             assert a["tracks"].tobytes() == b["tracks"].tobytes()
             assert a["grains"].tobytes() == b["grains"].tobytes()
+
+
+def test_new_grains_in_the_same_staging_memory():
+    """Host views are read from staging memory that later calls write over:
+    calls of the same size on other grains see the new ones, as a tracker that
+    has seen nothing else does."""
+    from paper_1311_5334_amd import emt
+    views = [synth.make_density_view(60 + k, 4.0, 150.0).xyz[:4000] for k in range(6)]
+    with emt.Tracker(device=0) as t:
+        for k in (0, 1, 2, 3, 4, 5, 1, 0):
+            got = t([views[k], views[(k + 1) % 6]])
+            with emt.Tracker(device=0) as fresh:
+                want = fresh([views[k], views[(k + 1) % 6]])
+            for a, b in zip(got, want):
+                assert a["tracks"].tobytes() == b["tracks"].tobytes()
+                assert a["grains"].tobytes() == b["grains"].tobytes()
