@@ -17,6 +17,7 @@
 
 #include <algorithm>
 
+#include "deal.h"
 #include "emt_dev.h"
 
 namespace emt {
@@ -1494,52 +1495,30 @@ __device__ __forceinline__ void line_consts(int4 gi, int dx, int dy, int dz, int
 // the same mix of long and short lines; or, from kApartSeeds on, each XCD has
 // an eighth of the list, so that its L2 holds the records and words of views
 // of its own; candidates always (a third of their loads hit L2 when dealt in
-// turn; the members stage of 8 c5 views 2.24 -> 1.70 ms). An XCD whose share is used up takes chunks of the others. The waves
-// of a workgroup take `step` seeds at a time from its chunk: they stay close
-// together in the class's order and so share the CU's cache. range: the
-// chunk's next seed and, in the upper half, its end.
+// turn; the members stage of 8 c5 views 2.24 -> 1.70 ms). Which chunk is whose
+// is deal.h's: every chunk has one taker, as two listing the same candidate
+// would write its members at once. A workgroup whose XCD has no chunk left
+// takes those of the others. The waves of a workgroup take `step` seeds at a
+// time from its chunk: they stay close together in the class's order and so
+// share the CU's cache. range: the chunk's next seed and, in the upper half,
+// its end.
 struct Feed {
     unsigned long long range;
     uint32_t lock, done;
+    Deal deal;  // (here rather than in registers, which the walk needs)
 };
 
-// Seeds of a chunk: one a workgroup where its waves take no more than two
-// times each, else about eight, at least a time for every wave and at most
-// kChunkSeeds.
-__device__ __forceinline__ uint32_t chunk_size(uint32_t n_items, uint32_t step) {
-    const uint32_t share = n_items / gridDim.x + 1u, round = step * kCountWaves;
-    if (share <= 2u * round) return (share + step - 1u) / step * step;
-    return min(kChunkSeeds, max(round, share / 8u / step * step));
-}
-
-// Chunks of an XCD's eighth, where the XCDs work apart.
-__device__ __forceinline__ uint32_t chunks_apart(uint32_t n_items, uint32_t size) {
-    return ((n_items + size - 1u) / size + 7u) / 8u;
-}
-
-__device__ __forceinline__ unsigned long long chunk_range(uint32_t chunk, uint32_t size,
-                                                          uint32_t n_items) {
-    const unsigned long long lo = min((unsigned long long)n_items, (unsigned long long)chunk * size);
-    return (min((unsigned long long)n_items, lo + size) << 32) | lo;
-}
-
-// The next chunk, by one lane of the wave that holds the feed's lock. The
-// first chunk of every workgroup is its own without a counter.
-__device__ __forceinline__ unsigned long long next_chunk(uint32_t *grab, uint32_t n_items,
-                                                         uint32_t step, bool apart) {
-    const uint32_t size = chunk_size(n_items, step), wgs = gridDim.x >> 3;
-    const uint32_t n_chunks = (n_items + size - 1u) / size;
-    const uint32_t per = chunks_apart(n_items, size);
-    for (uint32_t t = 0; t < 8; ++t) {
-        const uint32_t x = (blockIdx.x + t) & 7u;
-        // chunks x, x + 8, .. or x per .. (x + 1) per - 1
-        const uint32_t mine = apart ? min(n_chunks, (x + 1u) * per) - min(n_chunks, x * per)
-                                    : (n_chunks + 7u - x) / 8u;
+// The next chunk, by one lane of the wave that holds the feed's lock; 0 if
+// there is none left.
+__device__ __forceinline__ unsigned long long next_chunk(uint32_t *grab, const Deal &D) {
+    const uint32_t wgs = gridDim.x / kXcds;
+    for (uint32_t t = 0; t < kXcds; ++t) {
+        const uint32_t x = (blockIdx.x + t) % kXcds, mine = deal_share(D, x);
         uint32_t *ctr = grab + 16 * x;
         const uint32_t cur = __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (wgs + cur >= mine) continue;
-        const uint32_t at = wgs + atomicAdd(ctr, 1u);
-        if (at < mine) return chunk_range(apart ? x * per + at : at * 8u + x, size, n_items);
+        const unsigned long long r = deal_range(D, x, wgs + atomicAdd(ctr, 1u));
+        if (r) return r;
     }
     return 0ull;
 }
@@ -1547,8 +1526,7 @@ __device__ __forceinline__ unsigned long long next_chunk(uint32_t *grab, uint32_
 // Takes the next seeds [next, next + n) for the calling wave, n <= step.
 // Returns false when every range is used up; n = 0 with true if another wave
 // of the workgroup is fetching a chunk. Wave-uniform.
-__device__ __forceinline__ bool take_seeds(Feed &F, uint32_t *grab, uint32_t n_items,
-                                           uint32_t step, bool apart, uint32_t &next,
+__device__ __forceinline__ bool take_seeds(Feed &F, uint32_t *grab, uint32_t step, uint32_t &next,
                                            uint32_t &n) {
     uint32_t s = 0, m = 0, ok = 1;
     if (lane_id() == 0) {
@@ -1565,7 +1543,7 @@ __device__ __forceinline__ bool take_seeds(Feed &F, uint32_t *grab, uint32_t n_i
             // this wave fetches; the others go on with the seeds they have
             r = V->range;
             if ((uint32_t)r >= (uint32_t)(r >> 32) && !V->done) {
-                r = next_chunk(grab, n_items, step, apart);
+                r = next_chunk(grab, F.deal);
                 if (r == 0ull) {
                     atomicExch(&F.done, 1u);
                     ok = 0;
@@ -1730,18 +1708,17 @@ k_count(DevPtrs d, Caps c, Params P) {
     // 247 -> 215 us).
     uint32_t *grab = d.grab + (kEmit ? 8 * 16 : 0);
     const uint32_t step = min(64u, max(16u, n_items / ((grid_threads() >> 6) * (kEmit ? 8u : 1u))));
-    const bool apart = kEmit || n_items >= kApartSeeds;
     if (threadIdx.x == 0) {
-        const uint32_t size = chunk_size(n_items, step), per = chunks_apart(n_items, size);
-        s_feed.range = apart ? chunk_range((blockIdx.x & 7u) * per + (blockIdx.x >> 3), size, n_items)
-                             : chunk_range(blockIdx.x, size, n_items);
+        s_feed.deal = make_deal(n_items, step, kCountWaves, gridDim.x, kChunkSeeds,
+                                kEmit || n_items >= kApartSeeds);
+        s_feed.range = deal_range(s_feed.deal, blockIdx.x % kXcds, blockIdx.x / kXcds);
         s_feed.lock = 0u;
         s_feed.done = 0u;
     }
     __syncthreads();
     for (;;) {
         uint32_t s0, n_here;
-        if (!take_seeds(s_feed, grab, n_items, step, apart, s0, n_here)) break;
+        if (!take_seeds(s_feed, grab, step, s0, n_here)) break;
         if (n_here == 0) {
             __builtin_amdgcn_s_sleep(4);  // another wave is fetching a chunk
             continue;
@@ -3571,7 +3548,7 @@ constexpr uint32_t kPersistentBlocks = EMT_PERSISTENT_BLOCKS;  // 8 blocks of 4 
 // the counting kernel's grid: one resident generation (two workgroups of
 // twelve waves per CU, bound by registers and LDS), so none waits for a slot
 constexpr uint32_t kCountBlocks = EMT_COUNT_BLOCKS;
-static_assert(kCountBlocks % 8 == 0, "whole workgroups per XCD");
+static_assert(kCountBlocks % kXcds == 0, "whole workgroups per XCD");
 constexpr uint32_t kFewBlocks = 1024;  // one resident generation of k_count_few
 
 }  // namespace
