@@ -265,9 +265,11 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_parts(uint32_t *part, uint3
 }
 
 // Offset of this workgroup's tile: the sum of the earlier tiles, or what
-// k_scan_parts left. Called by the whole workgroup.
+// k_scan_parts left. Called by the whole workgroup. Nothing is before the first
+// tile, and where there are no items at all nobody has written its place.
 template <bool kDirect>
 __device__ __forceinline__ uint32_t tile_offset(const uint32_t *part) {
+    if (blockIdx.x == 0) return 0u;
     if constexpr (!kDirect) return part[blockIdx.x];
     uint32_t sum = 0;
 #pragma unroll 4
@@ -1695,9 +1697,9 @@ k_count(DevPtrs d, Caps c, Params P) {
     CountLds<kFinite, kEmit> &Q = sQ[threadIdx.x >> 6];
     uint32_t n_items = d.cnt->n_seeds_ok;
     if constexpr (kEmit) {
-        // nothing to list when the entries overflow their buffer (the call
-        // is re-run)
-        const bool skip = d.cnt->err || d.cnt->n_members > c.mem_cap;
+        // nothing to list when the seeds or the entries overflow their buffer
+        // (the call is re-run)
+        const bool skip = n_items == 0u || d.cnt->err || d.cnt->n_members > c.mem_cap;
         n_items = skip ? 0u : min(d.cnt->n_cand, c.cand_cap);
     }
     unsigned long long tests = 0, hits = 0;
@@ -2076,9 +2078,9 @@ k_count_few(DevPtrs d, Caps c, Params P) {
     FewLds<kFinite, kEmit> &Q = sQ[threadIdx.x >> 6];
     uint32_t n_items = d.cnt->n_seeds_ok;
     if constexpr (kEmit) {
-        // nothing to list when the entries overflow their buffer (the call
-        // is re-run)
-        const bool skip = d.cnt->err || d.cnt->n_members > c.mem_cap;
+        // nothing to list when the seeds or the entries overflow their buffer
+        // (the call is re-run)
+        const bool skip = n_items == 0u || d.cnt->err || d.cnt->n_members > c.mem_cap;
         n_items = skip ? 0u : min(d.cnt->n_cand, c.cand_cap);
     }
     if (lane < kPieceWords) Q.mask[lane] = 0ull;
