@@ -8,6 +8,7 @@
 #include <stdint.h>
 
 #include "emt.h"
+#include "line_grid.h"
 #include "tile_table.h"
 
 namespace emt {
@@ -63,29 +64,8 @@ struct ViewGrid {
     int32_t pad[3];
 };
 
-// Per view: the grids the counting kernel walks, written by k_grid (see
-// there). Face a holds sub * sub classes of ns[a] planes each.
-constexpr int kSubMax = 4;                           // most slope bins an axis
-constexpr int kLineClasses = 3 * kSubMax * kSubMax;  // most line classes a view has
-constexpr int kLineEdge = 2048;                // cells of a plane along u or v
 constexpr int kLineKeys = 4096;                // places a face's grains are sorted into
 constexpr uint32_t kLineBand = 256;            // records a workgroup fills at a time
-constexpr int kPackSpan = 2048;                // units a packed word's u and v reach either way
-// Records a view may use per grain, when tables hold nc classes.
-__host__ __device__ inline uint32_t line_recs(int nc) { return (uint32_t)(nc + nc / 4); }
-constexpr uint32_t kLineEnt = 12;              // list words of a class per grain
-struct LineGrid {
-    int32_t sub;           // slope bins an axis
-    int32_t c, w;          // cell edge and slab thickness (units)
-    int32_t reach;         // cells start this far below the bounding box
-    float ic;              // 1 / c
-    int32_t packed;        // list words hold the grains' coordinates
-    int32_t ns[3];         // slabs along the face's axis
-    int32_t nu[3], nv[3];  // cells of a plane
-    int32_t bu[3];         // records (8 x 4 cells each) in a row of records
-    uint32_t plane[3];     // records from one plane to the next
-    uint32_t face_off[3];  // the face's first record, from the view's first
-};
 
 // Sizes of the batch in flight, in device memory so that one captured launch
 // sequence serves every batch within its capacities.

@@ -458,76 +458,6 @@ __global__ void __launch_bounds__(kBlock) k_bbox(int32_t *xyz, const int32_t *co
     }
 }
 
-// ------------------------------------------------------------ line grids
-//
-// The grids the counting kernel walks. A line's class is the axis a of its
-// largest |d| (its face) and which of sub x sub bins its slopes d_u / d_a,
-// d_v / d_a in [-1, 1] fall in (u, v the other two axes). For each class the
-// view is cut along a into slabs of w units, and each slab's middle plane
-// into c x c cells. A line of the class crosses the middle plane of slab k at
-// one point, so it looks at one cell a slab; that cell lists every grain of
-// the slab that any line of the class through the cell can have within r.
-// A grain h units off the middle plane is met by lines that cross the plane
-// within delta |h| + r sqrt(1 + s^2) of (u - s0 h, v - t0 h), (s0, t0) the
-// bin's middle slopes, delta = 1 / sub the bin's half width and s the
-// largest |slope| of the bin: the grain is listed in every cell of that
-// rectangle, widened by kMargin units against the FP32 rounding of the
-// crossing point (below 1 unit for coordinates up to 2^18, and 1.5 units for
-// its fixed-point steps). The exact test decides the grains.
-__device__ __forceinline__ int line_u(int a) { return a == 0 ? 1 : 0; }
-__device__ __forceinline__ int line_v(int a) { return a == 2 ? 1 : 2; }
-
-// Largest distance, in a plane's u or v, between a grain and the cells that
-// list it.
-__device__ __forceinline__ int line_reach(int w, int r) {
-    return w / 2 + 1 + (int)(1.42f * (float)r) + (int)kMargin + 1;
-}
-
-// c and w grow until the view's records fit their share; c is at least
-// `spread` times the half side of a grain's largest rectangle.
-__device__ LineGrid line_grid(const ViewGrid &G, const long long *span, const int *tab, int nc, int r,
-                              double spread) {
-    LineGrid L = {};
-    int sub = tab[2];
-    while (3 * sub * sub > nc) --sub;
-    L.sub = sub;
-    if (G.n == 0) return L;
-    const unsigned long long cap = (unsigned long long)line_recs(nc) * G.n;
-    double c = tab[0], w = tab[1];
-    for (;;) {
-        L.w = (int)w;
-        const double half = 0.5 * w / sub + 1.4143 * r + kMargin;
-        c = fmax(c, half * spread + 2.0);
-        if (c > 0.75 * w) {  // keeps the crossing points' fixed point exact enough
-            w *= 1.19;
-            continue;
-        }
-        L.c = (int)c;
-        L.reach = line_reach(L.w, r);
-        unsigned long long off = 0;
-        bool ok = true;
-        for (int a = 0; a < 3; ++a) {
-            const long long ns = span[a] / L.w + 1;
-            const long long nu = (span[line_u(a)] + 2 * L.reach) / L.c + 1;
-            const long long nv = (span[line_v(a)] + 2 * L.reach) / L.c + 1;
-            ok = ok && ns <= 65535 && nu <= kLineEdge && nv <= kLineEdge;
-            L.ns[a] = (int)ns;
-            L.nu[a] = (int)nu;
-            L.nv[a] = (int)nv;
-            L.bu[a] = (int)((nu + 7) / 8);
-            L.plane[a] = (uint32_t)(L.bu[a] * ((nv + 3) / 4));
-            L.face_off[a] = (uint32_t)off;
-            off += (unsigned long long)L.plane[a] * ns * (sub * sub);
-        }
-        if (ok && off <= cap) break;
-        c *= 1.19;
-        w *= 1.19;
-    }
-    L.ic = 1.0f / (float)L.c;
-    L.packed = 8 * L.c < kPackSpan && 2 * L.reach < kPackSpan ? 1 : 0;
-    return L;
-}
-
 // Cell geometry per view: the requested edges, doubled until the grid has at
 // most cell_cap cells. A view whose span exceeds the limit is marked: its
 // grains still go through the binning (into one cell, so every later view
@@ -578,8 +508,8 @@ __global__ void k_grid(ViewGrid *grids, LineGrid *lines, uint32_t *pool, uint32_
     if (nc == 1) return;  // the lines are not classed
     // the grid used unless its lists overflow their share, and a coarser one
     // whose lists cannot: a rectangle covers at most 2 x 2 cells, six words
-    lines[2 * v] = line_grid(G, span, P.line_tab[b], nc, P.r, 2.0 / 3.0);
-    lines[2 * v + 1] = line_grid(G, span, P.line_tab[b], nc, P.r, 2.0);
+    lines[2 * v] = line_grid(G.n, span, P.line_tab[b], nc, P.r, 2.0 / 3.0);
+    lines[2 * v + 1] = line_grid(G.n, span, P.line_tab[b], nc, P.r, 2.0);
     for (int i = 0; i < 2 * nc; ++i) pool[(size_t)v * 2 * nc + i] = 0u;
     coarse[v] = 0u;
 }
@@ -994,7 +924,7 @@ __global__ void __launch_bounds__(kOrderBlock) k_line_order(DevPtrs d) {
     if (v >= d.desc->n_views) return;
     const ViewGrid *G = &d.grids[v];
     const uint32_t n = G->n, goff = G->grain_off;
-    if (G->err || n == 0) return;
+    if (G->err || n < 2) return;
     if (blockIdx.x < 3) {
         line_sort(d, *G, v, (int)blockIdx.x, s_tile, s_wave);
         return;
@@ -1241,7 +1171,7 @@ __global__ void __launch_bounds__(kBlock) k_seeds(DevPtrs d, Caps c, Params P) {
 // ------------------------------------------------------- count / members
 
 
-// Line grids: filling the cells.
+// Line grids (line_grid.h): filling the cells.
 //
 // A record covers a block of 8 x 4 cells of a plane: x has a bit for every
 // cell that lists grains, cell 0's the topmost, y + 1 is the list word of its
@@ -1292,7 +1222,7 @@ __global__ void __launch_bounds__(kLineBlock) k_line_fill(DevPtrs d, Params P) {
     if (v >= d.desc->n_views) return;
     if (kPass == 1 && !line_coarse(d, v)) return;
     const ViewGrid G = d.grids[v];
-    if (G.err || G.n == 0) return;
+    if (G.err || G.n < 2) return;
     const LineGrid L = d.lines[2 * v + kPass];
     const int nsub = L.sub, cls = (int)blockIdx.y;
     if (cls >= 3 * nsub * nsub) return;
@@ -1306,8 +1236,7 @@ __global__ void __launch_bounds__(kLineBlock) k_line_fill(DevPtrs d, Params P) {
     const float su0 = (float)(2 * (sub / nsub) + 1) * delta - 1.0f;
     const float sv0 = (float)(2 * (sub % nsub) + 1) * delta - 1.0f;
     const float su = fabsf(su0) + delta, sv = fabsf(sv0) + delta;
-    const float hu0 = (float)P.r * sqrtf(1.0f + su * su) + kMargin;
-    const float hv0 = (float)P.r * sqrtf(1.0f + sv * sv) + kMargin;
+    const float hu0 = line_half(P.r, su, L.margin), hv0 = line_half(P.r, sv, L.margin);
     const int ns = L.ns[a], nu = L.nu[a], nv = L.nv[a], bu = L.bu[a];
     const uint32_t plane = L.plane[a];
     uint2 *recs = d.lrec + (size_t)line_recs(d.nc) * G.grain_off + L.face_off[a] +
@@ -1341,13 +1270,9 @@ __global__ void __launch_bounds__(kLineBlock) k_line_fill(DevPtrs d, Params P) {
                 const float4 g = sorted[i];
                 if (g.x < fa0 || g.x >= fa1) continue;
                 const float h = g.x - mid;
-                const float hu = fmaf(delta, fabsf(h), hu0), hv = fmaf(delta, fabsf(h), hv0);
-                const float cu = g.y + (float)L.reach - su0 * h;
-                const float cv = g.z + (float)L.reach - sv0 * h;
-                const int ju0 = max(0, (int)((cu - hu) * L.ic));
-                const int ju1 = min(nu - 1, (int)((cu + hu) * L.ic));
-                const int jv0 = max(b0, (int)((cv - hv) * L.ic));
-                const int jv1 = min(b1 - 1, (int)((cv + hv) * L.ic));
+                int ju0, ju1, jv0, jv1;
+                line_cells(L, g.y, h, su0, delta, hu0, 0, nu - 1, ju0, ju1);
+                line_cells(L, g.z, h, sv0, delta, hv0, b0, b1 - 1, jv0, jv1);
                 for (int jv = jv0; jv <= jv1; ++jv) {
                     const int row = ((jv >> 2) - r0) * bu, in = (jv & 3) << 3;
                     for (int ju = ju0; ju <= ju1; ++ju)
@@ -1447,12 +1372,6 @@ constexpr uint32_t kQueue = 64u * (kFetch + 1);
 // queued: position in the class's pool, lane of the line, and whether the
 // word is one of a cell's list (else a cell's first); the cell, u << 16 | v
 constexpr uint32_t kItemLane = 24, kItemList = 1u << 31;
-// fractional bits of a crossing point: its cell is the upper half word, and a
-// slab's step, rounded to half of the last bit, is off by at most 1.5 units at
-// the far side of the largest view (2^18 / w slabs; line_grid keeps c <= 3/4 w)
-constexpr int kLineBits = 16;
-constexpr float kLineOne = (float)(1 << kLineBits);
-static_assert((unsigned long long)kLineEdge << kLineBits <= 1ull << 31, "crossing points");
 static_assert((unsigned long long)kLineEnt * kNMax <= 1ull << kItemLane, "pool positions");
 
 template <bool kFinite, bool kEmit>
@@ -1772,14 +1691,12 @@ k_count(DevPtrs d, Caps c, Params P) {
             const int nu = a == 0 ? L->nu[0] : a == 1 ? L->nu[1] : L->nu[2];
             const int nv = a == 0 ? L->nv[0] : a == 1 ? L->nv[1] : L->nv[2];
             const int ns = a == 0 ? L->ns[0] : a == 1 ? L->ns[1] : L->ns[2];
-            const float w = (float)L->w, ic = L->ic;
-            const float off0 = 0.5f * w - ga;
-            const float u0 = fmaf(su, off0, (float)(ti.y + L->reach)) * ic, du = su * w * ic;
-            const float v0 = fmaf(sv, off0, (float)(ti.z + L->reach)) * ic, dv = sv * w * ic;
-            iu = (int)(u0 * kLineOne);
-            idu = (int)rintf(du * kLineOne);
-            iv = (int)(v0 * kLineOne);
-            idv = (int)rintf(dv * kLineOne);
+            const LineCross cu = line_cross(*L, su, ga, ti.y), cv = line_cross(*L, sv, ga, ti.z);
+            const float u0 = cu.x0, du = cu.step, v0 = cv.x0, dv = cv.step;
+            iu = cu.fixed0();
+            idu = cu.fixed_step();
+            iv = cv.fixed0();
+            idv = cv.fixed_step();
             // slabs whose plane the line crosses inside the cells: a bound a
             // slab too wide costs a look, not a result
             klo = 0.0f;
@@ -1800,7 +1717,7 @@ k_count(DevPtrs d, Caps c, Params P) {
                 // grains of the cylinder lie within cyl_ext along the line
                 // and r across it of the seed's stretch of axis a
                 const float reach = (float)P.cyl_ext + (float)P.r + kMargin;
-                const float iw = __builtin_amdgcn_rcpf(w);
+                const float iw = __builtin_amdgcn_rcpf((float)L->w);
                 klo = fmaxf(klo, (fminf(ga, ga + da) - reach) * iw - 1.0f);
                 khi = fminf(khi, (fmaxf(ga, ga + da) + reach) * iw + 1.0f);
             }

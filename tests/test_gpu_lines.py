@@ -173,3 +173,57 @@ def test_more_seeds_than_an_anchor_stages(emt, n, side):
     """Anchors with more seeds than are put in order before they are written."""
     xyz = synth.make_box_view(5, n, (side, side, side)).xyz
     check(emt, [xyz], dict(n_min=5), min_grains=5)
+
+
+def steep_lattice():
+    """The plane lattice of test_lists_that_overflow_their_share."""
+    k = np.arange(95) * 300 + 4
+    x, y = np.meshgrid(k, k)
+    xyz = np.stack([x.ravel(), y.ravel(), np.zeros(x.size)], axis=1).astype(np.int32)
+    return np.concatenate([np.zeros((1, 3), np.int32), xyz])
+
+
+@pytest.mark.parametrize("view", ["lattice", "plane"])
+def test_lists_that_overflow_at_every_budget(emt, view):
+    """Every number of line classes that a budget leaves, with lists that
+    overflow their share: the least budget that is accepted, and a fine and a
+    coarse row of larger ones."""
+    if view == "lattice":
+        xyz, cfg = steep_lattice(), dict(seed_dist=500, min_grains=60)
+        ref = oracle.track_view(xyz, R=500, n_min=60)
+        d = np.diff(xyz[np.asarray(ref.cand)[:, :2].astype(int)], axis=1)[:, 0]
+        assert (d[:, 0] == d[:, 1]).sum() > 1000  # lines of the steepest slope
+    else:
+        xyz, cfg = with_lines(14, 9000, (120000.0, 120000.0, 0.0), 40, 30), {}
+        ref = oracle.track_view(xyz)
+    assert len(ref.cand) > 0
+
+    def run(kb):
+        try:
+            with emt.Tracker(device=0, flags=emt.EMT_F_CANDIDATES, hbm_budget=kb << 10, **cfg) as tr:
+                got = tr([xyz])[0]
+                assert_candidates_equal(tr.candidates(0), ref)
+                assert_view_parity(xyz, got, ref)
+                assert tr.stats()["retries"] == 0
+        except emt.EmtError as e:
+            assert e.rc == emt.EMT_ENOMEM
+            return False
+        return True
+
+    refused, accepted = 1 << 10, 400 << 10
+    assert run(accepted) and not run(refused)
+    while accepted - refused > 32:
+        mid = (accepted + refused) // 2
+        if run(mid):
+            accepted = mid
+        else:
+            refused = mid
+    for more in [64 * k for k in range(24)] + [4 << 10, 12 << 10, 24 << 10, 48 << 10]:
+        assert run(accepted + more)
+
+
+@pytest.mark.parametrize("line", ["200,800,1", "1,1,1", "10,262144,4", "262144,1,2"])
+def test_line_grids_of_any_shape(emt, monkeypatch, line):
+    monkeypatch.setenv("EMT_LINE", line)
+    check(emt, [steep_lattice()], {"R": 700, "n_min": 40}, seed_dist=700, min_grains=40)
+    check(emt, [moderate(21), moderate(15)[:2], moderate(15)[:1]])
