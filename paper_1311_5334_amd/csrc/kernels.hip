@@ -19,6 +19,7 @@
 
 #include "deal.h"
 #include "emt_dev.h"
+#include "seed_rows.h"
 
 namespace emt {
 
@@ -1053,7 +1054,7 @@ __global__ void __launch_bounds__(kBlock) k_seeds(DevPtrs d, Caps c, Params P) {
             // the box's first and last cells, to the cell or one too wide
             // (reciprocals; coordinates are below 2^18, and the pair test and
             // the least position decide what a wider box adds)
-            constexpr float kLess = 1.0f - 0x1p-20f, kMore = 1.0f + 0x1p-20f;
+            constexpr float kLess = 1.0f - 0x1p-20f, kMore = kRowsMore;
             const float icx = __builtin_amdgcn_rcpf((float)cx), icy = __builtin_amdgcn_rcpf((float)cy),
                         icz = __builtin_amdgcn_rcpf((float)cz);
             const int x0 = (int)((float)max(0, g.x - R1) * (icx * kLess));
@@ -1083,7 +1084,7 @@ __global__ void __launch_bounds__(kBlock) k_seeds(DevPtrs d, Caps c, Params P) {
                 const int rr = rb + lane;
                 uint32_t k0 = 0, k1 = 0;
                 if (rr < nrows) {
-                    const int rz = (int)((float)rr * inyr);  // exact: rr < 2^18
+                    const int rz = row_layer(rr, nyr, inyr);
                     const int y = y0 + rr - rz * nyr, z = z0 + rz;
                     const uint32_t row = off + (uint32_t)((z * ny + y) * nx);
                     k0 = max(d.cell_start[row + x0], p + 1);
