@@ -567,6 +567,35 @@ int launch_sequence(emt_ctx *ctx, const Caps &c) {
     return EMT_OK;
 }
 
+// An allocation of this device's memory, while a call looks at its views.
+struct DevRange {
+    uintptr_t lo = 0, hi = 0;
+    bool holds(const void *p, size_t bytes) const {
+        const uintptr_t a = (uintptr_t)p;
+        return a >= lo && a < hi && bytes <= hi - a;
+    }
+};
+
+// Whether a kernel of this device can read all of [p, p + bytes): one
+// allocation of its memory holds them. seen: the last allocation found, as a
+// call's views are often of one.
+bool readable(int device, const void *p, size_t bytes, DevRange &seen) {
+    if (seen.holds(p, bytes)) return true;
+    hipPointerAttribute_t at{};
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess ||
+        hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (at.type != hipMemoryTypeDevice || at.device != device) return false;
+    const DevRange found{(uintptr_t)base, (uintptr_t)base + size};
+    if (!found.holds(p, bytes)) return false;
+    seen = found;
+    return true;
+}
+
 // Enqueue one attempt at the whole batch on the context's stream: the
 // views' addresses, then the kernel sequence. Nothing waits.
 int run_launch(emt_ctx *ctx, const emt_view_in *views, uint32_t nv, const Caps &c) {
@@ -575,22 +604,21 @@ int run_launch(emt_ctx *ctx, const emt_view_in *views, uint32_t nv, const Caps &
     ctx->h_desc->n_anchor = (uint32_t)c.nc * ctx->h_desc->n_total;
     record(ctx, 0);
     // Where the first kernels read the grains: the staging buffer, or the
-    // caller's device buffers. Addresses a kernel of this device could not
-    // read (a peer's memory, the host's) or not as words are copied.
+    // caller's device buffers. Those that a kernel of this device could not
+    // read (a peer's memory, the host's), not as words, or not to their end,
+    // are copied: the copy refuses a buffer shorter than its view.
     if (ctx->cfg.flags & EMT_F_DEVICE_PTRS) {
+        DevRange seen;
         for (uint32_t v = 0; v < nv; ++v) {
             int32_t *packed = d.xyz + 3 * (size_t)ctx->h_grids[v].grain_off;
             ctx->h_src[v] = packed;
-            if (!views[v].n_grains) continue;
-            hipPointerAttribute_t at{};
-            const bool known = hipPointerGetAttributes(&at, views[v].xyz) == hipSuccess;
-            if (!known) (void)hipGetLastError();
-            if (known && at.type == hipMemoryTypeDevice && at.device == ctx->cfg.device &&
-                ((uintptr_t)views[v].xyz & 3u) == 0)
+            const size_t bytes = 12 * (size_t)views[v].n_grains;
+            if (!bytes) continue;
+            if (((uintptr_t)views[v].xyz & 3u) == 0 &&
+                readable(ctx->cfg.device, views[v].xyz, bytes, seen))
                 ctx->h_src[v] = views[v].xyz;
             else
-                HIP_OK(hipMemcpyAsync(packed, views[v].xyz, 12 * (size_t)views[v].n_grains,
-                                      hipMemcpyDeviceToDevice, s));
+                HIP_OK(hipMemcpyAsync(packed, views[v].xyz, bytes, hipMemcpyDeviceToDevice, s));
         }
     } else {
         void *staged = nullptr;

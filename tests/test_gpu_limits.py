@@ -60,3 +60,27 @@ def test_seeds_that_overflow_a_large_buffer(emt):
         a, b = min(int(i), j), max(int(i), j)
         n = on_line(g, a, b)
         assert listed.get((a, b), 0) == (n if n >= 16 else 0)
+
+
+def test_device_view_longer_than_its_allocation(emt):
+    """A device view that runs past the end of its allocation is refused, as a
+    copy of it is. (By 12 bytes here, in the allocation's own page, so that they
+    are there whatever reads them.)"""
+    import ctypes as C
+    lib = emt.load()  # (the HIP runtime it is linked to finds hipMalloc)
+    lib.hipMalloc.argtypes, lib.hipFree.argtypes = [C.POINTER(C.c_void_p), C.c_size_t], [C.c_void_p]
+    p = C.c_void_p()
+    assert lib.hipMalloc(C.byref(p), 1200) == 0
+
+    def call(ctx, n):
+        v = (emt.EmtViewIn * 1)()
+        v[0].xyz = p.value
+        v[0].n_grains = n
+        return lib.emt_track_views(ctx, v, 1, (emt.EmtViewOut * 1)())
+
+    lib.hipMemset.argtypes = [C.c_void_p, C.c_int, C.c_size_t]
+    assert lib.hipMemset(p, 0, 1200) == 0
+    with emt.Tracker(device=0, flags=emt.EMT_F_DEVICE_PTRS) as tr:
+        assert call(tr.ctx, 100) == emt.EMT_OK
+        assert call(tr.ctx, 101) == emt.EMT_EDEVICE
+    assert lib.hipFree(p) == 0
