@@ -63,6 +63,7 @@ struct emt_ctx {
     DevPtrs d{};
     // capacities the buffers currently hold (nc: line classes)
     Caps held_caps{};
+    int nc_most = kLineClasses;  // fewer once the device had no room for those
     // capacities learned from earlier calls
     double seeds_per_grain = 256.0, cand_per_grain = 8.0, mem_per_cand = 24.0;
     // grid-wide merge rounds for the next call of each size class (the
@@ -263,10 +264,12 @@ size_t seed_bytes(size_t n) {
 // records and list words: the seed, counting and listing kernels are done with
 // them by then.
 size_t order_bytes(size_t n_total, size_t n_views, int nc) {
+    if (nc == 1) return bytes_of<uint32_t>(n_total);
     return bytes_of<float4>(3 * n_total) + bytes_of<uint32_t>(3 * (n_total + n_views)) +
            2 * bytes_of<uint32_t>(nc * n_total);
 }
 size_t line_bytes(size_t n_total, int nc) {
+    if (nc == 1) return 0;
     return bytes_of<uint2>(line_recs(nc) * n_total) +
            bytes_of<uint2>((size_t)kLineEnt * nc * n_total);
 }
@@ -280,8 +283,9 @@ size_t mem_bytes(size_t n, size_t n_total, int nc) {
            std::max(2 * bytes_of<uint32_t>(n) + bytes_of<long long>(n), line_bytes(n_total, nc));
 }
 size_t view_bytes(size_t n, int nc) {
-    return bytes_of<ViewGrid>(n) + bytes_of<LineGrid>(2 * n) + bytes_of<uint32_t>(2 * nc * n) +
-           bytes_of<uint32_t>(n) + bytes_of<unsigned long long>(n) +
+    const size_t lines = nc == 1 ? 0 : bytes_of<LineGrid>(2 * n) + bytes_of<uint32_t>(2 * nc * n) +
+                                           bytes_of<uint32_t>(n);
+    return bytes_of<ViewGrid>(n) + lines + bytes_of<unsigned long long>(n) +
            5 * bytes_of<uint32_t>(n + 1) + bytes_of<Counters>(1) +
            bytes_of<uint32_t>((size_t)max_merge_rounds()) + bytes_of<uint32_t>(kGrabWords) +
            bytes_of<unsigned long long>(kPartWords) + bytes_of<BatchDesc>(1);
@@ -296,6 +300,7 @@ size_t scan_bytes(const Caps &c, int nc) {
 }
 
 // Sizes the arenas are carved for.
+constexpr int kArenas = 6;
 struct ArenaSizes {
     size_t grain, seed, cand, mem, cell, view;
     size_t total() const { return grain + seed + cand + mem + cell + view; }
@@ -309,9 +314,10 @@ ArenaSizes arena_sizes(const Caps &c, int nc) {
 // Line classes the tables hold: more slope bins make the lines of a class
 // more alike, so fewer grains are tested, and take more memory (118 bytes per
 // grain and class, part of it shared). The most that the budget has room for
-// beside everything else; three classes need no more memory than the buffers
-// they share.
-constexpr int kLineChoices[] = {kLineClasses, 12, 3};
+// beside everything else. Three classes need no more memory than the buffers
+// they share, but in the largest calls; one: no tables, the binned cells are
+// walked.
+constexpr int kLineChoices[] = {kLineClasses, 12, 3, 1};
 
 bool same_caps(const Caps &a, const Caps &b) {
     return a.n_total == b.n_total && a.n_views == b.n_views && a.n_cells == b.n_cells &&
@@ -320,39 +326,84 @@ bool same_caps(const Caps &a, const Caps &b) {
            a.wide_rounds == b.wide_rounds && a.nc == b.nc;
 }
 
+// Give the buffers of tracking calls back; ensure makes them again.
+void release_arenas(emt_ctx *ctx) {
+    DevArena *const arenas[kArenas] = {&ctx->grain_buf, &ctx->seed_buf, &ctx->cand_buf,
+                                       &ctx->mem_buf, &ctx->cell_buf, &ctx->view_buf};
+    ctx->held_caps = Caps{};
+    for (DevArena *a : arenas) {
+        if (a->p) (void)hipFree(a->p);
+        ctx->held -= a->bytes;
+        *a = DevArena{};
+    }
+}
+
+// Make the arenas hold the capacities in h with the most line classes that the
+// budget has room for and the device gives, and set h.nc. An arena only grows,
+// unless there is room only without what the others hold too much (the tables
+// of more classes than there is room for now): then all are made anew.
+int make_arenas(emt_ctx *ctx, Caps &h) {
+    DevArena *const arenas[kArenas] = {&ctx->grain_buf, &ctx->seed_buf, &ctx->cand_buf,
+                                       &ctx->mem_buf, &ctx->cell_buf, &ctx->view_buf};
+    bool refused = false;
+    for (int nc : kLineChoices) {
+        if (nc > ctx->nc_most) continue;
+        h.nc = nc;
+        if (same_caps(h, ctx->held_caps)) return EMT_OK;
+        const ArenaSizes z = arena_sizes(h, nc);
+        const size_t want[kArenas] = {z.grain, z.seed, z.cand, z.mem, z.cell, z.view};
+        size_t others = ctx->held, grown = 0;
+        for (int i = 0; i < kArenas; ++i) {
+            others -= arenas[i]->bytes;
+            grown += std::max(want[i], arenas[i]->bytes);
+        }
+        if (others + z.total() > ctx->budget) continue;
+        if (others + grown > ctx->budget) release_arenas(ctx);
+        ctx->held_caps = Caps{};  // nothing is held until all of them are
+        int rc = EMT_OK;
+        for (int i = 0; i < kArenas && rc == EMT_OK; ++i) rc = arena(ctx, *arenas[i], want[i]);
+        if (rc == EMT_OK) {
+            ctx->held_caps = h;
+            ctx->gen++;  // pointers move, within the arenas at least
+            if (refused) ctx->nc_most = nc;
+            return EMT_OK;
+        }
+        if (rc != EMT_ENOMEM) return rc;
+        release_arenas(ctx);  // the device has less than the budget
+        refused = true;
+    }
+    return EMT_ENOMEM;
+}
+
 // Make every buffer hold the capacities in c, carve the pointer table, and
-// raise c to what the buffers hold. The arenas only grow, so c is first raised
-// to the capacities held; they are carved again whenever one changes.
+// raise c to what the buffers hold: c raised to the capacities held before, or
+// c alone if there is no room for both. Nothing of an earlier call is in flight.
 int ensure(emt_ctx *ctx, Caps &c) {
     int rc;
     DevPtrs &d = ctx->d;
-    Caps h = ctx->held_caps;
-    h.n_total = std::max({h.n_total, c.n_total, 1024u});
-    h.seed_cap = std::max(h.seed_cap, c.seed_cap);
-    h.cand_cap = std::max(h.cand_cap, c.cand_cap);
-    h.mem_cap = std::max(h.mem_cap, c.mem_cap);
-    h.n_cells = std::max({h.n_cells, c.n_cells, 1u << 16});
-    h.n_views = std::max({h.n_views, c.n_views, 64u});
-    DevArena *const arenas[] = {&ctx->grain_buf, &ctx->seed_buf, &ctx->cand_buf,
-                                &ctx->mem_buf, &ctx->cell_buf, &ctx->view_buf};
-    size_t others = ctx->held;
-    for (const DevArena *a : arenas) others -= a->bytes;
-    ArenaSizes z{};
-    for (int nc : kLineChoices) {
-        h.nc = nc;
-        z = arena_sizes(h, nc);
-        const size_t want[] = {z.grain, z.seed, z.cand, z.mem, z.cell, z.view};
-        size_t sum = others;
-        for (int i = 0; i < 6; ++i) sum += std::max(want[i], arenas[i]->bytes);
-        if (sum <= ctx->budget) break;
-    }
-    if (!same_caps(h, ctx->held_caps)) {
-        const size_t want[] = {z.grain, z.seed, z.cand, z.mem, z.cell, z.view};
-        ctx->held_caps = Caps{};  // nothing is held until all of them are
-        for (int i = 0; i < 6; ++i)
-            if ((rc = arena(ctx, *arenas[i], want[i]))) return rc;
-        ctx->held_caps = h;
-        ctx->gen++;  // pointers move, within the arenas at least
+    Caps h{};
+    h.n_total = std::max(c.n_total, 1024u);
+    h.seed_cap = c.seed_cap;
+    h.cand_cap = c.cand_cap;
+    h.mem_cap = c.mem_cap;
+    h.n_cells = std::max(c.n_cells, 1u << 16);
+    h.n_views = std::max(c.n_views, 64u);
+    Caps both = h;
+    const Caps &held = ctx->held_caps;
+    both.n_total = std::max(both.n_total, held.n_total);
+    both.seed_cap = std::max(both.seed_cap, held.seed_cap);
+    both.cand_cap = std::max(both.cand_cap, held.cand_cap);
+    both.mem_cap = std::max(both.mem_cap, held.mem_cap);
+    both.n_cells = std::max(both.n_cells, held.n_cells);
+    both.n_views = std::max(both.n_views, held.n_views);
+    const unsigned gen = ctx->gen;
+    rc = make_arenas(ctx, both);
+    if (rc == EMT_ENOMEM)
+        rc = make_arenas(ctx, h);
+    else
+        h = both;
+    if (rc) return rc;
+    if (ctx->gen != gen) {
         const size_t n = h.n_total, nv = h.n_views, nc = (size_t)h.nc;
         d.nc = h.nc;
         char *p = (char *)ctx->grain_buf.p;
@@ -387,10 +438,12 @@ int ensure(emt_ctx *ctx, Caps &c) {
         d.track_cand = carve<uint32_t>(p, k);
         d.status = carve<uint8_t>(p, k);
         char *q = p;
-        d.lsg = carve<float4>(q, 3 * n);
-        d.lkey = carve<uint32_t>(q, 3 * (n + nv));
         d.seed_cnt = carve<uint32_t>(q, nc * n);
-        d.lrank = carve<uint32_t>(q, nc * n);
+        if (nc > 1) {
+            d.lsg = carve<float4>(q, 3 * n);
+            d.lkey = carve<uint32_t>(q, 3 * (n + nv));
+            d.lrank = carve<uint32_t>(q, nc * n);
+        }
         d.tracks = carve<emt_track>(p, k);
 
         const size_t m = h.mem_cap;
@@ -398,8 +451,10 @@ int ensure(emt_ctx *ctx, Caps &c) {
         d.members = carve<uint32_t>(p, m);
         d.taken = carve<uint8_t>(p, m);
         q = p;
-        d.lrec = carve<uint2>(q, line_recs(h.nc) * n);
-        d.lent = carve<uint2>(q, (size_t)kLineEnt * nc * n);
+        if (nc > 1) {
+            d.lrec = carve<uint2>(q, line_recs(h.nc) * n);
+            d.lent = carve<uint2>(q, (size_t)kLineEnt * nc * n);
+        }
         d.tord = carve<uint32_t>(p, m);
         d.out_grains = carve<uint32_t>(p, m);
         d.tvals = carve<long long>(p, m);
@@ -411,9 +466,11 @@ int ensure(emt_ctx *ctx, Caps &c) {
 
         p = (char *)ctx->view_buf.p;
         d.grids = carve<ViewGrid>(p, nv);
-        d.lines = carve<LineGrid>(p, 2 * nv);
-        d.lpool = carve<uint32_t>(p, 2 * nc * nv);
-        d.lcoarse = carve<uint32_t>(p, nv);
+        if (nc > 1) {
+            d.lines = carve<LineGrid>(p, 2 * nv);
+            d.lpool = carve<uint32_t>(p, 2 * nc * nv);
+            d.lcoarse = carve<uint32_t>(p, nv);
+        }
         d.view_seeds = carve<unsigned long long>(p, nv);
         d.view_cand = carve<uint32_t>(p, nv + 1);
         d.view_ntr = carve<uint32_t>(p, nv + 1);
@@ -890,8 +947,7 @@ int emt_create(const emt_config *cfg, emt_ctx **out) {
 
 namespace emt {
 
-// Device bytes a context needs for a batch of these sizes (its arenas only
-// grow, so this bounds what the batch adds to the context's holdings).
+// Device bytes a context cannot do without for a batch of these sizes.
 size_t batch_bytes(const emt_ctx *ctx, unsigned long long n_total, uint32_t n_views,
                    uint32_t max_n) {
     Caps c{};
@@ -899,8 +955,9 @@ size_t batch_bytes(const emt_ctx *ctx, unsigned long long n_total, uint32_t n_vi
     c.n_total = std::max(c.n_total, 1024u);
     c.n_cells = std::max(c.n_cells, 1u << 16);
     c.n_views = std::max(c.n_views, 64u);
-    // with the fewest line classes: more only use what the budget has left
-    return arena_sizes(c, 3).total();
+    // without line classes: they only use what the budget has left, and a
+    // context that holds more gives it back (make_arenas)
+    return arena_sizes(c, 1).total();
 }
 
 size_t held_bytes(const emt_ctx *ctx) { return ctx->held; }
@@ -1097,6 +1154,15 @@ int emt_track_views(emt_ctx *ctx, const emt_view_in *views, uint32_t n_views, em
 }
 
 
+// The buffers of a stack call, in the place of the tracking ones if there is no
+// room beside them.
+static int stack_arena(emt_ctx *ctx, size_t bytes) {
+    const int rc = arena(ctx, ctx->stack_buf, bytes);
+    if (rc != EMT_ENOMEM || bytes > ctx->budget) return rc;
+    release_arenas(ctx);
+    return arena(ctx, ctx->stack_buf, bytes);
+}
+
 // static_buf: null for emt_find_grains (buffers from the context's arena,
 // grown as needed); the device address of scratch for the no-allocation
 // variant (device pointers only, no allocation, stacks up to its size).
@@ -1149,7 +1215,7 @@ static int find_grains_impl(emt_ctx *ctx, const uint8_t *stack, const emt_stack_
                              bytes_of<uint32_t>(ng) + bytes_of<uint16_t>(grain_stage_slots(G)) +
                              (dev ? 0 : bytes_of<int32_t>(3 * (size_t)max_out));
         int rc;
-        if ((rc = arena(ctx, ctx->stack_buf, bytes))) return rc;
+        if ((rc = stack_arena(ctx, bytes))) return rc;
         p = (char *)ctx->stack_buf.p;
     }
     const uint8_t *img = stack;
@@ -1208,7 +1274,7 @@ static int filter_impl(emt_ctx *ctx, const uint8_t *raw, const emt_stack_geom *g
     if (!dev) {
         const size_t bytes = 2 * bytes_of<uint8_t>((size_t)npix) + bytes_of<uint16_t>(plane) +
                              bytes_of<uint8_t>(plane);
-        if ((rc = arena(ctx, ctx->stack_buf, bytes))) return rc;
+        if ((rc = stack_arena(ctx, bytes))) return rc;
         char *p = (char *)ctx->stack_buf.p;
         uint8_t *h_raw = carve<uint8_t>(p, (size_t)npix);
         d_out = carve<uint8_t>(p, (size_t)npix);

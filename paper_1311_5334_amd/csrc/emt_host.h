@@ -20,7 +20,8 @@ bool views_ready(emt_ctx *ctx);
 // Wait for the batch, re-run it if a capacity overflowed, and fill out[]
 // exactly as emt_track_views does.
 int finish_views(emt_ctx *ctx, emt_view_out *out);
-// Device bytes the context's buffers need for a batch of these sizes.
+// Device bytes the context's buffers cannot do without for a batch of these
+// sizes.
 size_t batch_bytes(const emt_ctx *ctx, unsigned long long n_total, uint32_t n_views,
                    uint32_t max_n);
 // Device bytes the context holds now.

@@ -3474,9 +3474,11 @@ constexpr uint32_t kFewBlocks = 1024;  // one resident generation of k_count_few
 }  // namespace
 
 // tile sums of a scan of n_cap items, or of the mask words of n_seeds seeds
+// (launch_candidates)
 size_t scan_scratch_words(uint32_t n_cap, unsigned long long n_seeds) {
-    return std::max({(size_t)n_cap / kScanTile, (size_t)(n_seeds / 32 / (4 * kBlock)),
-                     (size_t)kScanDirect}) + 2;
+    const size_t words = n_seeds / 32 + 1, tiles = words / kBlock + 1;
+    return std::max((size_t)n_cap / kScanTile + 1,
+                    tiles <= kScanDirect ? tiles : words / (4 * kBlock) + 1) + 1;
 }
 
 void launch_prepare(const DevPtrs &d, const Caps &c, const Params &, hipStream_t s) {

@@ -84,3 +84,109 @@ def test_device_view_longer_than_its_allocation(emt):
         assert call(tr.ctx, 100) == emt.EMT_OK
         assert call(tr.ctx, 101) == emt.EMT_EDEVICE
     assert lib.hipFree(p) == 0
+
+
+def dense_view():
+    """More seeds than a first call's buffers hold (256 for each of 2^14 grains)."""
+    return synth.make_box_view(33, 12000, (88.0, 88.0, 88.0)).xyz
+
+
+def tracked(emt, views, kb):
+    """The last call's candidates and tracks of calls of one view each on one
+    context, or None if any is refused for its budget."""
+    try:
+        with emt.Tracker(device=0, flags=emt.EMT_F_CANDIDATES, min_grains=12, hbm_budget=kb << 10) as tr:
+            for xyz in views:
+                got = tr([xyz])[0]
+            cand = tr.candidates(0)
+            return got, cand[np.lexsort((cand[:, 1], cand[:, 0]))], tr.stats()["retries"]
+    except emt.EmtError as e:
+        assert e.rc == emt.EMT_ENOMEM
+        return None
+
+
+def test_every_larger_budget_is_accepted_too(emt):
+    """A call that is run again with larger buffers, at budgets from one that is
+    accepted on: whatever the first attempt took, the second has its room, and
+    so has a dense call after a sparse one on the same context."""
+    dense, sparse = dense_view(), synth.make_density_view(20, 4.4, 205.0).xyz
+    assert 8192 < len(sparse) <= 1 << 14
+    whole, cand, retries = tracked(emt, [dense], 1 << 20)
+    assert retries == 1 and len(cand) > 0
+    least = None
+    for kb in range(100 << 10, 400 << 10, 4 << 10):
+        got = tracked(emt, [dense], kb)
+        if got is None:
+            assert least is None, f"{kb} KB are refused, {least} KB were not"
+            continue
+        least = least or kb
+        for again in (got, tracked(emt, [sparse, dense], kb), tracked(emt, [dense, sparse, dense], kb)):
+            assert again is not None, f"{kb} KB"
+            assert np.array_equal(again[1], cand)
+            assert again[0]["tracks"].tobytes() == whole["tracks"].tobytes()
+            assert np.array_equal(again[0]["grains"], whole["grains"])
+    assert least is not None
+
+
+def test_served_views_after_others_of_their_budget(emt):
+    """A server whose pipeline has served sparse views serves dense ones at every
+    budget at which a new one does."""
+    dense, sparse = dense_view(), synth.make_density_view(20, 4.4, 205.0).xyz
+
+    def serve(views, kb):
+        out = []
+        with emt.Server(n_pipes=1, max_batch_views=1, device=0, min_grains=12, hbm_budget=kb << 10) as s:
+            for xyz in views:
+                s.submit(xyz)
+                got = s.poll(wait_ms=60000)
+                assert len(got) == 1
+                out.append(got[0])
+        return out
+
+    served = 0
+    for kb in range(130 << 10, 300 << 10, 5 << 10):
+        if serve([dense], kb)[0]["status"] != emt.EMT_OK:
+            continue
+        served += 1
+        out = serve([sparse, dense, sparse, dense], kb)
+        assert [o["status"] for o in out] == [emt.EMT_OK] * 4, kb
+        assert out[1]["n_candidates"] == out[3]["n_candidates"] > 0
+    assert served > 3
+
+
+def test_recognition_beside_tracking_in_one_budget(emt):
+    """Host stacks and views on one context: the stack's buffers have room
+    beside the tracking ones, or in their place, in whatever order they come."""
+    sparse = synth.make_density_view(20, 4.4, 205.0).xyz
+    rng = np.random.default_rng(3)
+    stack = np.where(rng.random((16, 1024, 1024)) < 1e-3, 200, 0).astype(np.uint8)
+    with emt.Tracker(device=0) as tr:
+        grains, tracks = tr.find_grains(stack, 100), tr([sparse])[0]["tracks"].tobytes()
+    with emt.Tracker(device=0, hbm_budget=175 << 20) as tr:
+        for _ in range(2):
+            assert tr([sparse])[0]["tracks"].tobytes() == tracks
+            assert np.array_equal(tr.find_grains(stack, 100), grains)
+
+
+def test_device_with_less_memory_than_the_budget(emt):
+    """The line classes' tables are an offer: where the device has no room for
+    the most of them (2.75 GB in all here, 2.2 with a quarter) there are fewer."""
+    import torch
+    xyz = synth.make_density_view(22, 4.4, 820.0).xyz
+    assert 1 << 17 < len(xyz) <= 1 << 18
+    with emt.Tracker(device=0) as tr:
+        whole = tr([xyz])[0]
+        assert tr.stats()["retries"] == 0
+    torch.cuda.empty_cache()
+    keep = []
+    try:
+        while (free := torch.cuda.mem_get_info()[0] - (2450 << 20)) > 4 << 20:
+            keep.append(torch.empty(min(free, 16 << 30) >> 21 << 21, dtype=torch.uint8, device="cuda:0"))
+        with emt.Tracker(device=0, hbm_budget=8 << 30) as tr:
+            for _ in range(2):
+                got = tr([xyz])[0]
+                assert got["tracks"].tobytes() == whole["tracks"].tobytes()
+                assert np.array_equal(got["grains"], whole["grains"])
+    finally:
+        keep.clear()
+        torch.cuda.empty_cache()
