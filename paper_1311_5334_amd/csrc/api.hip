@@ -699,7 +699,7 @@ int run_check(emt_ctx *ctx, const Caps &c, bool *overflow) {
     *overflow = false;
     HIP_OK(hipEventSynchronize(ctx->done));
     const Counters &h = *ctx->h.cnt;
-    const Needs need{h.seeds64, h.members64, h.n_cand};
+    const Needs need{h.seeds64, h.members64, h.n_cand, true};
     const CapSizes have{c.seed_cap, c.cand_cap, c.mem_cap};
     if (!fits(need, have)) {
         *overflow = true;
@@ -1035,7 +1035,7 @@ int finish_views(emt_ctx *ctx, emt_view_out *out) {
         if (attempt + 1 >= kMaxAttempts) return EMT_EOVERFLOW;
         ++retries;
         const Counters h = *ctx->h.cnt;
-        const Needs need{h.seeds64, h.members64, h.n_cand};
+        const Needs need{h.seeds64, h.members64, h.n_cand, true};
         CapSizes next{c.seed_cap, c.cand_cap, c.mem_cap};
         Ratios ratios{ctx->seeds_per_grain, ctx->cand_per_grain, ctx->mem_per_cand};
         if (!plan_retry(need, c.n_total, next, ratios)) return EMT_EOVERFLOW;

@@ -23,6 +23,9 @@ struct Needs {
     unsigned long long seeds;
     unsigned long long members;
     uint32_t cand;
+    // members are those of all candidates, also of those that found no room,
+    // and not of the first ones only (which the order of the seeds chooses)
+    bool all_members = false;
 };
 
 // Capacities of an attempt.
@@ -61,17 +64,19 @@ inline bool plan_retry(const Needs &h, uint32_t n_total, CapSizes &c, Ratios &r)
         r.seeds_per_grain = std::max(r.seeds_per_grain, 1.125 * (double)h.seeds / grains);
     }
     const bool cand_over = h.cand > c.cand_cap;
-    const uint32_t cand_seen = cand_over ? c.cand_cap : h.cand;  // candidates with members
+    // candidates whose members were counted
+    const uint32_t cand_seen = cand_over && !h.all_members ? c.cand_cap : h.cand;
     if (cand_over) {
         c.cand_cap = clamp_cap((double)h.cand * 1.125 + 1024);
         r.cand_per_grain = std::max(r.cand_per_grain, 1.125 * (double)h.cand / grains);
     }
-    // with too few candidate slots the member count covers only the first
-    // cand_cap candidates: size the members from the ratio as well
+    // with too few candidate slots the members had no buffer to overflow: size
+    // them from the ratio as well (all of them counted, the candidates' spare
+    // eighth is theirs too; from the first ones, with an eighth of its own)
     if (h.members > c.mem_cap || cand_over) {
         if (h.members > kMemCapMax) return false;
         const double per = cand_seen ? (double)h.members / (double)cand_seen : r.mem_per_cand;
-        r.mem_per_cand = std::max(r.mem_per_cand, 1.125 * per);
+        r.mem_per_cand = std::max(r.mem_per_cand, (cand_over && h.all_members ? 1.0 : 1.125) * per);
         c.mem_cap = clamp_cap(std::max((double)h.members * 1.125 + 1024,
                                        r.mem_per_cand * (double)c.cand_cap));
     }

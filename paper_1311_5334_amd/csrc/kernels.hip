@@ -2238,7 +2238,9 @@ __global__ void __launch_bounds__(kBlock) k_cand_list(DevPtrs d, Caps c, const u
         d.pass_pos[nwd] = off + tot;
         d.cnt->n_cand = off + tot;
     }
-    unsigned long long listed = 0;  // member entries of the listed candidates
+    // member entries, of candidates past the buffer's end too: a call that is
+    // run again is sized by them
+    unsigned long long listed = 0;
     for (uint32_t r0 = 0; r0 < tot; r0 += kCandList) {  // uniform
         uint32_t at = before - r0;  // wraps for the candidates of earlier rounds
 #pragma unroll
@@ -2249,10 +2251,11 @@ __global__ void __launch_bounds__(kBlock) k_cand_list(DevPtrs d, Caps c, const u
                                             (uint32_t)__ffs((int)bits) - 1u);
         __syncthreads();
         const uint32_t m = min(tot - r0, kCandList);
-        for (uint32_t i = threadIdx.x; i < m && off + r0 + i < c.cand_cap; i += kBlock) {
+        for (uint32_t i = threadIdx.x; i < m; i += kBlock) {
             const uint32_t s = 32u * kTile * blockIdx.x + s_list[i];
             const uint32_t n = d.seed_n[s];
             listed += n;
+            if (off + r0 + i >= c.cand_cap) continue;
             const uint2 pq = d.seeds[s];
             Cand cd;
             cd.p = pq.x;
