@@ -94,10 +94,10 @@ constexpr int kTunedCells[8][3] = {{
 TILE_TABLE = os.path.join(HERE, "csrc", "tile_table.h")
 # candidate values of each tile constant (see csrc/tile_table.h)
 TILE_SPACE = {
-    "EMT_COUNT_FETCH": (4, 6, 8),
-    "EMT_CHUNK_SEEDS": (512, 1024, 2048),
-    "EMT_COUNT_THREADS": (256, 512),
-    "EMT_COUNT_BLOCKS": (512, 1024),
+    "EMT_COUNT_FETCH": (3, 4, 6),
+    "EMT_CHUNK_SEEDS": (1024, 2048, 4096),
+    "EMT_COUNT_THREADS": (512, 768, 1024),
+    "EMT_COUNT_BLOCKS": (256, 512, 768),
     "EMT_COUNT_OCCUPANCY": (4, 6, 8),
     "EMT_MERGE_WIDE": (12, 16),
     "EMT_CELLS_PER_GRAIN": (4, 8),

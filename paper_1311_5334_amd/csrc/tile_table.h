@@ -2,11 +2,9 @@
 // the cell budget per grain, chosen by paper_1311_5334_amd/autotune.py
 // --tiles from timings of the whole path; -D on the compiler line overrides
 // each value.
-//   Against each value's neighbours, in ms a call for one c2 view, 8 c5 views
-//   and 16 c3 views (here 0.774, 20.39, 3.535): 3 or 6 slabs a step 0.783,
-//   20.56, 3.583 and 0.775, 20.36, 3.525; 1024 or 4096 seeds a chunk 0.777,
-//   20.48, 3.533 and 0.777, 20.60, 3.604; 768 workgroups of 512 threads 0.805,
-//   20.59, 3.624; 512 of 1024 at eight waves a SIMD 0.848, 22.75, 3.960.
+//   starting tiles {'EMT_COUNT_FETCH': 4, 'EMT_CHUNK_SEEDS': 2048, 'EMT_COUNT_THREADS': 768, 'EMT_COUNT_BLOCKS': 512, 'EMT_COUNT_OCCUPANCY': 6, 'EMT_MERGE_WIDE': 16, 'EMT_CELLS_PER_GRAIN': 4}: c2 0.771 ms, c5x8 20.128 ms, c3x16 3.569 ms
+//   chosen tiles {'EMT_COUNT_FETCH': 4, 'EMT_CHUNK_SEEDS': 2048, 'EMT_COUNT_THREADS': 768, 'EMT_COUNT_BLOCKS': 512, 'EMT_COUNT_OCCUPANCY': 6, 'EMT_MERGE_WIDE': 16, 'EMT_CELLS_PER_GRAIN': 4} (each constant's best one-at-a-time variation)
+//   13 builds timed
 #ifndef EMT_TILE_TABLE_H
 #define EMT_TILE_TABLE_H
 
