@@ -758,7 +758,6 @@ int batch_caps(const emt_ctx *ctx, unsigned long long n_total, uint32_t n_views,
                          4096, (unsigned long long)(ctx->seeds_per_grain * (double)c.n_total)));
     c.cand_cap = clamp_cap(ctx->cand_per_grain * (double)c.n_total);
     c.mem_cap = clamp_cap(ctx->mem_per_cand * (double)c.cand_cap);
-    c.few = few_grains(n_total, max_n, ctx->cfg.cyl_ext, ctx->last_seeds[size_class(c.n_total)]);
     const int wide = ctx->next_wide[size_class(c.n_total)];
     c.wide_rounds = wide > 0 ? wide : max_wide_rounds();
     *out = c;
@@ -977,14 +976,17 @@ int begin_views(emt_ctx *ctx, const emt_view_in *views, uint32_t n_views) {
     }
     // batch sizes (to the device) and capacity buckets (launch shapes)
     unsigned long long n_total = 0, n_cells = 0;
-    uint32_t max_n = 0;
+    uint32_t max_n = 0, with_grains = 0;
     for (uint32_t v = 0; v < n_views; ++v) {
         n_total += views[v].n_grains;
+        with_grains += views[v].n_grains ? 1u : 0u;
         n_cells += (unsigned long long)kCellsPerGrain * views[v].n_grains + kCellsBase + 1;
         max_n = std::max(max_n, views[v].n_grains);
     }
     Caps c{};
     if ((rc = batch_caps(ctx, n_total, n_views, max_n, &c))) return rc;
+    c.few = few_grains(n_total, with_grains, ctx->cfg.cyl_ext,
+                       ctx->last_seeds[size_class(c.n_total)]);
 
     // ensure the view tables exist before filling pinned staging
     if ((rc = ensure(ctx, c))) return rc;

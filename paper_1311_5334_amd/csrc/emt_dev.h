@@ -22,27 +22,38 @@ constexpr int kBlock = 256;
 constexpr uint32_t kCellsPerGrain = EMT_CELLS_PER_GRAIN;
 constexpr uint32_t kCellsBase = 4096;
 // Whether a call counts over the binned cells instead of line grids: those
-// cost 60 us and more for every view, which its seeds have to win back.
+// cost some microseconds for every view of many, and 60 for one alone, which
+// the seeds have to win back. So the line lies at the seeds of a view in the
+// mean, whatever the views' sizes.
 // seeds_per_grain: of the last call of its size, 0 if there was none.
 // Measured (call times in us, cells / line grids): 32 views of 1800 grains at
 // 1.5, 4.4, 10 and 30 per 1000 um^3 (123, 198, 441, 1314 thousand seeds a
 // view) 477 / 607, 828 / 856, 1475 / 1357, 3245 / 2181; 4 views of 7000 at 1.5,
 // 4.4 and 10 (1.1, 3.1, 6.9 million seeds in all) 290 / 318, 557 / 557, 1043 /
-// 726. Without a call before it, by grains: 48 views of 900 1201 / 1351, 3 of
-// 27 thousand at 11 2690 / 3911. Short finite cylinders find few grains: 27
-// thousand reaching 3 um 508 / 586, 20 um 640 / 630.
+// 726. One view of 35 thousand grains among 1000 of 300, 300 of 1200, 1000 of
+// 1200 and 100 of 1800 (23, 119, 110, 206 thousand a view) 2679 / 6122, 4039 /
+// 4806, 11090 / 13570, 2658 / 2733; a c2 view among 40 and 10 of 2000 (264, 469
+// thousand) 1588 / 1582, 1079 / 995; but a c5 view, whose lines are dearer over
+// cells, among 300 of 300 (86 thousand) 5760 / 5394. Without a call before it,
+// by grains: 48 views of 900 1201 / 1351, 3 of 27 thousand at 11 2690 / 3911.
+// Short finite cylinders look at few cells: one view of 27 thousand grains at
+// 1.2, 4.4 and 11 per 1000 um^3 reaching 3 um 592 / 713, 465 / 546, 765 / 704,
+// 15 um 732 / 831, 565 / 595, 971 / 757; of 60 thousand 3 um 1183 / 1435, 815 /
+// 921, 1503 / 1390, of 130 thousand at 4.4 and 11 1574 / 1837, 3238 / 2787.
 constexpr unsigned long long kFewGrains = 8192;
-constexpr uint32_t kFewViewGrains = 1024;
+constexpr unsigned long long kFewViewGrains = 1024;
 constexpr unsigned long long kFewGrainsShort = 65536;
 constexpr int kShortCylinder = 1000;
 constexpr double kFewSeeds = 2.5e6, kFewViewSeeds = 280e3;
-__host__ inline bool few_grains(unsigned long long n_grains, uint32_t largest_view, int cyl_ext,
+// n_views: those that have grains.
+__host__ inline bool few_grains(unsigned long long n_grains, uint32_t n_views, int cyl_ext,
                                 double seeds_per_grain) {
     if (cyl_ext >= 0 && cyl_ext < kShortCylinder && n_grains <= kFewGrainsShort) return true;
-    if (seeds_per_grain > 0.0)
-        return seeds_per_grain * (double)n_grains <= kFewSeeds ||
-               seeds_per_grain * (double)largest_view <= kFewViewSeeds;
-    return n_grains <= kFewGrains || largest_view <= kFewViewGrains;
+    if (seeds_per_grain > 0.0) {
+        const double seeds = seeds_per_grain * (double)n_grains;
+        return seeds <= kFewSeeds || seeds <= kFewViewSeeds * (double)n_views;
+    }
+    return n_grains <= kFewGrains || n_grains <= kFewViewGrains * n_views;
 }
 // Entries of the sorted-grain array past the last grain: the counting kernel
 // of those calls loads fixed groups of consecutive grains and may read (and
