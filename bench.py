@@ -38,7 +38,8 @@ OPS_PER_TEST = 18
 HBM_PEAK_GBS = 8000.0
 # the counting kernel's code and the tables that shape its work
 COUNT_KERNEL_SRCS = [os.path.join(ROOT, "paper_1311_5334_amd", "csrc", f)
-                     for f in ("kernels.hip", "cell_table.h", "tile_table.h")]
+                     for f in ("kernels.hip", "line_grid.h", "deal.h", "seed_rows.h",
+                               "cell_table.h", "line_table.h", "tile_table.h")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "count_traffic.json")
 VALU_FILE = os.path.join(ROOT, "profiles", "count_valu.json")
 BIN_BYTES_PER_GRAIN = 44

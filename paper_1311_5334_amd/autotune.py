@@ -248,7 +248,10 @@ def tune_tiles(prebuilt: str, report: str | None) -> int:
         chosen[k] = best_v
     lines = [f"starting tiles {start}: " + ", ".join(f"{w} {base[w]:.3f} ms" for w in WORKLOADS),
              f"chosen tiles {chosen} (each constant's best one-at-a-time variation)",
-             f"{len(times)} builds timed"]
+             f"{len(times)} builds timed; one value changed:"]
+    for tiles, res in times[1:]:
+        k = next(m for m in tiles if tiles[m] != start[m])
+        lines.append(f"  {k} {tiles[k]}: " + ", ".join(f"{w} {res[w]:.3f} ms" for w in WORKLOADS))
     write_tiles(TILE_TABLE, chosen, "\n".join("//   " + ln for ln in lines))
     print("wrote", TILE_TABLE, flush=True)
     if report:

@@ -802,19 +802,7 @@ __device__ __forceinline__ void wave_lds_sync() {
 }
 
 // ----------------------------------------------------------------- seeds
-//
-// One wave per anchor grain p (a sorted position); lanes take the (y, z)
-// rows of the cell box overlapping [g_p - (R-1), g_p + (R-1)]. Every grain q
-// of those rows at a higher sorted position with 0 < |g_q - g_p|^2 < R^2
-// makes a seed, stored with the lower input index first. A first pass counts
-// the seeds of every anchor, a scan turns the counts into offsets, and a
-// second pass writes them: no shared counter, and the seed list comes out in
-// anchor order, so each view's seeds are contiguous. Bound by VALU issue (the
-// count pass by itself, the write pass also by its partly written lines, 2.9 GB
-// for 1.3): finding an element's row by counting row ends instead of a search
-// over the row starts, cell bounds by reciprocals and the pair test in FP32
-// took 8 c5 views' passes from 2.9 to 2.45 ms, one c2 view's from 74 to 52 us.
-// The write pass puts an anchor's seeds in order in LDS first (kSeedStage).
+
 // The line class of direction d (up to the rounding at the bins' edges, where
 // both classes list the line's grains): its face, and its slopes' bins.
 __device__ __forceinline__ int line_face(int ax, int ay, int az) {
@@ -980,6 +968,19 @@ constexpr uint32_t kSeedWords = 64;  // one a lane: 4096 elements
 // 8 1.75 -> 1.45; 384: 7.1, 768: 6.3 but one c2 view 105 -> 113 us in all).
 constexpr uint32_t kSeedStage = 512;
 
+// One wave per anchor grain p (a sorted position); lanes take the (y, z)
+// rows of the cell box overlapping [g_p - (R-1), g_p + (R-1)]. Every grain q
+// of those rows at a higher sorted position with 0 < |g_q - g_p|^2 < R^2
+// makes a seed, stored with the lower input index first. A first pass counts
+// the seeds of every anchor and line class, a scan turns the counts into
+// offsets, and a second pass writes them: no shared counter, and the seed list
+// comes out by view, class and anchor. Bound by VALU issue (the count pass by
+// itself, the write pass also by its partly written lines, 7.8 GB for 5.2 GB of
+// seeds with 32 c5 views): finding an element's row by counting row ends instead
+// of a search over the row starts, cell bounds by reciprocals and the pair test
+// in FP32 took 8 c5 views' passes from 2.9 to 2.45 ms, one c2 view's from 74 to
+// 52 us. The write pass puts an anchor's seeds in order in LDS first
+// (kSeedStage).
 template <bool kWrite>
 __global__ void __launch_bounds__(kBlock) k_seeds(DevPtrs d, Caps c, Params P) {
     // per wave: for each row that has grains, the sorted position of its first
@@ -1366,7 +1367,12 @@ constexpr int kFetch = EMT_COUNT_FETCH;            // slabs walked per step
 constexpr int kCountBlock = EMT_COUNT_THREADS;     // threads of a workgroup
 constexpr int kCountWaves = kCountBlock / 64;
 constexpr uint32_t kChunkSeeds = EMT_CHUNK_SEEDS;  // most seeds a workgroup takes at a time
-constexpr uint32_t kApartSeeds = 50000000;         // seeds from which XCDs work apart
+// Seeds from which XCDs work apart. Apart / in turn, us a call: one c2 view (3.3 M
+// seeds) 729 / 720, four (12.8 M) 1793 / 1870, one c5 view (20 M) 3271 / 3394, 16
+// and 32 c3 views (26, 51 M) 3618 / 3688, 6482 / 6628, 3, 8 and 16 c5 views (61,
+// 162, 326 M) 8207 / 8672, 20930 / 22320, 42300 / 45000. In turn is the better
+// side for a single small view only; the line is well on the safe side of it.
+constexpr uint32_t kApartSeeds = 50000000;
 // at most 63 words are left in the queue before a step's are added, and a
 // test adds back at most one for each it takes
 constexpr uint32_t kQueue = 64u * (kFetch + 1);
@@ -3352,8 +3358,8 @@ void launch_find_grains(const uint8_t *img, const StackGeom &G, const GrainBufs 
 // from x = 255 on both are 0. So a pixel is one 24-bit multiply-add, and two
 // pixels share a saturating 16-bit subtraction and a byte permutation to pack
 // them: 14 instructions for four pixels. The output goes past the caches, which
-// the next frames' pixels can use. Calls on 52 M pixels 35.8 -> 32.8 us (kernel
-// 20.1 -> 16.9; a copy of as many bytes 13.2), on 210 M pixels 95.5 -> 86.5.
+// the next frames' pixels can use. Calls on 52 M pixels 38.2 -> 31.5 us (kernel
+// 20.3 -> 18.2; a copy of as many bytes 13.2), on 210 M pixels 95.5 -> 86.5.
 
 namespace {
 
